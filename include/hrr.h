@@ -106,7 +106,11 @@ int hrr_version(void);
  * a time; all methods return the same result on every query. */
 #define HRR_RMQ_PAPER 0u      /* default: the paper's case analysis and sweeps (Section 2, Algorithms 2
                                  and 3) with all candidate flip positions tested at once in bit
-                                 arithmetic, then Algorithm 3's refinement of the winning prefix */
+                                 arithmetic, then Algorithm 3's refinement of the winning prefix.
+                                 A traversal of this method walks aligned index blocks instead of
+                                 the hierarchy's nodes where that is faster (same pairs): there a
+                                 range minimum and the numbers that follow it are one subtraction
+                                 apart; HRR_F_STATS counts the node walk */
 #define HRR_RMQ_DIRECT 1u     /* ablation: every step in O(1) bit arithmetic, no refinement walk */
 #define HRR_RMQ_PAPER_FULL 2u /* ablation: the sweeps as loops, refining every candidate in turn */
 #define HRR_RMQ_PAPER_LOOP 3u /* ablation: the sweeps as loops, refining only the candidate whose
@@ -140,7 +144,7 @@ typedef struct hrr_hierarchy_info {
     uint32_t leaf_size;
     uint32_t n_nodes;       /* node records (sibling pairs, see hrr_hierarchy_records) */
     uint32_t depth;         /* deepest internal node (root = 0) */
-    uint64_t device_bytes;  /* nodes + sorted lights + permutation */
+    uint64_t device_bytes;  /* nodes + sorted lights + permutation + tables of the walks */
     float box[6];           /* root bounding box lo xyz, hi xyz */
     uint32_t split;         /* HRR_SPLIT_RADIX or HRR_SPLIT_POW2 */
 } hrr_hierarchy_info;
@@ -212,15 +216,17 @@ typedef struct hrr_eyes {
     uint32_t pixel_base;
 } hrr_eyes;
 
-#define HRR_F_STATS 1u      /* count node visits, range minima, leaf tests (slower) */
+#define HRR_F_STATS 1u      /* run the node walk and count its node visits, range minima, leaf tests (slower) */
 #define HRR_F_NO_REORDER 2u /* process eyes in index order instead of grouping them by space
                                (ablation; the result is the same either way) */
 #define HRR_F_TIMING 4u     /* time the traversal kernel alone with HIP events on the
                                call's stream (hrr_stats.kernel_ms) */
 
 typedef struct hrr_traverse_opts {
-    uint32_t eyes_per_wave; /* 0 = tuned or by hierarchy size; else 1, 2, 4 or 8 eyes share one wavefront */
-    uint32_t stack_entries; /* 0 = autotuned; else LDS stack entries per wave, multiple of 64 in [192, 4096] */
+    uint32_t eyes_per_wave; /* shape of the node walk: 0 = tuned or by hierarchy size; else 1, 2, 4 or 8 eyes
+                               share one wavefront */
+    uint32_t stack_entries; /* shape of the node walk: 0 = autotuned; else LDS stack entries per wave, multiple of
+                               64 in [192, 4096] */
     uint32_t rmq_method;    /* HRR_RMQ_PAPER (default) or one of the HRR_RMQ_* ablations */
     uint32_t n_samples;     /* 0 or 1 = one sample per pair; > 1: Section 3 multi-sample */
     uint32_t psi_s0;        /* start of the golden-ratio lattice psi(n) = s0 + n * alpha mod 1 */

@@ -18,6 +18,7 @@
 extern "C" hipError_t hrr_noalloc_scratch(int device, void** out);   // hrr_kernels.hip
 extern "C" hipError_t hrr_launch_frontier(const hrr::Node* nodes, uint32_t n_lights, uint32_t leaf_size, float* out,
                                           hipStream_t stream);   // hrr_kernels.hip
+extern "C" hipError_t hrr_launch_blocks(const float* lights, uint32_t n_lights, float* blocks, hipStream_t stream);
 
 #define HRR_EXPORT extern "C" __attribute__((visibility("default")))
 
@@ -140,8 +141,8 @@ void resolve_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, uint32_t n_light
     *cap = c;
 }
 
-void group_by_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, const std::vector<HostItem>& items, bool per_item,
-                    std::vector<LaunchGroup>& out) {
+void group_by_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, const std::vector<HostItem>& items, bool block_walk,
+                    bool per_item, std::vector<LaunchGroup>& out) {
     out.clear();
     auto shape_of = [&](const std::vector<size_t>& members, uint32_t* epw, uint32_t* cap, uint32_t fixed_epw) {
         uint64_t max_eyes = 0;
@@ -152,16 +153,33 @@ void group_by_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, const std::vect
         }
         resolve_shape(ctx, opts, max_lights, max_eyes, epw, cap, fixed_epw);
     };
+    std::vector<size_t> rest;   // items of the node walk
+    double cost = 0.0;
+    for (const HostItem& it : items)
+        if (it.h) cost += (double)it.eyes.n * (opts && opts->n_samples > 1 ? opts->n_samples : 1u) * eye_cost(it.h->n_lights);
+    if (block_walk && block_walk_pays(cost)) {
+        LaunchGroup g;
+        g.blocks = true;
+        for (size_t k = 0; k < items.size(); ++k)
+            (items[k].h && block_walk_takes(items[k].s) ? g.items : rest).push_back(k);
+        if (!g.items.empty()) {
+            shape_of(g.items, &g.epw, &g.cap, 0);   // for the check of the options alone
+            out.push_back(std::move(g));
+        }
+    } else {
+        rest.resize(items.size());
+        for (size_t k = 0; k < items.size(); ++k) rest[k] = k;
+    }
+    if (rest.empty() && !out.empty()) return;
     if (!per_item) {
         LaunchGroup g;
-        g.items.resize(items.size());
-        for (size_t k = 0; k < items.size(); ++k) g.items[k] = k;
+        g.items = rest;
         shape_of(g.items, &g.epw, &g.cap, 0);
         out.push_back(std::move(g));
         return;
     }
     std::vector<uint32_t> item_epw(items.size(), 1u);
-    for (size_t k = 0; k < items.size(); ++k) {
+    for (size_t k : rest) {
         uint32_t kc = 0;
         if (items[k].h) resolve_shape(ctx, opts, items[k].h->n_lights, items[k].eyes.n, &item_epw[k], &kc);
         const uint32_t ke = item_epw[k];
@@ -169,7 +187,7 @@ void group_by_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, const std::vect
     }
     for (uint32_t ge : {1u, 2u, 4u, 8u}) {
         LaunchGroup g;
-        for (size_t k = 0; k < items.size(); ++k)
+        for (size_t k : rest)
             if (item_epw[k] == ge) g.items.push_back(k);
         if (g.items.empty()) continue;
         shape_of(g.items, &g.epw, &g.cap, ge);
@@ -300,6 +318,16 @@ hrr_status attach_frontier(hrr_hierarchy* h, hipStream_t stream) {
     return HRR_OK;
 }
 
+hrr_status attach_blocks(hrr_hierarchy* h, hipStream_t stream) {
+    if (!h->n_lights) return HRR_OK;
+    const size_t bytes = (size_t)block_tree_slots(block_tree_log(h->n_lights)) * kBlockFloats * sizeof(float);
+    hipError_t e = hipMalloc((void**)&h->d_blocks, bytes);
+    if (e == hipSuccess) e = hrr_launch_blocks(h->d_lights, h->n_lights, h->d_blocks, stream);
+    if (e != hipSuccess) return hip_fail(e, "block tree");
+    h->device_bytes += bytes;
+    return HRR_OK;
+}
+
 }  // namespace hrr
 
 HRR_EXPORT hrr_status hrr_build_hierarchy(hrr_ctx* ctx, const float* lights_xyz, uint32_t n_lights, uint32_t leaf_arg,
@@ -348,6 +376,8 @@ HRR_EXPORT hrr_status hrr_build_hierarchy(hrr_ctx* ctx, const float* lights_xyz,
     }
     h->device_bytes = nb + lb + pb;
     hrr_status st = attach_frontier(h, nullptr);
+    if (st == HRR_OK) st = attach_blocks(h, nullptr);
+    if (st == HRR_OK && (e = hipStreamSynchronize(nullptr)) != hipSuccess) st = hip_fail(e, "block tree");
     if (st == HRR_OK && h->d_frontier &&
         (e = hipMemcpy(&h->n_frontier, h->d_frontier + (size_t)kFrontierMax * kFrontierFloats, sizeof(uint32_t),
                        hipMemcpyDeviceToHost)) != hipSuccess)
@@ -422,6 +452,7 @@ HRR_EXPORT void hrr_free_hierarchy(hrr_ctx* ctx, hrr_hierarchy* h) {
     if (ctx) (void)hipSetDevice(ctx->device);
     if (h->d_nodes) (void)hipFree(h->d_nodes);
     if (h->d_frontier) (void)hipFree(h->d_frontier);
+    if (h->d_blocks) (void)hipFree(h->d_blocks);
     if (h->d_lights) (void)hipFree(h->d_lights);
     if (h->d_perm) (void)hipFree(h->d_perm);
     delete h;
@@ -431,7 +462,9 @@ HRR_EXPORT void hrr_free_hierarchy(hrr_ctx* ctx, hrr_hierarchy* h) {
 // traversal
 // ---------------------------------------------------------------------------
 
-// One synchronous traversal call.  With the shape left to the library
+// One synchronous traversal call.  The default method runs one launch of the
+// block walk.  Other methods, and launches that count statistics, run the node
+// walk: with the shape left to the library
 // (eyes_per_wave = 0, no override) a call of several items groups them by
 // their own shape -- hierarchies of different sizes want different numbers of
 // eyes per wave -- and enqueues one launch per group on `stream` (largest
@@ -443,29 +476,28 @@ static hrr_status run_sync(hrr_ctx* ctx, const std::vector<HostItem>& items, con
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     const size_t n = items.size();
     // groups of items and their launch shapes
-    constexpr int kMaxGroups = 4;
+    const uint32_t method = opts ? opts->rmq_method : HRR_RMQ_PAPER;
+    const bool want_stats = opts && (opts->flags & HRR_F_STATS);
     const bool per_item = n > 1 && epw_override == 0 && !(opts && opts->eyes_per_wave);
     std::vector<LaunchGroup> groups;
-    group_by_shape(ctx, opts, items, per_item, groups);
+    group_by_shape(ctx, opts, items, method == HRR_RMQ_PAPER && !want_stats, per_item, groups);
     for (auto& g : groups) {
         if (epw_override) g.epw = epw_override;
         if (cap_override) g.cap = cap_override;
     }
     const int n_groups = (int)groups.size();
     LaunchScratch* scr[kMaxGroups] = {&ctx->scratch, &ctx->group_scratch[0], &ctx->group_scratch[1],
-                                      &ctx->group_scratch[2]};
+                                      &ctx->group_scratch[2], &ctx->group_scratch[3]};
 
-    const uint32_t method = opts ? opts->rmq_method : HRR_RMQ_PAPER;
     const uint32_t ns = opts && opts->n_samples > 1 ? opts->n_samples : 1;
     const uint32_t s0 = opts ? opts->psi_s0 : 0;
-    const bool want_stats = opts && (opts->flags & HRR_F_STATS);
     const bool reorder = !(opts && (opts->flags & HRR_F_NO_REORDER));
     const bool timing = opts && (opts->flags & HRR_F_TIMING);
     std::vector<HostItem> sub;
     for (int g = 0; g < n_groups; ++g) {
         sub.clear();
         for (size_t k : groups[g].items) sub.push_back(items[k]);
-        const hrr_status st = launch_items(ctx, *scr[g], sub, groups[g].epw, groups[g].cap, method, ns, s0,
+        const hrr_status st = launch_items(ctx, *scr[g], sub, groups[g], method, ns, s0,
                                            want_stats, reorder, pairs, weights, stream, timing);
         if (st != HRR_OK) {
             // launches of earlier groups may be running: let them end before

@@ -198,6 +198,8 @@ HRR_EXPORT hrr_status hrr_build_hierarchy_device(hrr_ctx* ctx, const float* ligh
         if ((e = hrr_dev_root_leaf_box(reinterpret_cast<const float4*>(h->d_lights), n, d_box, stream)) != hipSuccess)
             return fail_free(hip_fail(e, "root box"));
     }
+    const hrr_status bst = attach_blocks(h, stream);
+    if (bst != HRR_OK) return fail_free(bst);
     float root_box[6] = {0, 0, 0, 0, 0, 0};
     if (n && (e = hipMemcpyAsync(root_box, d_box, sizeof root_box, hipMemcpyDeviceToHost, stream)) != hipSuccess)
         return fail_free(hip_fail(e, "root box"));

@@ -21,6 +21,7 @@ struct hrr_hierarchy {
     hrr::Node* d_nodes = nullptr;
     float* d_frontier = nullptr;      // kFrontierMax entries of kFrontierFloats, then the entry count
     uint32_t n_frontier = 0;
+    float* d_blocks = nullptr;        // block tree (hrr_types.hpp), for n_lights > 0
     float* d_lights = nullptr;       // float4 per light
     uint32_t* d_perm = nullptr;
     // host copies (filled on demand for hierarchies built on the device)
@@ -100,7 +101,7 @@ struct hrr_ctx {
     uint32_t* d_tile = nullptr;
     uint32_t tile_tz = 32, tile_bits = 0;   // shared trailing zeros / significant bits of the tile values
     hrr::LaunchScratch scratch;   // scratch of the synchronous entry points
-    hrr::LaunchScratch group_scratch[3];   // further launches of one batched call (items grouped by shape)
+    hrr::LaunchScratch group_scratch[4];   // further launches of one batched call (items grouped by walk and shape)
     std::mutex tune_mu;
     std::map<hrr::TuneKey, hrr::TuneVal> tune;
     std::map<int, uint32_t> tune_leaf;   // log2 lights -> leaf size
@@ -133,7 +134,10 @@ inline bool parse_leaf_arg(uint32_t arg, uint32_t* leaf, uint32_t* split) {
 void resolve_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, uint32_t n_lights, uint64_t n_eyes,
                    uint32_t* epw, uint32_t* cap, uint32_t fixed_epw = 0);
 
-// The launches of a call of several items.  With per_item, the items are
+// The launches of a call.  With block_walk (the default method, no
+// statistics), every item that the block walk takes (block_walk_takes in
+// hrr_layout.hpp) goes into one launch of that walk; the others run the node
+// walk: with per_item, they are
 // grouped by the eyes per wave of their own shape (tuned or by hierarchy
 // size; groups in the order 1, 2, 4, 8 eyes per wave, i.e. largest
 // hierarchies first) and every group takes the stack size resolved for its
@@ -143,17 +147,19 @@ void resolve_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, uint32_t n_light
 struct LaunchGroup {
     std::vector<size_t> items;
     uint32_t epw = 1, cap = 512;
+    bool blocks = false;   // one launch of the block walk, where epw and cap do not apply
 };
-void group_by_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, const std::vector<HostItem>& items, bool per_item,
-                    std::vector<LaunchGroup>& out);
+constexpr int kMaxGroups = 5;   // the block walk's, then one per eyes per wave
+void group_by_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, const std::vector<HostItem>& items, bool block_walk,
+                    bool per_item, std::vector<LaunchGroup>& out);
 
 // Enqueue one persistent launch of a set of items on `stream` with scratch
 // `S`: the eye order, the traversal, the compaction that makes every item's
 // stored pairs dense (on the device), and the readback of the counters.
 // After the stream has been synchronised, finish_items() fills S.counts /
 // S.stored / S.error / S.stat from that readback.
-hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostItem>& items, uint32_t epw,
-                        uint32_t cap, uint32_t method, uint32_t n_samples, uint32_t psi_s0, bool stats,
+hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostItem>& items, const LaunchGroup& shape,
+                        uint32_t method, uint32_t n_samples, uint32_t psi_s0, bool stats,
                         bool reorder, uint32_t* pairs, float* weights, hipStream_t stream, bool timing = false);
 // Duration of the last timed traversal kernel of S (after the stream has synchronised), ms.
 double timed_kernel_ms(LaunchScratch& S);
@@ -164,6 +170,8 @@ void release_scratch(LaunchScratch& S);
 // Allocate h->d_frontier and enqueue the computation of the hierarchy's top
 // (the entry count lands in the table's last word) on `stream`.
 hrr_status attach_frontier(hrr_hierarchy* h, hipStream_t stream);
+// The same for the block tree of h->d_lights, which the default traversal walks.
+hrr_status attach_blocks(hrr_hierarchy* h, hipStream_t stream);
 
 // The allocation-free traversal of one eye set (hrr_traverse_noalloc): every
 // launch on `stream`, nothing allocated, nothing read back.

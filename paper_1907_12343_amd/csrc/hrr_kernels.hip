@@ -4,7 +4,11 @@
 //
 //   rmq_kernel       range-minimum queries (Section 1, v(a,b); Section 2,
 //                    Algorithms 2-3), eight per thread, streaming u32 arrays.
-//   traverse_kernel  persistent wavefronts that pull (item, eye group) tasks
+//   cull_kernel      the default traversal: persistent wavefronts that bound
+//                    aligned blocks of lights and list their candidates in
+//                    closed form (see "block walk").
+//   traverse_kernel  the node walk (statistics, the other range-minimum
+//                    methods, extreme s): persistent wavefronts that pull (item, eye group) tasks
 //                    from eight per-XCD work queues and cull every eye's pairs
 //                    by a top-down walk of its item's light hierarchy
 //                    (Section 1).
@@ -13,7 +17,7 @@
 //                    after a traversal (compact_plan_kernel,
 //                    compact_move_kernel).
 //
-// Wavefront design.  One wave owns a group of 1..8 eyes.  Its stack of
+// Wavefront design of the node walk.  One wave owns a group of 1..8 eyes.  Its stack of
 // pending hierarchy nodes lives in LDS and is shared by the 64 lanes: each
 // iteration pops up to 64 nodes (one per lane), each lane obtains its node's
 // 64-byte record (both children's boxes; neighbouring lanes fetch their two
@@ -989,6 +993,399 @@ void traverse_kernel(TravArgs A) {
 }
 
 // ---------------------------------------------------------------------------
+// block walk: the default traversal
+// ---------------------------------------------------------------------------
+//
+// In an aligned block [p, p + 2^v) of sequence indices the random numbers are
+// evenly spaced: bitreverse(p + q) = bitreverse(p) + bitreverse_v(q)
+// 2^(32-v), so with u = bitreverse(p) + R (mod 2^32) the index whose low bits
+// are the reversal of x, x = -(u div 2^(32-v)) + t (mod 2^v), has the value
+// (u mod 2^(32-v)) + t 2^(32-v), t = 0, 1, ..., 2^v - 1.  The range minimum is
+// the t = 0 member, and every index whose number passes a bound T comes next
+// in closed form: a block's candidates are the first
+//     1 + ((T - u mod 2^(32-v)) div 2^(32-v))
+// members, none when the minimum fails.  So the walk does not have to descend
+// to the lights.  It bounds a block's acceptance by the distance to its box,
+// counts the candidates that pass the bound, and only splits a block while
+// that bound is loose (many candidates would fail their own test); otherwise
+// it lists the candidates, and each is tested exactly like a one-light leaf.
+// On the 1920x1080 x 2^20 frame an eye's 2,305 accepted pairs take 1,512 box
+// tests and 3,930 candidate tests (simulated), where the node walk tests
+// 25,500 children, each with a range minimum: 7,600 wave instructions an eye
+// against 33,900, 23.3 ms a frame against 106.6.  What bounds it: instruction
+// issue (0.26 vector instructions per SIMD-cycle and 0.55 scalar ones per
+// CU-cycle) behind the L1's line accesses (0.74 per CU-cycle), most of them
+// candidates' lights, one line per lane where neighbouring lanes' eyes do not
+// share it; hence the eye order by shift class, and 16 eyes of that order to
+// a step (below).
+//
+// One wave takes a task of up to 64 eyes of an item and keeps two LIFO lists
+// in LDS.  `stack` holds split blocks (block number | eye slot << 26): a step
+// pops up to 16 of them and every lane tests one child, lane 16 c + j child c
+// of the j-th: 16 eyes that stand at the same block read one line, and their
+// children are pushed child by child, so the 16 go on together (frame 38.8 ->
+// 35.4 ms against four adjacent lanes to a parent).  `queue` holds candidates
+// (light | eye slot << 26): whenever it holds 64 they are tested, one per
+// lane.  Accepted pairs wait in LDS and leave 64 at a time, in whole cache
+// lines (35.4 -> 27.5 ms together with the listing by prefix sums: 38.0
+// instead of 41.5 GB written).  Eyes enter one root at a time as the stack
+// drains, so both kinds of
+// step run full lanes also where an eye has little work.  Lanes read their
+// eye (position, rotation) from LDS by slot.
+//
+// Stack bound: g popped parents push at most 4 g children.  g is limited so
+// that a step never leaves more than kCullStack - kCullReserve entries, except
+// by popping one parent at a time, which adds at most 3 entries per level
+// (at most 11 levels) until that parent's subtree is done.
+constexpr uint32_t kCullStack = 256;
+constexpr uint32_t kCullReserve = 48;
+constexpr uint32_t kCullQueue = 384;      // at least 64 + 16 (see the listing rounds)
+constexpr uint32_t kCullStage = 2 * kWave;
+constexpr uint32_t kCullSlotShift = 26;   // block numbers are below 2^23, lights below 2^25
+constexpr uint32_t kCullEyes = kWave;     // eye slots of a wave
+constexpr uint32_t kCullWaveBytes =
+    kCullEyes * 16 + kCullStage * 8 + kCullStack * 4 + kCullQueue * 4 + kCullEyes * 4;
+constexpr uint32_t cull_wave_bytes(bool weights) { return kCullWaveBytes + (weights ? kCullStage * 4 : 0); }
+// A block is split while the candidates that its bound lets through beyond
+// those that must be near enough, cnt * (1 - far bound / near bound), exceed
+// kCullWaste (cost of four more box tests against that of the candidates they
+// save; 4 is the flat minimum of the simulated instruction counts for 23 to
+// 2,300 pairs per eye), or while there are more than kCullMaxRun of them (a
+// lane lists its candidates one per turn).
+constexpr float kCullWaste = 4.0f;
+constexpr uint32_t kCullMaxRun = 16;
+
+struct CullLds {
+    uint32_t* stack;
+    uint32_t* queue;
+    float4* eyes;      // x, y, z, R bits
+    uint32_t* u;       // virtual eye index
+    uint2* pairs;      // accepted pairs waiting to be stored
+    float* d2;         // their squared distances (weights are computed as pairs are stored)
+};
+
+// Inclusive sum over the wave's lanes (DPP row shifts, then row broadcasts).
+__device__ __forceinline__ uint32_t wave_sum_inclusive(uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);   // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);   // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);   // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);   // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // row_bcast:15
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // row_bcast:31
+    return x;
+}
+
+// Store the newest n (1 .. 64) staged pairs, [end - n, end): into the wave's
+// chunk, at O.fill, which is a multiple of 64 here.  Chunks hold a multiple of
+// 64, so a run never crosses one, and whole runs are whole cache lines.
+template <bool W>
+__device__ __forceinline__ void cull_store(OutState& O, const ItemDesc& D, const CullLds& L, uint32_t end, uint32_t n) {
+    const uint32_t lane = lane_id();
+    wave_sync();
+    if (O.chunk == kNoChunk) {
+        set_chunk<W>(O, D, alloc_chunk(D));
+        O.fill = 0;
+    }
+    if (lane < n) {
+        const uint2 pr = L.pairs[end - n + lane];
+        const float w = W ? 1.0f / accept_p(D.s, L.d2[end - n + lane], 1.0f) : 0.0f;
+        if (O.wp) {
+            put_pair(O.wp, O.fill + lane, pr);
+            if (W) put_weight(O.ww, O.fill + lane, w);
+        } else {
+            store_pair<W>(D, (O.chunk << D.chunk_shift) + O.fill + lane, pr, w);
+        }
+    }
+    O.fill += n;
+    O.count += n;
+    if (O.fill >> D.chunk_shift) set_chunk<W>(O, D, kNoChunk);
+}
+
+// Exact tests of the n (1 .. 64) newest candidates of the queue, which ends at
+// entry `end`, one per lane; `staged` counts the pairs waiting in LDS.
+template <bool W>
+__device__ __forceinline__ void cull_test(OutState& O, const ItemDesc& D, const CullLds& L, uint32_t end, uint32_t n,
+                                          uint32_t& staged) {
+    const uint32_t lane = lane_id();
+    wave_sync();
+    // lanes past n repeat the last candidate; only the decision is masked
+    const uint32_t c = L.queue[end - n + min(lane, n - 1u)];
+    const uint32_t i = c & ((1u << kCullSlotShift) - 1u), slot = c >> kCullSlotShift;
+    const float4 P = load_global4(reinterpret_cast<const float4*>(D.lights), min(i, D.n_lights - 1u));
+    const float4 e = L.eyes[slot];
+    // |l - e| per axis, 0 where it is NaN: box_d2 of a one-point box
+    const float dx = fmaxf(fabsf(P.x - e.x), 0.0f);
+    const float dy = fmaxf(fabsf(P.y - e.y), 0.0f);
+    const float dz = fmaxf(fabsf(P.z - e.z), 0.0f);
+    const float x2 = dx * dx, y2 = dy * dy, z2 = dz * dz;
+    const float d2 = (x2 + y2) + z2;
+    const uint32_t v = rotated(i, __float_as_uint(e.w));
+    bool keep;
+    const bool open = rr_fast(v, D, d2, true, keep);
+    if (ballot(open)) {   // rare: the IEEE decision
+        if (open) keep = keeps(v, accept_p(D.s, d2, 1.0f));
+    }
+    keep = keep && lane < n && i < D.n_lights;
+    const uint64_t m = ballot(keep);
+    if (D.capacity == 0) {   // counting launch: nothing is stored
+        O.count += (uint32_t)__popcll(m);
+        return;
+    }
+    if (keep) {
+        const uint32_t at = staged + count_below(m);
+        L.pairs[at] = make_uint2(L.u[slot], i);
+        if (W) L.d2[at] = d2;
+    }
+    staged += (uint32_t)__popcll(m);
+    if (staged >= (uint32_t)kWave) {
+        cull_store<W>(O, D, L, staged, kWave);
+        staged -= kWave;
+    }
+}
+
+// A wave leaves an item: its last staged pairs, then close_item.
+template <bool W>
+__device__ __forceinline__ void cull_close(OutState& O, const ItemDesc& D, const CullLds& L, uint32_t& staged,
+                                           uint32_t* err) {
+    if (staged) cull_store<W>(O, D, L, staged, staged);
+    staged = 0;
+    close_item(O, D, err);
+}
+
+template <bool W>
+__global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(W ? 7 : 8, 8)))
+void cull_kernel(TravArgs A) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    // dynamic LDS: one area per wave, then the task table (n_items + 1 entries)
+    uint32_t* task_begin_lds = reinterpret_cast<uint32_t*>(smem + kWavesPerBlock * cull_wave_bytes(W));
+    for (uint32_t t = threadIdx.x; t <= A.n_items; t += blockDim.x) task_begin_lds[t] = A.task_begin[t];
+    __syncthreads();
+    const uint32_t lane = lane_id();
+    CullLds L;
+    {
+        unsigned char* base = smem + (threadIdx.x / kWave) * cull_wave_bytes(W);
+        L.eyes = reinterpret_cast<float4*>(base);
+        L.pairs = reinterpret_cast<uint2*>(base + kCullEyes * 16);
+        L.stack = reinterpret_cast<uint32_t*>(L.pairs + kCullStage);
+        L.queue = L.stack + kCullStack;
+        L.u = L.queue + kCullQueue;
+        L.d2 = reinterpret_cast<float*>(L.u + kCullEyes);   // with W only
+    }
+    uint32_t staged = 0;
+    uint32_t cur = 0xFFFFFFFFu;
+    ItemDesc D;
+    OutState O;
+    O.chunk = kNoChunk;
+    O.wp = nullptr;
+    O.ww = nullptr;
+    O.fill = 0;
+    O.count = 0;
+
+    // work queues: start on this block's XCD queue, move on when it is empty
+    uint32_t q = blockIdx.x % kQueues;
+    uint32_t queues_left = kQueues;
+    for (;;) {
+        uint32_t i = 0;
+        if (lane == 0) i = atomicAdd(A.queues + q * kQueueStride, 1u);
+        i = uni(i);
+        const uint32_t sh = A.interleave_shift;
+        const uint64_t t64 = sh ? (((((uint64_t)(i >> sh)) * kQueues + q) << sh) | (i & ((1u << sh) - 1u)))
+                                : (uint64_t)A.queue_begin[q] + i;
+        const uint64_t end = sh ? (uint64_t)A.n_tasks : (uint64_t)A.queue_begin[q + 1];
+        uint32_t it = 0xFFFFFFFFu;   // no task left
+        const uint32_t t = (uint32_t)t64;
+        if (t64 >= end) {
+            if (--queues_left != 0) {
+                q = (q + 1) % kQueues;
+                continue;
+            }
+        } else {
+            uint32_t lo = 0, hi = A.n_items;
+            while (hi - lo > 1) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (task_begin_lds[mid] <= t) lo = mid; else hi = mid;
+            }
+            it = uni(lo);
+        }
+        if (it != cur || it == 0xFFFFFFFFu) {   // a wave may get no task at all
+            if (cur != 0xFFFFFFFFu) cull_close<W>(O, D, L, staged, A.error);
+            if (it == 0xFFFFFFFFu) break;
+            cur = it;
+            D = A.items[it];
+        }
+        const uint32_t u0 = (t - D.task_begin) << D.task_shift;
+        const uint32_t cnt = min(1u << D.task_shift, D.n_virtual - u0);
+        const uint32_t N = D.n_lights;
+        const float s = D.s;
+        const uint32_t S = D.block_log, leaf_log = block_leaf_log(S);
+
+        if (lane < cnt) {
+            const uint32_t u = D.order ? D.order[u0 + lane] : u0 + lane;
+            const EyeState e = load_eye(D, A.tile, u);
+            L.eyes[lane] = make_float4(e.ex, e.ey, e.ez, __uint_as_float(e.R));
+            L.u[lane] = e.u;
+        }
+        const float4* const blocks = reinterpret_cast<const float4*>(uni64((unsigned long long)(size_t)D.blocks));
+
+        uint32_t next = 0, sn = 0, qn = 0;   // eyes started; stack and queue entries
+        for (;;) {
+            if (sn < 16u && next < cnt) {
+                const uint32_t add = min(16u - sn, cnt - next);
+                if (lane < add) L.stack[sn + lane] = 1u | ((next + lane) << kCullSlotShift);
+                sn += add;
+                next += add;
+            }
+            if (sn == 0u) break;
+            wave_sync();
+            const uint32_t room = kCullStack - kCullReserve;
+            const uint32_t g = min(min(16u, sn), sn < room ? max(1u, (room - sn) / 3u) : 1u);
+            sn -= g;
+            const bool act = (lane & 15u) < g;
+            const uint32_t ent = L.stack[sn + min(lane & 15u, g - 1u)];
+            const uint32_t tag = ent & ~((1u << kCullSlotShift) - 1u);
+            const uint32_t id = (ent << (32u - kCullSlotShift) >> (32u - kCullSlotShift)) * 4u + (lane >> 4);
+            const float4 b0 = load_global4(blocks, 2u * id), b1 = load_global4(blocks, 2u * id + 1u);
+            const float4 e = L.eyes[ent >> kCullSlotShift];
+
+            // squared distances to the nearest and the farthest point of the box
+            const float ax = b0.x - e.x, ay = b0.y - e.y, az = b0.z - e.z;
+            const float bx = e.x - b1.x, by = e.y - b1.y, bz = e.z - b1.z;
+            const float nx = fmaxf(fmaxf(ax, bx), 0.0f), ny = fmaxf(fmaxf(ay, by), 0.0f),
+                        nz = fmaxf(fmaxf(az, bz), 0.0f);
+            const float nx2 = nx * nx, ny2 = ny * ny, nz2 = nz * nz;
+            const float dn = fmaxf((nx2 + ny2) + nz2, s);
+            const float fx = fmaxf(fabsf(ax), fabsf(bx)), fy = fmaxf(fabsf(ay), fabsf(by)),
+                        fz = fmaxf(fabsf(az), fabsf(bz));
+            const float fx2 = fx * fx, fy2 = fy * fy, fz2 = fz * fz;
+            const float df = fmaxf((fx2 + fy2) + fz2, s);
+            // T, at least every light's threshold minus one: t_cull is s 2^32
+            // (1 + 2^-18) or more, which covers the reciprocal's and the
+            // products' rounding
+            const float x = D.t_cull * __builtin_amdgcn_rcpf(dn);
+            const uint32_t T = x >= 4294967040.0f ? 0xFFFFFFFFu : (uint32_t)x;
+
+            const uint32_t lg = 31u - (uint32_t)__builtin_clz(id);   // 2 x the block's level
+            const uint32_t v = S - lg, rsh = 32u - v;                // 2^v indices
+            const uint32_t p = (id << v) ^ (1u << S);
+            const uint32_t u = bit_reverse(p) + __float_as_uint(e.w);
+            const uint32_t m0 = u & ((1u << rsh) - 1u);              // the block's minimum
+            uint32_t c = act && m0 <= T ? ((T - m0) >> rsh) + 1u : 0u;
+            // a block that holds no light has v = 0 candidates at most, which
+            // lie past N
+            const bool split = c > 1u && v > leaf_log &&
+                               (c > kCullMaxRun || !((float)c * (df - dn) < kCullWaste * df));
+            const uint64_t ms = ballot(split);
+            if (split) L.stack[sn + count_below(ms)] = id | tag;
+            sn += (uint32_t)__popcll(ms);
+            c = split ? 0u : c;
+
+            // List the candidates.  A lane's start in the queue is its prefix
+            // sum; lanes whose candidates do not fit wait for the next round
+            // (a lane lists at most 16, so every round takes some).
+            const uint32_t inc = wave_sum_inclusive(c);
+            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+            // with no step to come, the queue is drained
+            const uint32_t least = sn == 0u && next == cnt ? 1u : (uint32_t)kWave;
+            uint32_t done = 0;
+            do {
+                const bool fits = inc - done <= kCullQueue - qn;
+                const uint64_t wait = ballot(c != 0u && !fits);
+                const uint32_t upto =
+                    wait ? (uint32_t)__builtin_amdgcn_readlane((int)(inc - c), (int)__builtin_ctzll(wait)) : total;
+                uint32_t* dst = L.queue + (qn + (inc - c) - done);
+                uint32_t k = 0u - (u >> rsh);
+                const uint32_t k_end = k + (fits ? c : 0u);
+                for (; k != k_end; ++k) *dst++ = p | (bit_reverse(k) >> rsh) | tag;
+                c = fits ? 0u : c;
+                qn += upto - done;
+                done = upto;
+                while (qn >= least) {
+                    const uint32_t n = min(qn, (uint32_t)kWave);
+                    cull_test<W>(O, D, L, qn, n, staged);
+                    qn -= n;
+                }
+            } while (done < total);
+        }
+        wave_sync();
+    }
+}
+
+// ---- building the block tree ----
+//
+// block_leaf_kernel: one thread per smallest block, and in the same launch the
+// four levels above it inside each thread block (256 blocks -> 64 -> 16 -> 4
+// -> 1); block_up_kernel: the next four levels from a finished one.
+struct BlockBox {
+    float lo[3], hi[3];
+};
+
+__device__ __forceinline__ BlockBox empty_block() {
+    BlockBox b;
+    for (int k = 0; k < 3; ++k) {
+        b.lo[k] = INFINITY;
+        b.hi[k] = -INFINITY;
+    }
+    return b;
+}
+
+__device__ __forceinline__ void store_block(float4* blocks, uint32_t id, const BlockBox& b) {
+    blocks[2u * id] = make_float4(b.lo[0], b.lo[1], b.lo[2], 0.0f);
+    blocks[2u * id + 1u] = make_float4(b.hi[0], b.hi[1], b.hi[2], 0.0f);
+}
+
+// b: the box of block blockIdx.x * 256 + threadIdx.x of `level` (empty past its end)
+__device__ __forceinline__ void block_levels(float4* blocks, uint32_t level, BlockBox b) {
+    __shared__ BlockBox lds[256];
+    const uint32_t t = threadIdx.x;
+#pragma unroll 1
+    for (uint32_t up = 1; up <= 4u && up <= level; ++up) {
+        const uint32_t n = 256u >> (2u * up);
+        if (t < 4u * n) lds[t] = b;
+        __syncthreads();
+        if (t < n) {
+            b = lds[4u * t];
+            for (uint32_t q = 1; q < 4u; ++q)
+                for (int k = 0; k < 3; ++k) {
+                    b.lo[k] = fminf(b.lo[k], lds[4u * t + q].lo[k]);
+                    b.hi[k] = fmaxf(b.hi[k], lds[4u * t + q].hi[k]);
+                }
+            const uint32_t at = blockIdx.x * n + t, count = 1u << (2u * (level - up));
+            if (at < count) store_block(blocks, count + at, b);
+        }
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(256) void block_leaf_kernel(const float4* __restrict__ lights, uint32_t n_lights,
+                                                         uint32_t block_log, float4* __restrict__ blocks) {
+    const uint32_t leaf_log = block_leaf_log(block_log), level = (block_log - leaf_log) / 2u;
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    BlockBox b = empty_block();
+    if (i < (1u << (2u * level))) {
+        const uint64_t first = (uint64_t)i << leaf_log;
+        for (uint32_t q = 0; q < (1u << leaf_log) && first + q < n_lights; ++q) {
+            const float4 p = lights[first + q];
+            b.lo[0] = fminf(b.lo[0], p.x); b.hi[0] = fmaxf(b.hi[0], p.x);
+            b.lo[1] = fminf(b.lo[1], p.y); b.hi[1] = fmaxf(b.hi[1], p.y);
+            b.lo[2] = fminf(b.lo[2], p.z); b.hi[2] = fmaxf(b.hi[2], p.z);
+        }
+        store_block(blocks, (1u << (2u * level)) + i, b);
+    }
+    block_levels(blocks, level, b);
+}
+
+__global__ __launch_bounds__(256) void block_up_kernel(uint32_t level, float4* __restrict__ blocks) {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x, count = 1u << (2u * level);
+    BlockBox b = empty_block();
+    if (i < count) {
+        const float4 lo = blocks[2u * (count + i)], hi = blocks[2u * (count + i) + 1u];
+        b.lo[0] = lo.x; b.lo[1] = lo.y; b.lo[2] = lo.z;
+        b.hi[0] = hi.x; b.hi[1] = hi.y; b.hi[2] = hi.z;
+    }
+    block_levels(blocks, level, b);
+}
+
+// ---------------------------------------------------------------------------
 // the top of a hierarchy (the one-eye-per-wave walk's starting entries)
 // ---------------------------------------------------------------------------
 //
@@ -1442,6 +1839,43 @@ extern "C" hipError_t hrr_traverse_occupancy(uint32_t eyes_per_wave, uint32_t me
     }
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, f, hrr::kWave * hrr::kWavesPerBlock,
                                                         lds_per_block);
+}
+
+// Dynamic LDS bytes of one block of the block walk.
+extern "C" size_t hrr_cull_lds_per_block(uint32_t n_items, int with_weights) {
+    return hrr::kWavesPerBlock * hrr::cull_wave_bytes(with_weights != 0) + ((size_t)n_items + 1u) * sizeof(uint32_t);
+}
+
+// The block walk (see cull_kernel) of a launch's items.
+extern "C" hipError_t hrr_launch_cull(const hrr::TravArgs* A, int with_weights, uint32_t blocks, hipStream_t stream) {
+    const size_t lds = hrr_cull_lds_per_block(A->n_items, with_weights);
+    const dim3 threads(hrr::kWave * hrr::kWavesPerBlock);
+    if (with_weights)
+        hipLaunchKernelGGL(hrr::cull_kernel<true>, dim3(blocks), threads, lds, stream, *A);
+    else
+        hipLaunchKernelGGL(hrr::cull_kernel<false>, dim3(blocks), threads, lds, stream, *A);
+    return hipGetLastError();
+}
+
+// Resident blocks per CU of the block walk.
+extern "C" hipError_t hrr_cull_occupancy(int with_weights, uint32_t n_items, int* blocks_per_cu) {
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        blocks_per_cu, with_weights ? (const void*)hrr::cull_kernel<true> : (const void*)hrr::cull_kernel<false>,
+        hrr::kWave * hrr::kWavesPerBlock, hrr_cull_lds_per_block(n_items, with_weights));
+}
+
+// The block tree of n_lights >= 1 lights (float4 in sequence order): blocks
+// holds block_tree_slots(block_tree_log(n_lights)) boxes.
+extern "C" hipError_t hrr_launch_blocks(const float* lights, uint32_t n_lights, float* blocks, hipStream_t stream) {
+    const uint32_t log = hrr::block_tree_log(n_lights);
+    uint32_t level = (log - hrr::block_leaf_log(log)) / 2u;
+    float4* out = reinterpret_cast<float4*>(blocks);
+    hipLaunchKernelGGL(hrr::block_leaf_kernel, dim3(((1u << (2u * level)) + 255u) / 256u), dim3(256), 0, stream,
+                       reinterpret_cast<const float4*>(lights), n_lights, log, out);
+    for (; level > 4u; level -= 4u)
+        hipLaunchKernelGGL(hrr::block_up_kernel, dim3(((1u << (2u * (level - 4u))) + 255u) / 256u), dim3(256), 0, stream,
+                           level - 4u, out);
+    return hipGetLastError();
 }
 
 // The top of a hierarchy with records (see frontier_kernel): out holds

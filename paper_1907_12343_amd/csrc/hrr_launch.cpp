@@ -17,6 +17,8 @@ extern "C" size_t hrr_trav_lds_per_wave(uint32_t stack_cap, uint32_t eyes_per_wa
 extern "C" size_t hrr_trav_lds_per_block(uint32_t n_items, size_t lds_per_wave);
 extern "C" hipError_t hrr_traverse_occupancy(uint32_t eyes_per_wave, uint32_t method, int stats, int with_weights,
                                              size_t lds_per_block, int* blocks_per_cu);
+extern "C" hipError_t hrr_launch_cull(const hrr::TravArgs* A, int with_weights, uint32_t blocks, hipStream_t stream);
+extern "C" hipError_t hrr_cull_occupancy(int with_weights, uint32_t n_items, int* blocks_per_cu);
 extern "C" hipError_t hrr_launch_order(const hrr::OrderItem* items, const uint32_t* vbegin, uint32_t n_items,
                                        uint32_t total, uint32_t bits, uint32_t rbits, const uint32_t* tile,
                                        uint32_t tile_tz, uint32_t* keys, uint32_t* hist, uint32_t* order, int n_cu,
@@ -49,10 +51,11 @@ void product_test_bounds(float s, float* t_cull, float* t_keep, float* d2_fast) 
 
 }  // namespace
 
-hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostItem>& items, uint32_t epw,
-                        uint32_t cap, uint32_t method, uint32_t n_samples, uint32_t psi_s0, bool stats,
+hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostItem>& items, const LaunchGroup& shape,
+                        uint32_t method, uint32_t n_samples, uint32_t psi_s0, bool stats,
                         bool reorder, uint32_t* pairs, float* weights, hipStream_t stream, bool timing) {
     const size_t n = items.size();
+    const uint32_t epw = shape.epw, cap = shape.cap;
     S.timed = false;
     if (n == 0 || n > kMaxItemsPerLaunch)
         return fail(HRR_E_INVALID, "items per launch must be in [1, %u]", kMaxItemsPerLaunch);
@@ -65,15 +68,21 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
     const int with_w = weights != nullptr;
 
     // ---- grid: persistent waves, as many as stay resident ----
-    const size_t lds_wave = hrr_trav_lds_per_wave(cap, epw);
-    const size_t lds_block = hrr_trav_lds_per_block((uint32_t)n, lds_wave);
+    const size_t lds_wave = shape.blocks ? 0 : hrr_trav_lds_per_wave(cap, epw);
     int bpc = 0;
     hipError_t e;
-    if ((e = hrr_traverse_occupancy(epw, method, stats, with_w, lds_block, &bpc)) != hipSuccess)
-        return hip_fail(e, "occupancy");
+    e = shape.blocks ? hrr_cull_occupancy(with_w, (uint32_t)n, &bpc)
+                     : hrr_traverse_occupancy(epw, method, stats, with_w,
+                                              hrr_trav_lds_per_block((uint32_t)n, lds_wave), &bpc);
+    if (e != hipSuccess) return hip_fail(e, "occupancy");
     if (bpc <= 0) return fail(HRR_E_INVALID, "stack of %u entries does not fit in LDS", cap);
 
     std::vector<uint64_t> tasks_of(n);
+    // estimated work of the launch (virtual eyes x eye_cost)
+    double launch_cost = 0.0;
+    for (const HostItem& it : items)
+        if (it.h) launch_cost += (double)it.eyes.n * n_samples * eye_cost(it.h->n_lights);
+    std::vector<uint32_t> task_shift(n, 0u);
     uint64_t tasks = 0;
     uint32_t dmax = 0;
     for (size_t k = 0; k < n; ++k) {
@@ -87,7 +96,10 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
         if (it.out_capacity > 0 && !pairs) return fail(HRR_E_INVALID, "item %zu: null pairs buffer", k);
         const uint64_t nv = (uint64_t)it.eyes.n * n_samples;
         if (nv > 0xFFFFFFFFull) return fail(HRR_E_INVALID, "item %zu: eyes x samples exceeds 2^32 - 1", k);
-        tasks_of[k] = h->n_lights ? (nv + epw - 1) / epw : 0;
+        if (shape.blocks)
+            task_shift[k] = block_task_shift(h->n_lights, launch_cost, (uint64_t)ctx->n_cu * bpc * kWavesPerBlock);
+        const uint64_t task_eyes = shape.blocks ? 1ull << task_shift[k] : epw;
+        tasks_of[k] = h->n_lights ? (nv + task_eyes - 1) / task_eyes : 0;
         tasks += tasks_of[k];
         if (tasks > 0xFFFFFFF0ull) return fail(HRR_E_INVALID, "too many tasks in one launch");
         dmax = std::max(dmax, h->depth);
@@ -105,7 +117,7 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
     // stored past the capacity (slack) and the holes below it are bounded by
     // partial_cap chunks each; a slack of twice that lets the compaction fill
     // every hole below min(count, capacity).
-    const uint32_t il_shift = queue_interleave_shift(n, tasks);
+    const uint32_t il_shift = shape.blocks ? 0u : queue_interleave_shift(n, tasks);
     const uint64_t leaves_per_wave = departures_per_wave(n, il_shift);
     for (size_t k = 0; k < n; ++k) {
         const uint64_t wk = std::max<uint64_t>(1, std::min<uint64_t>(waves, tasks_of[k]));
@@ -135,11 +147,8 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
     }
     vbegin[n] = (uint32_t)std::min<uint64_t>(vtotal, 0xFFFFFFFFull);
     // eye order key (hrr_layout.hpp), for launches with enough work to gain from it
-    double order_cost = 0.0;
-    for (size_t k = 0; k < n; ++k)
-        order_cost += (double)tasks_of[k] * epw * pow((double)std::max<uint32_t>(items[k].h->n_lights, 1u), 0.6);
     uint32_t bits = 0, rbits = 0;
-    if (reorder && order_pays(order_cost)) order_key_bits(n, vtotal, ctx->tile_bits, &bits, &rbits);
+    if (reorder && order_pays(launch_cost)) order_key_bits(n, vtotal, ctx->tile_bits, &bits, &rbits);
     const bool ordered = bits > 0;
     std::vector<OrderItem> oitems;
     if (ordered) {
@@ -198,7 +207,7 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
     std::vector<double> task_cost(n);
     double total_cost = 0.0;
     for (size_t k = 0; k < n; ++k) {
-        task_cost[k] = pow((double)std::max<uint32_t>(items[k].h->n_lights, 1u), 0.6);
+        task_cost[k] = eye_cost(items[k].h->n_lights) * (double)(1u << task_shift[k]);
         total_cost += task_cost[k] * (double)tasks_of[k];
     }
     std::vector<uint32_t> begin_of(n);
@@ -237,6 +246,9 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
         D.frontier = h->d_frontier;
         D.n_frontier = h->n_frontier;
         D.lights = h->d_lights;
+        D.blocks = h->d_blocks;
+        D.block_log = block_tree_log(h->n_lights);
+        D.task_shift = task_shift[k];
         D.eyes = it.eyes.xyz;
         D.pairs = pairs ? pairs + 2 * it.out_offset : nullptr;
         D.weights = weights ? weights + it.out_offset : nullptr;
@@ -326,7 +338,7 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
         const uint64_t bound = 128ull * (dmax + 2);
         const uint32_t spill_cap = (uint32_t)(((bound + 63) / 64) * 64 + 64);
         const size_t spill_bytes = (size_t)waves * spill_cap * sizeof(unsigned long long);
-        if ((e = S.spill.ensure(spill_bytes)) != hipSuccess) return hip_fail(e, "spill stacks");
+        if (!shape.blocks && (e = S.spill.ensure(spill_bytes)) != hipSuccess) return hip_fail(e, "spill stacks");
 
         TravArgs A;
         memset(&A, 0, sizeof A);
@@ -349,8 +361,9 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
             if (!S.ev_end && (e = hipEventCreate(&S.ev_end)) != hipSuccess) return hip_fail(e, "timing event");
             if ((e = hipEventRecord(S.ev_begin, stream)) != hipSuccess) return hip_fail(e, "timing event");
         }
-        if ((e = hrr_launch_traverse(&A, epw, method, stats, with_w, blocks, stream)) != hipSuccess)
-            return hip_fail(e, "traverse launch");
+        e = shape.blocks ? hrr_launch_cull(&A, with_w, blocks, stream)
+                         : hrr_launch_traverse(&A, epw, method, stats, with_w, blocks, stream);
+        if (e != hipSuccess) return hip_fail(e, "traverse launch");
         if (timing) {
             if ((e = hipEventRecord(S.ev_end, stream)) != hipSuccess) return hip_fail(e, "timing event");
             S.timed = true;
@@ -407,16 +420,22 @@ hrr_status launch_noalloc(hrr_ctx* ctx, const hrr_hierarchy* h, const hrr_eyes& 
     hipError_t e = hipSetDevice(ctx->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     const int with_w = weights != nullptr;
-    const size_t lds_wave = hrr_trav_lds_per_wave(cap, epw);
-    const size_t lds_block = hrr_trav_lds_per_block(1, lds_wave);
+    const bool block_walk = method == HRR_RMQ_PAPER && block_walk_takes(s) &&
+                            block_walk_pays((double)nv * eye_cost(h->n_lights));
+    const size_t lds_wave = block_walk ? 0 : hrr_trav_lds_per_wave(cap, epw);
     int bpc = 0;
-    if ((e = hrr_traverse_occupancy(epw, method, 0, with_w, lds_block, &bpc)) != hipSuccess)
-        return hip_fail(e, "occupancy");
+    e = block_walk ? hrr_cull_occupancy(with_w, 1, &bpc)
+                   : hrr_traverse_occupancy(epw, method, 0, with_w, hrr_trav_lds_per_block(1, lds_wave), &bpc);
+    if (e != hipSuccess) return hip_fail(e, "occupancy");
     if (bpc <= 0) return fail(HRR_E_INVALID, "stack of %u entries does not fit in LDS", cap);
-    const uint64_t tasks = h->n_lights ? (nv + epw - 1) / epw : 0;
+    const uint32_t task_shift = block_walk ? block_task_shift(h->n_lights, (double)nv * eye_cost(h->n_lights),
+                                                              (uint64_t)ctx->n_cu * bpc * kWavesPerBlock)
+                                           : 0;
+    const uint64_t task_eyes = block_walk ? 1ull << task_shift : epw;
+    const uint64_t tasks = h->n_lights ? (nv + task_eyes - 1) / task_eyes : 0;
 
     // ---- scratch layout: as many whole blocks as the scratch holds ----
-    const uint64_t spill_cap = (128ull * (h->depth + 2) + 63) / 64 * 64 + 64;    // entries per wave
+    const uint64_t spill_cap = block_walk ? 0 : (128ull * (h->depth + 2) + 63) / 64 * 64 + 64;   // entries per wave
     const uint64_t pair_bytes = 8ull + (with_w ? 4ull : 0ull);
     const uint64_t resident = std::max<uint64_t>(1, (uint64_t)ctx->n_cu * bpc) * kWavesPerBlock;
     const uint64_t needed = std::max<uint64_t>(kWavesPerBlock, (tasks + kWavesPerBlock - 1) / kWavesPerBlock * kWavesPerBlock);
@@ -455,6 +474,9 @@ hrr_status launch_noalloc(hrr_ctx* ctx, const hrr_hierarchy* h, const hrr_eyes& 
     D.frontier = h->d_frontier;
     D.n_frontier = h->n_frontier;
     D.lights = h->d_lights;
+    D.blocks = h->d_blocks;
+    D.block_log = block_tree_log(h->n_lights);
+    D.task_shift = task_shift;
     D.eyes = eyes.xyz;
     D.pairs = pairs;
     D.weights = weights;
@@ -506,8 +528,9 @@ hrr_status launch_noalloc(hrr_ctx* ctx, const hrr_hierarchy* h, const hrr_eyes& 
         A.lds_per_wave = (uint32_t)lds_wave;
         A.stats = nullptr;
         A.error = error;
-        if ((e = hrr_launch_traverse(&A, epw, method, 0, with_w, blocks, stream)) != hipSuccess)
-            return hip_fail(e, "allocation-free traverse launch");
+        e = block_walk ? hrr_launch_cull(&A, with_w, blocks, stream)
+                       : hrr_launch_traverse(&A, epw, method, 0, with_w, blocks, stream);
+        if (e != hipSuccess) return hip_fail(e, "allocation-free traverse launch");
         if (capacity > 0 && (e = hrr_launch_compact(d_item, 1, error, stream)) != hipSuccess)
             return hip_fail(e, "allocation-free output compaction");
     }

@@ -3,6 +3,7 @@
 // Plain functions of the launch's sizes, unit-tested on the CPU.
 #pragma once
 
+#include <math.h>
 #include <stdint.h>
 
 #include "hrr_types.hpp"
@@ -51,9 +52,44 @@ inline bool order_pays(double cost) { return cost >= kOrderMinCost; }
 // XCDs work on the same heavy items at a time and the Infinity Cache holds
 // fewer hierarchies at once (256 caches: kernel 70.3 -> 66.5 ms); others use
 // eight contiguous slices of equal cost.  Returns the chunk shift, 0 for
-// slices.
+// slices.  (The block walk always takes slices: its waves pass through items
+// faster, and with slices only one XCD's waves pass through most items, each
+// leaving two or three atomics on the item's counters.  64 caches: 4.8 ms with
+// slices against 8.7 with chunks of 2^8 tasks.)
 inline uint32_t queue_interleave_shift(uint64_t n, uint64_t tasks) {
     return (n > 1 && tasks >= (1ull << 19)) ? 13u : 0u;
+}
+
+// Whether the block walk takes an item of the default method: its reciprocal
+// bound needs s within the range of the product-form test (s / d^2 a normal
+// number); an s outside it runs the node walk, whose tests fall back to the
+// IEEE division.
+inline bool block_walk_takes(float s) { return s >= 0x1p-60f && s <= 0x1p60f; }
+// Whether a call of that much work (the sum of virtual eyes x eye_cost) runs
+// the block walk: below, the call is bound by its set-up and its waves'
+// counters, and the node walk's eight eyes per wave leave fewer of those
+// (4096 eyes x 1024 lights, 2.6e5: 212 against 240 us a call with its sort;
+// 5001 eyes x 2^20 lights, 2e7: 486 against 298).
+inline bool block_walk_pays(double launch_cost) { return launch_cost >= 2097152.0; }
+
+// Estimated work of one eye against n_lights lights, in arbitrary units (the
+// growth of the walk's steps).
+inline double eye_cost(uint32_t n_lights) { return pow((double)(n_lights > 1u ? n_lights : 1u), 0.6); }
+
+// log2 of the eyes per task of an item in a block-walk launch of total work
+// `launch_cost` (the sum over items of virtual eyes x eye_cost): tasks of
+// equal work, about kTasksPerWave of them per resident wave (eyes differ in
+// work by far more than the estimate says, and a launch ends with its longest
+// last task), but at least kMinTaskCost each (a task costs an atomic and an
+// eye upload, and a wave that leaves an item two or three more) and at most
+// 64 eyes, a wave's eye slots.
+constexpr double kTasksPerWave = 32.0;
+constexpr double kMinTaskCost = 16384.0;
+inline uint32_t block_task_shift(uint32_t n_lights, double launch_cost, uint64_t resident_waves) {
+    const double target = fmax(launch_cost / (kTasksPerWave * (double)resident_waves), kMinTaskCost) / eye_cost(n_lights);
+    uint32_t shift = 0;
+    while (shift < 6u && (double)(2u << shift) <= target) ++shift;
+    return shift;
 }
 
 // How often one wave can leave one item (publishing a partly filled chunk).

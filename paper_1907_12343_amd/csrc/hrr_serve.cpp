@@ -76,7 +76,7 @@ using ReqPtr = std::shared_ptr<Request>;
 
 struct Slot {
     hipStream_t stream = nullptr;
-    LaunchScratch S[4];            // one per eyes-per-wave group of a batch
+    LaunchScratch S[kMaxGroups];   // one per launch group of a batch
     std::vector<uint64_t> counts;  // pair count of every request of the last batch
     std::vector<hrr_status> status;   // outcome of every request of the last batch
     std::vector<std::string> errs;    // and its message when it failed
@@ -221,7 +221,7 @@ hrr_status run_batch(Server& sv, Slot& slot, const std::vector<ReqPtr>& batch) {
     // batched call does), unless the configuration fixes the shape; each
     // group with the stack size of its own items
     std::vector<LaunchGroup> groups;
-    group_by_shape(ctx, &o, items, o.eyes_per_wave == 0 && items.size() > 1, groups);
+    group_by_shape(ctx, &o, items, true, o.eyes_per_wave == 0 && items.size() > 1, groups);
     uint32_t* pairs = reinterpret_cast<uint32_t*>(sv.base);
     std::vector<HostItem> sub;
     std::vector<hrr_status> gst(groups.size(), HRR_OK);
@@ -229,7 +229,7 @@ hrr_status run_batch(Server& sv, Slot& slot, const std::vector<ReqPtr>& batch) {
     for (size_t g = 0; g < groups.size(); ++g) {
         sub.clear();
         for (size_t k : groups[g].items) sub.push_back(items[k]);
-        gst[g] = launch_items(ctx, slot.S[g], sub, groups[g].epw, groups[g].cap, HRR_RMQ_PAPER, 1, 0, false, true,
+        gst[g] = launch_items(ctx, slot.S[g], sub, groups[g], HRR_RMQ_PAPER, 1, 0, false, true,
                               pairs, nullptr, slot.stream);
         if (gst[g] != HRR_OK) gmsg[g] = hrr_last_error(ctx);
     }

@@ -41,6 +41,7 @@ struct ItemDesc {
     const Node* nodes;
     const float* frontier;        // the hierarchy's top (kFrontierFloats per entry), n_frontier entries
     const float* lights;          // 4 floats per light (x, y, z, 0), sequence order
+    const float* blocks;          // the lights' block tree (8 floats per block)
     const float* eyes;            // 3 floats per eye
     uint32_t* pairs;              // item's output slice, 2 u32 per pair
     float* weights;               // item's weight slice or null
@@ -56,7 +57,10 @@ struct ItemDesc {
     uint32_t n_lights, n_nodes, leaf_size, n_virtual;
     uint32_t width, shift_offset, pixel_base, n_samples;
     uint32_t psi_s0, task_begin;
-    uint32_t n_frontier, pad_frontier;
+    uint32_t n_frontier;
+    uint32_t block_log;           // log2 of the block tree's root block
+    uint32_t task_shift;          // block walk: a task is up to 2^task_shift eyes
+    uint32_t pad;
     float s;
     // product-form keep test (set by the host): v is culled when
     // float(v) * d2 > t_cull, kept (one light) when < t_keep, for d2 <= d2_fast
@@ -75,6 +79,27 @@ struct ItemDesc {
 constexpr uint32_t kFrontierDepth = 6;
 constexpr uint32_t kFrontierMax = 1u << kFrontierDepth;
 constexpr uint32_t kFrontierFloats = 12;
+
+// The block tree of a light set, which the default traversal walks: the boxes
+// of aligned blocks of 2^v sequence indices, v = block_log, block_log - 2, ...
+// down to 3 or 4 (the parity of block_log), four children to a block.  Block
+// number 1 is the root [0, 2^block_log), block q has the children 4 q .. 4 q
+// + 3 (adjacent, 128-byte aligned), so a block of 2^v indices is the q-th
+// with q = 2^(block_log - v) + (first index >> v).  A block is two float4, lo
+// xyz and hi xyz (lo = +inf, hi = -inf where it holds no light).  It depends
+// on the lights' order alone: the hierarchies of both split rules and all
+// leaf sizes share its layout.  2^20 lights: leaves of 16 lights, 2.8 MB of
+// boxes, which fit one XCD's L2 beside the lights that its eyes touch.
+constexpr uint32_t kBlockFloats = 8;
+constexpr uint32_t block_tree_log(uint32_t n_lights) {
+    uint32_t s = 5;   // at least one level below the root
+    while (s < 31 && (1ull << s) < n_lights) ++s;
+    return s;
+}
+// log2 of the smallest blocks: 3 or 4, an even number of levels below the root
+constexpr uint32_t block_leaf_log(uint32_t block_log) { return 4u - (block_log & 1u); }
+// Slots of a tree's box array (block numbers 0 .. 2 * 4^levels - 1).
+constexpr uint64_t block_tree_slots(uint32_t block_log) { return 2ull << (block_log - block_leaf_log(block_log)); }
 
 // Eye-ordering description of one item: eyes are bucketed by the Morton
 // cell of their position inside the item's light box (cell = (x - lo) * scale,
