@@ -82,10 +82,7 @@ void DevBuf::release() {
 }
 
 void release_scratch(LaunchScratch& S) {
-    S.items.release();
-    S.task_begin.release();
-    S.counters.release();
-    S.misc.release();
+    S.tables.release();
     S.spill.release();
     S.partials.release();
     S.plan.release();
@@ -94,9 +91,6 @@ void release_scratch(LaunchScratch& S) {
     S.order_keys.release();
     S.order_idx.release();
     S.order_hist.release();
-    S.order_items.release();
-    S.order_vbegin.release();
-    S.queues.release();
     if (S.h_pinned) (void)hipHostFree(S.h_pinned);
     S.h_pinned = nullptr;
     S.h_pinned_n = 0;
@@ -154,10 +148,7 @@ void group_by_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, const std::vect
         resolve_shape(ctx, opts, max_lights, max_eyes, epw, cap, fixed_epw);
     };
     std::vector<size_t> rest;   // items of the node walk
-    double cost = 0.0;
-    for (const HostItem& it : items)
-        if (it.h) cost += (double)it.eyes.n * (opts && opts->n_samples > 1 ? opts->n_samples : 1u) * eye_cost(it.h->n_lights);
-    if (block_walk && block_walk_pays(cost)) {
+    if (block_walk) {
         LaunchGroup g;
         g.blocks = true;
         for (size_t k = 0; k < items.size(); ++k)

@@ -70,8 +70,8 @@ struct ItemMeta {
 // Per-launch device scratch: one set per stream slot so that concurrent
 // launches (the server) never share queue heads or counters.
 struct LaunchScratch {
-    DevBuf items, task_begin, counters, misc, spill, partials, plan, slack_pairs, slack_weights;
-    DevBuf order_keys, order_idx, order_hist, order_items, order_vbegin, queues;
+    DevBuf tables, spill, partials, plan, slack_pairs, slack_weights;
+    DevBuf order_keys, order_idx, order_hist;
     std::vector<ItemDesc> h_items;
     std::vector<uint32_t> h_task_begin;
     std::vector<unsigned long long> h_partial_off;   // per item, first entry in `partials`
@@ -81,6 +81,7 @@ struct LaunchScratch {
     size_t n_items = 0;
     bool with_weights = false;
     bool stats = false;
+    bool dense = false;   // the launch wrote its output dense, without compaction
     // results of finish_items
     std::vector<unsigned long long> counts;    // true pairs per item
     std::vector<unsigned long long> stored;    // valid pairs stored at the front of each slice

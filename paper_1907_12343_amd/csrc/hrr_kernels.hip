@@ -1040,12 +1040,14 @@ void traverse_kernel(TravArgs A) {
 constexpr uint32_t kCullStack = 256;
 constexpr uint32_t kCullReserve = 48;
 constexpr uint32_t kCullQueue = 384;      // at least 64 + 16 (see the listing rounds)
-constexpr uint32_t kCullStage = 2 * kWave;
+constexpr uint32_t kCullStage = 2 * kWave;        // staged pairs: chunked output
+constexpr uint32_t kCullStageDense = 8 * kWave;   // ... dense output (see DENSE)
 constexpr uint32_t kCullSlotShift = 26;   // block numbers are below 2^23, lights below 2^25
 constexpr uint32_t kCullEyes = kWave;     // eye slots of a wave
-constexpr uint32_t kCullWaveBytes =
-    kCullEyes * 16 + kCullStage * 8 + kCullStack * 4 + kCullQueue * 4 + kCullEyes * 4;
-constexpr uint32_t cull_wave_bytes(bool weights) { return kCullWaveBytes + (weights ? kCullStage * 4 : 0); }
+constexpr uint32_t cull_wave_bytes(bool weights, bool dense) {
+    return kCullEyes * 16 + kCullStack * 4 + kCullQueue * 4 + kCullEyes * 4 +
+           (dense ? kCullStageDense : kCullStage) * (weights ? 12u : 8u);
+}
 // A block is split while the candidates that its bound lets through beyond
 // those that must be near enough, cnt * (1 - far bound / near bound), exceed
 // kCullWaste (cost of four more box tests against that of the candidates they
@@ -1101,9 +1103,29 @@ __device__ __forceinline__ void cull_store(OutState& O, const ItemDesc& D, const
     if (O.fill >> D.chunk_shift) set_chunk<W>(O, D, kNoChunk);
 }
 
+// Dense output: the n staged pairs go to positions [base, base + n).
+template <bool W>
+__device__ __forceinline__ void cull_store_at(const ItemDesc& D, const CullLds& L, unsigned long long base, uint32_t n) {
+    wave_sync();
+    for (uint32_t k = lane_id(); k < n; k += (uint32_t)kWave) {
+        const unsigned long long at = base + k;
+        if (at >= D.capacity) break;
+        put_pair(reinterpret_cast<uint2*>(D.pairs), at, L.pairs[k]);
+        if (W) put_weight(D.weights, at, 1.0f / accept_p(D.s, L.d2[k], 1.0f));
+    }
+    wave_sync();
+}
+
+// Dense output: the next n positions of the item.
+__device__ __forceinline__ unsigned long long take_positions(const ItemDesc& D, unsigned long long n) {
+    unsigned long long base = 0;
+    if (lane_id() == 0) base = atomicAdd(D.counters + CNT_PAIRS, n);
+    return uni64(base);
+}
+
 // Exact tests of the n (1 .. 64) newest candidates of the queue, which ends at
 // entry `end`, one per lane; `staged` counts the pairs waiting in LDS.
-template <bool W>
+template <bool W, bool DENSE>
 __device__ __forceinline__ void cull_test(OutState& O, const ItemDesc& D, const CullLds& L, uint32_t end, uint32_t n,
                                           uint32_t& staged) {
     const uint32_t lane = lane_id();
@@ -1137,36 +1159,58 @@ __device__ __forceinline__ void cull_test(OutState& O, const ItemDesc& D, const 
         if (W) L.d2[at] = d2;
     }
     staged += (uint32_t)__popcll(m);
-    if (staged >= (uint32_t)kWave) {
+    if (DENSE) {
+        if (staged > kCullStageDense - (uint32_t)kWave) {   // no room for another test's pairs
+            cull_store_at<W>(D, L, take_positions(D, staged), staged);
+            staged = 0;
+        }
+    } else if (staged >= (uint32_t)kWave) {
         cull_store<W>(O, D, L, staged, kWave);
         staged -= kWave;
     }
 }
 
 // A wave leaves an item: its last staged pairs, then close_item.
-template <bool W>
+template <bool W, bool DENSE>
 __device__ __forceinline__ void cull_close(OutState& O, const ItemDesc& D, const CullLds& L, uint32_t& staged,
                                            uint32_t* err) {
-    if (staged) cull_store<W>(O, D, L, staged, staged);
+    if (DENSE) {
+        const unsigned long long n = D.capacity ? staged : O.count;
+        if (n) {
+            const unsigned long long base = take_positions(D, n);
+            cull_store_at<W>(D, L, base, staged);
+        }
+        O.count = 0;
+    } else {
+        if (staged) cull_store<W>(O, D, L, staged, staged);
+        close_item(O, D, err);
+    }
     staged = 0;
-    close_item(O, D, err);
 }
 
-template <bool W>
-__global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(W ? 7 : 8, 8)))
+// DENSE: the output of launches with few pairs.  A wave stages up to 512 pairs
+// and takes exactly as many positions with one atomic, so the output is dense
+// as it is written and needs no chunks and no compaction; the last pairs of a
+// block's four waves share one atomic.  Same-address atomics are the cost (about
+// 15 ns each on this GPU): 512 staged pairs keep them below the compaction's
+// two launches up to about 2^21 pairs, and large outputs keep the chunks of
+// thousands of pairs.
+template <bool W, bool DENSE>
+__global__ __launch_bounds__(kWave * kWavesPerBlock)
+__attribute__((amdgpu_waves_per_eu(DENSE ? 1 : (W ? 7 : 8), 8)))
 void cull_kernel(TravArgs A) {
     extern __shared__ __align__(16) unsigned char smem[];
     // dynamic LDS: one area per wave, then the task table (n_items + 1 entries)
-    uint32_t* task_begin_lds = reinterpret_cast<uint32_t*>(smem + kWavesPerBlock * cull_wave_bytes(W));
+    uint32_t* task_begin_lds = reinterpret_cast<uint32_t*>(smem + kWavesPerBlock * cull_wave_bytes(W, DENSE));
     for (uint32_t t = threadIdx.x; t <= A.n_items; t += blockDim.x) task_begin_lds[t] = A.task_begin[t];
     __syncthreads();
     const uint32_t lane = lane_id();
     CullLds L;
     {
-        unsigned char* base = smem + (threadIdx.x / kWave) * cull_wave_bytes(W);
+        unsigned char* base = smem + (threadIdx.x / kWave) * cull_wave_bytes(W, DENSE);
         L.eyes = reinterpret_cast<float4*>(base);
         L.pairs = reinterpret_cast<uint2*>(base + kCullEyes * 16);
-        L.stack = reinterpret_cast<uint32_t*>(L.pairs + kCullStage);
+        L.stack = reinterpret_cast<uint32_t*>(L.pairs + (DENSE ? kCullStageDense : kCullStage));
         L.queue = L.stack + kCullStack;
         L.u = L.queue + kCullQueue;
         L.d2 = reinterpret_cast<float*>(L.u + kCullEyes);   // with W only
@@ -1185,13 +1229,27 @@ void cull_kernel(TravArgs A) {
     uint32_t q = blockIdx.x % kQueues;
     uint32_t queues_left = kQueues;
     for (;;) {
-        uint32_t i = 0;
-        if (lane == 0) i = atomicAdd(A.queues + q * kQueueStride, 1u);
-        i = uni(i);
-        const uint32_t sh = A.interleave_shift;
-        const uint64_t t64 = sh ? (((((uint64_t)(i >> sh)) * kQueues + q) << sh) | (i & ((1u << sh) - 1u)))
-                                : (uint64_t)A.queue_begin[q] + i;
-        const uint64_t end = sh ? (uint64_t)A.n_tasks : (uint64_t)A.queue_begin[q + 1];
+        uint64_t t64, end;
+        if (DENSE && A.static_tasks) {
+            t64 = queues_left == kQueues ? blockIdx.x * kWavesPerBlock + threadIdx.x / kWave : A.n_tasks;
+            t64 = uni64(t64);
+            end = A.n_tasks;
+            queues_left = 1;
+        } else {
+            // another block's queue is looked at before it is taken from: the
+            // end of a launch would else be eight atomics of every wave, 13 ns
+            // apart on each queue's line
+            uint32_t* const head = A.queues + q * kQueueStride;
+            uint32_t i = 0;
+            end = A.queue_begin[q + 1];
+            if (queues_left != kQueues) i = uni(__hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            if (i < (uint32_t)end - A.queue_begin[q]) {
+                i = 0;
+                if (lane == 0) i = atomicAdd(head, 1u);
+                i = uni(i);
+            }
+            t64 = (uint64_t)A.queue_begin[q] + i;
+        }
         uint32_t it = 0xFFFFFFFFu;   // no task left
         const uint32_t t = (uint32_t)t64;
         if (t64 >= end) {
@@ -1208,12 +1266,15 @@ void cull_kernel(TravArgs A) {
             it = uni(lo);
         }
         if (it != cur || it == 0xFFFFFFFFu) {   // a wave may get no task at all
-            if (cur != 0xFFFFFFFFu) cull_close<W>(O, D, L, staged, A.error);
+            if (DENSE && it == 0xFFFFFFFFu) break;   // the block's waves close together, below
+            if (cur != 0xFFFFFFFFu) cull_close<W, DENSE>(O, D, L, staged, A.error);
             if (it == 0xFFFFFFFFu) break;
             cur = it;
             D = A.items[it];
         }
-        const uint32_t u0 = (t - D.task_begin) << D.task_shift;
+        const uint32_t part = t - D.task_begin;
+        const uint32_t u0 = part >> D.sub_log << D.task_shift;
+        const uint32_t root = (1u << D.sub_log) | (part & ((1u << D.sub_log) - 1u));
         const uint32_t cnt = min(1u << D.task_shift, D.n_virtual - u0);
         const uint32_t N = D.n_lights;
         const float s = D.s;
@@ -1231,7 +1292,7 @@ void cull_kernel(TravArgs A) {
         for (;;) {
             if (sn < 16u && next < cnt) {
                 const uint32_t add = min(16u - sn, cnt - next);
-                if (lane < add) L.stack[sn + lane] = 1u | ((next + lane) << kCullSlotShift);
+                if (lane < add) L.stack[sn + lane] = root | ((next + lane) << kCullSlotShift);
                 sn += add;
                 next += add;
             }
@@ -1301,12 +1362,43 @@ void cull_kernel(TravArgs A) {
                 done = upto;
                 while (qn >= least) {
                     const uint32_t n = min(qn, (uint32_t)kWave);
-                    cull_test<W>(O, D, L, qn, n, staged);
+                    cull_test<W, DENSE>(O, D, L, qn, n, staged);
                     qn -= n;
                 }
             } while (done < total);
         }
         wave_sync();
+    }
+    if (DENSE) {
+        // the block's last pairs (or counts): one atomic where its waves hold
+        // the same item
+        __shared__ unsigned long long sums[kWavesPerBlock];
+        __shared__ uint32_t held[kWavesPerBlock];
+        __shared__ unsigned long long first;
+        const uint32_t wv = threadIdx.x / kWave;
+        const unsigned long long mine = cur == 0xFFFFFFFFu ? 0ull : (D.capacity ? staged : O.count);
+        if (lane == 0) {
+            sums[wv] = mine;
+            held[wv] = mine ? cur : 0xFFFFFFFFu;
+        }
+        __syncthreads();
+        unsigned long long before = 0, total = 0;
+        uint32_t item = 0xFFFFFFFFu;
+        bool same = true;
+        for (uint32_t w = 0; w < (uint32_t)kWavesPerBlock; ++w) {
+            if (held[w] == 0xFFFFFFFFu) continue;
+            same = same && (item == 0xFFFFFFFFu || item == held[w]);
+            item = held[w];
+            if (w < wv) before += sums[w];
+            total += sums[w];
+        }
+        if (same) {   // uniform over the block
+            if (total && threadIdx.x == 0) first = atomicAdd(A.items[item].counters + CNT_PAIRS, total);
+            __syncthreads();
+            if (mine && D.capacity) cull_store_at<W>(D, L, uni64(first) + before, staged);
+        } else if (mine) {
+            cull_close<W, true>(O, D, L, staged, A.error);
+        }
     }
 }
 
@@ -1842,26 +1934,32 @@ extern "C" hipError_t hrr_traverse_occupancy(uint32_t eyes_per_wave, uint32_t me
 }
 
 // Dynamic LDS bytes of one block of the block walk.
-extern "C" size_t hrr_cull_lds_per_block(uint32_t n_items, int with_weights) {
-    return hrr::kWavesPerBlock * hrr::cull_wave_bytes(with_weights != 0) + ((size_t)n_items + 1u) * sizeof(uint32_t);
+extern "C" size_t hrr_cull_lds_per_block(uint32_t n_items, int with_weights, int dense) {
+    return hrr::kWavesPerBlock * hrr::cull_wave_bytes(with_weights != 0, dense != 0) +
+           ((size_t)n_items + 1u) * sizeof(uint32_t);
 }
 
+namespace {
+typedef void (*CullKernel)(hrr::TravArgs);
+CullKernel pick_cull(int with_weights, int dense) {
+    if (with_weights) return dense ? hrr::cull_kernel<true, true> : hrr::cull_kernel<true, false>;
+    return dense ? hrr::cull_kernel<false, true> : hrr::cull_kernel<false, false>;
+}
+}  // namespace
+
 // The block walk (see cull_kernel) of a launch's items.
-extern "C" hipError_t hrr_launch_cull(const hrr::TravArgs* A, int with_weights, uint32_t blocks, hipStream_t stream) {
-    const size_t lds = hrr_cull_lds_per_block(A->n_items, with_weights);
-    const dim3 threads(hrr::kWave * hrr::kWavesPerBlock);
-    if (with_weights)
-        hipLaunchKernelGGL(hrr::cull_kernel<true>, dim3(blocks), threads, lds, stream, *A);
-    else
-        hipLaunchKernelGGL(hrr::cull_kernel<false>, dim3(blocks), threads, lds, stream, *A);
+extern "C" hipError_t hrr_launch_cull(const hrr::TravArgs* A, int with_weights, int dense, uint32_t blocks,
+                                      hipStream_t stream) {
+    hipLaunchKernelGGL(pick_cull(with_weights, dense), dim3(blocks), dim3(hrr::kWave * hrr::kWavesPerBlock),
+                       hrr_cull_lds_per_block(A->n_items, with_weights, dense), stream, *A);
     return hipGetLastError();
 }
 
 // Resident blocks per CU of the block walk.
-extern "C" hipError_t hrr_cull_occupancy(int with_weights, uint32_t n_items, int* blocks_per_cu) {
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        blocks_per_cu, with_weights ? (const void*)hrr::cull_kernel<true> : (const void*)hrr::cull_kernel<false>,
-        hrr::kWave * hrr::kWavesPerBlock, hrr_cull_lds_per_block(n_items, with_weights));
+extern "C" hipError_t hrr_cull_occupancy(int with_weights, int dense, uint32_t n_items, int* blocks_per_cu) {
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, (const void*)pick_cull(with_weights, dense),
+                                                        hrr::kWave * hrr::kWavesPerBlock,
+                                                        hrr_cull_lds_per_block(n_items, with_weights, dense));
 }
 
 // The block tree of n_lights >= 1 lights (float4 in sequence order): blocks

@@ -17,8 +17,9 @@ extern "C" size_t hrr_trav_lds_per_wave(uint32_t stack_cap, uint32_t eyes_per_wa
 extern "C" size_t hrr_trav_lds_per_block(uint32_t n_items, size_t lds_per_wave);
 extern "C" hipError_t hrr_traverse_occupancy(uint32_t eyes_per_wave, uint32_t method, int stats, int with_weights,
                                              size_t lds_per_block, int* blocks_per_cu);
-extern "C" hipError_t hrr_launch_cull(const hrr::TravArgs* A, int with_weights, uint32_t blocks, hipStream_t stream);
-extern "C" hipError_t hrr_cull_occupancy(int with_weights, uint32_t n_items, int* blocks_per_cu);
+extern "C" hipError_t hrr_launch_cull(const hrr::TravArgs* A, int with_weights, int dense, uint32_t blocks,
+                                      hipStream_t stream);
+extern "C" hipError_t hrr_cull_occupancy(int with_weights, int dense, uint32_t n_items, int* blocks_per_cu);
 extern "C" hipError_t hrr_launch_order(const hrr::OrderItem* items, const uint32_t* vbegin, uint32_t n_items,
                                        uint32_t total, uint32_t bits, uint32_t rbits, const uint32_t* tile,
                                        uint32_t tile_tz, uint32_t* keys, uint32_t* hist, uint32_t* order, int n_cu,
@@ -69,20 +70,25 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
 
     // ---- grid: persistent waves, as many as stay resident ----
     const size_t lds_wave = shape.blocks ? 0 : hrr_trav_lds_per_wave(cap, epw);
+    // estimated work of the launch (virtual eyes x eye_cost) and room for its pairs
+    double launch_cost = 0.0;
+    uint64_t room = 0;
+    for (const HostItem& it : items) {
+        if (it.h) launch_cost += (double)it.eyes.n * n_samples * eye_cost(it.h->n_lights);
+        room = it.out_capacity > ~0ull - room ? ~0ull : room + it.out_capacity;
+    }
+    const bool dense = shape.blocks && block_walk_dense(room, launch_cost);
     int bpc = 0;
     hipError_t e;
-    e = shape.blocks ? hrr_cull_occupancy(with_w, (uint32_t)n, &bpc)
+    e = shape.blocks ? hrr_cull_occupancy(with_w, dense, (uint32_t)n, &bpc)
                      : hrr_traverse_occupancy(epw, method, stats, with_w,
                                               hrr_trav_lds_per_block((uint32_t)n, lds_wave), &bpc);
     if (e != hipSuccess) return hip_fail(e, "occupancy");
     if (bpc <= 0) return fail(HRR_E_INVALID, "stack of %u entries does not fit in LDS", cap);
 
     std::vector<uint64_t> tasks_of(n);
-    // estimated work of the launch (virtual eyes x eye_cost)
-    double launch_cost = 0.0;
-    for (const HostItem& it : items)
-        if (it.h) launch_cost += (double)it.eyes.n * n_samples * eye_cost(it.h->n_lights);
-    std::vector<uint32_t> task_shift(n, 0u);
+    const uint64_t resident = (uint64_t)ctx->n_cu * bpc * kWavesPerBlock;
+    std::vector<uint32_t> task_shift(n, 0u), sub_log(n, 0u);
     uint64_t tasks = 0;
     uint32_t dmax = 0;
     for (size_t k = 0; k < n; ++k) {
@@ -97,9 +103,9 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
         const uint64_t nv = (uint64_t)it.eyes.n * n_samples;
         if (nv > 0xFFFFFFFFull) return fail(HRR_E_INVALID, "item %zu: eyes x samples exceeds 2^32 - 1", k);
         if (shape.blocks)
-            task_shift[k] = block_task_shift(h->n_lights, launch_cost, (uint64_t)ctx->n_cu * bpc * kWavesPerBlock);
+            block_task_split(h->n_lights, launch_cost, resident, dense, &task_shift[k], &sub_log[k]);
         const uint64_t task_eyes = shape.blocks ? 1ull << task_shift[k] : epw;
-        tasks_of[k] = h->n_lights ? (nv + task_eyes - 1) / task_eyes : 0;
+        tasks_of[k] = h->n_lights ? (nv + task_eyes - 1) / task_eyes << sub_log[k] : 0;
         tasks += tasks_of[k];
         if (tasks > 0xFFFFFFF0ull) return fail(HRR_E_INVALID, "too many tasks in one launch");
         dmax = std::max(dmax, h->depth);
@@ -123,11 +129,12 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
         const uint64_t wk = std::max<uint64_t>(1, std::min<uint64_t>(waves, tasks_of[k]));
         const uint64_t pk = std::max<uint64_t>(1, std::min<uint64_t>(leaves_per_wave * waves, tasks_of[k]));
         const unsigned long long capk = items[k].out_capacity;
-        const uint32_t shift = chunk_shift_for(capk, wk);
+        const uint32_t shift = shape.blocks ? block_chunk_shift(capk, wk) : chunk_shift_for(capk, wk);
         ItemMeta& m = M[k];
         m.out_offset = items[k].out_offset;
         m.capacity = capk;
         m.chunk_shift = shift;
+        if (dense) continue;   // no chunks, so no slack and nothing to compact
         m.slack = capk ? 2ull * pk << shift : 0ull;
         m.slack_off = slack_total;
         slack_total += m.slack;
@@ -148,7 +155,10 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
     vbegin[n] = (uint32_t)std::min<uint64_t>(vtotal, 0xFFFFFFFFull);
     // eye order key (hrr_layout.hpp), for launches with enough work to gain from it
     uint32_t bits = 0, rbits = 0;
-    if (reorder && order_pays(launch_cost)) order_key_bits(n, vtotal, ctx->tile_bits, &bits, &rbits);
+    double big_cost = 0.0;
+    for (const HostItem& it : items)
+        if (block_order_counts(it.h->n_lights)) big_cost += (double)it.eyes.n * n_samples * eye_cost(it.h->n_lights);
+    if (reorder && (shape.blocks ? block_order_pays(big_cost) : order_pays(launch_cost))) order_key_bits(n, vtotal, ctx->tile_bits, &bits, &rbits);
     const bool ordered = bits > 0;
     std::vector<OrderItem> oitems;
     if (ordered) {
@@ -171,16 +181,21 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
         if ((e = S.order_idx.ensure(vtotal * sizeof(uint32_t))) != hipSuccess) return hip_fail(e, "eye order");
         if ((e = S.order_hist.ensure((((size_t)n << (3 * bits + rbits)) + 1024) * sizeof(uint32_t))) != hipSuccess)
             return hip_fail(e, "order histogram");
-        if ((e = S.order_items.ensure(n * sizeof(OrderItem))) != hipSuccess) return hip_fail(e, "order items");
-        if ((e = S.order_vbegin.ensure((n + 1) * sizeof(uint32_t))) != hipSuccess) return hip_fail(e, "order offsets");
     }
-    if ((e = S.queues.ensure(kQueues * kQueueStride * sizeof(uint32_t))) != hipSuccess) return hip_fail(e, "queues");
 
     S.n_items = n;
     S.with_weights = with_w;
     S.stats = stats;
-    if ((e = S.counters.ensure(n * CNT_STRIDE * sizeof(unsigned long long))) != hipSuccess) return hip_fail(e, "counters");
-    if ((e = S.misc.ensure(16 * sizeof(unsigned long long))) != hipSuccess) return hip_fail(e, "misc");
+    // the launch's tables, in one buffer that one copy fills: counters, status
+    // words and queue heads (zero), items, tasks, and the eye order's inputs
+    const size_t zero_words = n * CNT_STRIDE + kStatusWords + kQueues * kQueueStride / 2;
+    const size_t items_at = zero_words * sizeof(unsigned long long);
+    const size_t tasks_at = items_at + n * sizeof(ItemDesc);
+    const size_t oi_at = (tasks_at + (n + 1) * sizeof(uint32_t) + 7) / 8 * 8;
+    const size_t vb_at = oi_at + (ordered ? n * sizeof(OrderItem) : 0);
+    const size_t table_bytes = vb_at + (ordered ? (n + 1) * sizeof(uint32_t) : 0);
+    if ((e = S.tables.ensure(table_bytes)) != hipSuccess) return hip_fail(e, "launch tables");
+    unsigned char* const d_tables = static_cast<unsigned char*>(S.tables.p);
     if ((e = S.partials.ensure(std::max<unsigned long long>(partial_total, 1) * 2 * sizeof(unsigned long long))) != hipSuccess)
         return hip_fail(e, "partial-chunk list");
     if ((e = S.plan.ensure(std::max<unsigned long long>(plan_total, 1) * sizeof(unsigned long long))) != hipSuccess)
@@ -189,8 +204,8 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
         return hip_fail(e, "output slack");
     if (with_w && (e = S.slack_weights.ensure(std::max<unsigned long long>(slack_total, 1) * sizeof(float))) != hipSuccess)
         return hip_fail(e, "weight slack");
-    unsigned long long* d_counters = static_cast<unsigned long long*>(S.counters.p);
-    unsigned long long* d_misc = static_cast<unsigned long long*>(S.misc.p);
+    unsigned long long* d_counters = reinterpret_cast<unsigned long long*>(d_tables);
+    unsigned long long* d_misc = d_counters + n * CNT_STRIDE;
     unsigned long long* d_partials = static_cast<unsigned long long*>(S.partials.p);
 
     // ---- task order and work queues ----
@@ -207,7 +222,7 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
     std::vector<double> task_cost(n);
     double total_cost = 0.0;
     for (size_t k = 0; k < n; ++k) {
-        task_cost[k] = eye_cost(items[k].h->n_lights) * (double)(1u << task_shift[k]);
+        task_cost[k] = eye_cost(items[k].h->n_lights) * (double)(1u << task_shift[k]) / (double)(1u << sub_log[k]);
         total_cost += task_cost[k] * (double)tasks_of[k];
     }
     std::vector<uint32_t> begin_of(n);
@@ -249,6 +264,7 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
         D.blocks = h->d_blocks;
         D.block_log = block_tree_log(h->n_lights);
         D.task_shift = task_shift[k];
+        D.sub_log = sub_log[k];
         D.eyes = it.eyes.xyz;
         D.pairs = pairs ? pairs + 2 * it.out_offset : nullptr;
         D.weights = weights ? weights + it.out_offset : nullptr;
@@ -283,12 +299,8 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
     S.h_task_begin[n] = (uint32_t)tasks;
 
     // pinned staging: readback words first, then the upload of the tables
-    const size_t items_bytes = n * sizeof(ItemDesc);
-    const size_t tb_bytes = (n + 1) * sizeof(uint32_t);
-    const size_t oi_bytes = ordered ? n * sizeof(OrderItem) : 0;
-    const size_t vb_bytes = ordered ? (n + 1) * sizeof(uint32_t) : 0;
-    const size_t read_words = n * CNT_STRIDE + 1 + ST_N;
-    const size_t pin_words = read_words + (items_bytes + tb_bytes + oi_bytes + vb_bytes + 7) / 8 + 8;
+    const size_t read_words = n * CNT_STRIDE + kStatusWords;
+    const size_t pin_words = read_words + (table_bytes + 7) / 8;
     if (S.h_pinned_n < pin_words) {
         if (S.h_pinned) (void)hipHostFree(S.h_pinned);
         S.h_pinned = nullptr;
@@ -298,35 +310,19 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
         S.h_pinned_n = pin_words;
     }
     unsigned char* up = reinterpret_cast<unsigned char*>(S.h_pinned + read_words);
-    memcpy(up, S.h_items.data(), items_bytes);
-    memcpy(up + items_bytes, S.h_task_begin.data(), tb_bytes);
-    // OrderItem holds a pointer: keep it 8-byte aligned
-    const size_t oi_at = (items_bytes + tb_bytes + 7) / 8 * 8;
-    const size_t vb_at = oi_at + oi_bytes;
+    memset(up, 0, items_at);
+    memcpy(up + items_at, S.h_items.data(), n * sizeof(ItemDesc));
+    memcpy(up + tasks_at, S.h_task_begin.data(), (n + 1) * sizeof(uint32_t));
     if (ordered) {
-        memcpy(up + oi_at, oitems.data(), oi_bytes);
-        memcpy(up + vb_at, vbegin.data(), vb_bytes);
+        memcpy(up + oi_at, oitems.data(), n * sizeof(OrderItem));
+        memcpy(up + vb_at, vbegin.data(), (n + 1) * sizeof(uint32_t));
     }
-
-    if ((e = S.items.ensure(items_bytes)) != hipSuccess) return hip_fail(e, "item table");
-    if ((e = S.task_begin.ensure(tb_bytes)) != hipSuccess) return hip_fail(e, "task table");
-    if ((e = hipMemcpyAsync(S.items.p, up, items_bytes, hipMemcpyHostToDevice, stream)) != hipSuccess)
-        return hip_fail(e, "upload items");
-    if ((e = hipMemcpyAsync(S.task_begin.p, up + items_bytes, tb_bytes, hipMemcpyHostToDevice, stream)) != hipSuccess)
-        return hip_fail(e, "upload tasks");
-    if ((e = hipMemsetAsync(d_counters, 0, n * CNT_STRIDE * sizeof(unsigned long long), stream)) != hipSuccess)
-        return hip_fail(e, "clear counters");
-    if ((e = hipMemsetAsync(d_misc, 0, 16 * sizeof(unsigned long long), stream)) != hipSuccess)
-        return hip_fail(e, "clear misc");
-    if ((e = hipMemsetAsync(S.queues.p, 0, kQueues * kQueueStride * sizeof(uint32_t), stream)) != hipSuccess)
-        return hip_fail(e, "clear queues");
+    if ((e = hipMemcpyAsync(d_tables, up, table_bytes, hipMemcpyHostToDevice, stream)) != hipSuccess)
+        return hip_fail(e, "upload of the launch tables");
+    const ItemDesc* d_items = reinterpret_cast<const ItemDesc*>(d_tables + items_at);
     if (ordered) {
-        if ((e = hipMemcpyAsync(S.order_items.p, up + oi_at, oi_bytes, hipMemcpyHostToDevice, stream)) != hipSuccess)
-            return hip_fail(e, "upload order items");
-        if ((e = hipMemcpyAsync(S.order_vbegin.p, up + vb_at, vb_bytes, hipMemcpyHostToDevice, stream)) != hipSuccess)
-            return hip_fail(e, "upload order offsets");
-        if ((e = hrr_launch_order(static_cast<const OrderItem*>(S.order_items.p),
-                                  static_cast<const uint32_t*>(S.order_vbegin.p), (uint32_t)n, (uint32_t)vtotal, bits,
+        if ((e = hrr_launch_order(reinterpret_cast<const OrderItem*>(d_tables + oi_at),
+                                  reinterpret_cast<const uint32_t*>(d_tables + vb_at), (uint32_t)n, (uint32_t)vtotal, bits,
                                   rbits, ctx->d_tile, ctx->tile_tz, static_cast<uint32_t*>(S.order_keys.p),
                                   static_cast<uint32_t*>(S.order_hist.p), static_cast<uint32_t*>(S.order_idx.p),
                                   ctx->n_cu, stream)) != hipSuccess)
@@ -342,13 +338,14 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
 
         TravArgs A;
         memset(&A, 0, sizeof A);
-        A.items = static_cast<const ItemDesc*>(S.items.p);
-        A.task_begin = static_cast<const uint32_t*>(S.task_begin.p);
+        A.items = d_items;
+        A.task_begin = reinterpret_cast<const uint32_t*>(d_tables + tasks_at);
         A.n_items = (uint32_t)n;
         A.n_tasks = (uint32_t)tasks;
         for (uint32_t q = 0; q <= kQueues; ++q) A.queue_begin[q] = qbegin[q];
         A.interleave_shift = il_shift;
-        A.queues = static_cast<uint32_t*>(S.queues.p);
+        A.static_tasks = dense && tasks <= waves;
+        A.queues = reinterpret_cast<uint32_t*>(d_misc + kStatusWords);
         A.tile = ctx->d_tile;
         A.spill = static_cast<unsigned long long*>(S.spill.p);
         A.spill_cap = spill_cap;
@@ -361,7 +358,7 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
             if (!S.ev_end && (e = hipEventCreate(&S.ev_end)) != hipSuccess) return hip_fail(e, "timing event");
             if ((e = hipEventRecord(S.ev_begin, stream)) != hipSuccess) return hip_fail(e, "timing event");
         }
-        e = shape.blocks ? hrr_launch_cull(&A, with_w, blocks, stream)
+        e = shape.blocks ? hrr_launch_cull(&A, with_w, dense, blocks, stream)
                          : hrr_launch_traverse(&A, epw, method, stats, with_w, blocks, stream);
         if (e != hipSuccess) return hip_fail(e, "traverse launch");
         if (timing) {
@@ -371,17 +368,15 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
         // make every item's stored pairs dense (on the device, before the readback)
         bool any_capacity = false;
         for (size_t k = 0; k < n; ++k) any_capacity = any_capacity || items[k].out_capacity > 0;
-        if (any_capacity &&
-            (e = hrr_launch_compact(static_cast<const ItemDesc*>(S.items.p), (uint32_t)n, A.error, stream)) !=
+        if (any_capacity && !dense &&
+            (e = hrr_launch_compact(d_items, (uint32_t)n, A.error, stream)) !=
                 hipSuccess)
             return hip_fail(e, "output compaction");
     }
-    if ((e = hipMemcpyAsync(S.h_pinned, d_counters, n * CNT_STRIDE * sizeof(unsigned long long), hipMemcpyDeviceToHost,
+    S.dense = dense;
+    if ((e = hipMemcpyAsync(S.h_pinned, d_counters, read_words * sizeof(unsigned long long), hipMemcpyDeviceToHost,
                             stream)) != hipSuccess)
         return hip_fail(e, "read counters");
-    if ((e = hipMemcpyAsync(S.h_pinned + n * CNT_STRIDE, d_misc + 1, (1 + ST_N) * sizeof(unsigned long long),
-                            hipMemcpyDeviceToHost, stream)) != hipSuccess)
-        return hip_fail(e, "read status");
     return HRR_OK;
 }
 
@@ -420,19 +415,21 @@ hrr_status launch_noalloc(hrr_ctx* ctx, const hrr_hierarchy* h, const hrr_eyes& 
     hipError_t e = hipSetDevice(ctx->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     const int with_w = weights != nullptr;
-    const bool block_walk = method == HRR_RMQ_PAPER && block_walk_takes(s) &&
-                            block_walk_pays((double)nv * eye_cost(h->n_lights));
+    const bool block_walk = method == HRR_RMQ_PAPER && block_walk_takes(s);
     const size_t lds_wave = block_walk ? 0 : hrr_trav_lds_per_wave(cap, epw);
     int bpc = 0;
-    e = block_walk ? hrr_cull_occupancy(with_w, 1, &bpc)
+    const double cost = (double)nv * eye_cost(h->n_lights);
+    const bool dense = block_walk && block_walk_dense(capacity, cost);
+    e = block_walk ? hrr_cull_occupancy(with_w, dense, 1, &bpc)
                    : hrr_traverse_occupancy(epw, method, 0, with_w, hrr_trav_lds_per_block(1, lds_wave), &bpc);
     if (e != hipSuccess) return hip_fail(e, "occupancy");
     if (bpc <= 0) return fail(HRR_E_INVALID, "stack of %u entries does not fit in LDS", cap);
-    const uint32_t task_shift = block_walk ? block_task_shift(h->n_lights, (double)nv * eye_cost(h->n_lights),
-                                                              (uint64_t)ctx->n_cu * bpc * kWavesPerBlock)
-                                           : 0;
+    uint32_t task_shift = 0, sub_log = 0;
+    if (block_walk)
+        block_task_split(h->n_lights, cost, (uint64_t)ctx->n_cu * bpc * kWavesPerBlock, dense, &task_shift, &sub_log);
     const uint64_t task_eyes = block_walk ? 1ull << task_shift : epw;
-    const uint64_t tasks = h->n_lights ? (nv + task_eyes - 1) / task_eyes : 0;
+    const uint64_t tasks = h->n_lights ? (nv + task_eyes - 1) / task_eyes << sub_log : 0;
+    if (tasks > 0xFFFFFFF0ull) return fail(HRR_E_INVALID, "too many tasks in one launch");
 
     // ---- scratch layout: as many whole blocks as the scratch holds ----
     const uint64_t spill_cap = block_walk ? 0 : (128ull * (h->depth + 2) + 63) / 64 * 64 + 64;   // entries per wave
@@ -440,11 +437,12 @@ hrr_status launch_noalloc(hrr_ctx* ctx, const hrr_hierarchy* h, const hrr_eyes& 
     const uint64_t resident = std::max<uint64_t>(1, (uint64_t)ctx->n_cu * bpc) * kWavesPerBlock;
     const uint64_t needed = std::max<uint64_t>(kWavesPerBlock, (tasks + kWavesPerBlock - 1) / kWavesPerBlock * kWavesPerBlock);
     uint64_t waves = std::min(resident, needed);
-    uint32_t shift = std::min<uint32_t>(chunk_shift_for(capacity, std::min<uint64_t>(waves, std::max<uint64_t>(tasks, 1))),
-                                        kNoAllocMaxChunkShift);
+    const uint64_t touching = std::min<uint64_t>(waves, std::max<uint64_t>(tasks, 1));
+    uint32_t shift = std::min<uint32_t>(
+        block_walk ? block_chunk_shift(capacity, touching) : chunk_shift_for(capacity, touching), kNoAllocMaxChunkShift);
     auto bytes_for = [&](uint64_t w, uint32_t sh) {
         return kNoAllocHeaderBytes + w * spill_cap * 8ull + w * 2ull * 8ull + (3ull * w + 4ull) * 8ull +
-               (capacity ? 2ull * w * (1ull << sh) * pair_bytes : 0ull) + 1024ull;
+               (capacity && !dense ? 2ull * w * (1ull << sh) * pair_bytes : 0ull) + 1024ull;
     };
     while (waves > kWavesPerBlock && bytes_for(waves, shift) > kNoAllocScratchBytes)
         waves -= kWavesPerBlock;
@@ -463,7 +461,7 @@ hrr_status launch_noalloc(hrr_ctx* ctx, const hrr_hierarchy* h, const hrr_eyes& 
     uint2* spill = reinterpret_cast<uint2*>(carve(waves * spill_cap * 8ull));
     unsigned long long* partials = reinterpret_cast<unsigned long long*>(carve(pk * 2ull * 8ull));
     unsigned long long* plan = reinterpret_cast<unsigned long long*>(carve((3ull * pk + 4ull) * 8ull));
-    const unsigned long long slack = capacity ? 2ull * pk << shift : 0ull;
+    const unsigned long long slack = capacity && !dense ? 2ull * pk << shift : 0ull;
     uint32_t* slack_pairs = reinterpret_cast<uint32_t*>(carve(std::max<unsigned long long>(slack, 1) * 8ull));
     float* slack_weights = with_w ? reinterpret_cast<float*>(carve(std::max<unsigned long long>(slack, 1) * 4ull)) : nullptr;
     if (at > kNoAllocScratchBytes) return fail(HRR_E_DEVICE, "hrr_traverse_noalloc: scratch layout exceeds its size");
@@ -477,6 +475,7 @@ hrr_status launch_noalloc(hrr_ctx* ctx, const hrr_hierarchy* h, const hrr_eyes& 
     D.blocks = h->d_blocks;
     D.block_log = block_tree_log(h->n_lights);
     D.task_shift = task_shift;
+    D.sub_log = sub_log;
     D.eyes = eyes.xyz;
     D.pairs = pairs;
     D.weights = weights;
@@ -520,6 +519,7 @@ hrr_status launch_noalloc(hrr_ctx* ctx, const hrr_hierarchy* h, const hrr_eyes& 
         A.n_tasks = (uint32_t)tasks;
         for (uint32_t q = 0; q <= kQueues; ++q) A.queue_begin[q] = (uint32_t)(tasks * q / kQueues);
         A.interleave_shift = 0;
+        A.static_tasks = dense && tasks <= waves;
         A.queues = reinterpret_cast<uint32_t*>(base + kNoAllocQueues);
         A.tile = ctx->d_tile;
         A.spill = reinterpret_cast<unsigned long long*>(spill);
@@ -528,10 +528,10 @@ hrr_status launch_noalloc(hrr_ctx* ctx, const hrr_hierarchy* h, const hrr_eyes& 
         A.lds_per_wave = (uint32_t)lds_wave;
         A.stats = nullptr;
         A.error = error;
-        e = block_walk ? hrr_launch_cull(&A, with_w, blocks, stream)
+        e = block_walk ? hrr_launch_cull(&A, with_w, dense, blocks, stream)
                        : hrr_launch_traverse(&A, epw, method, 0, with_w, blocks, stream);
         if (e != hipSuccess) return hip_fail(e, "allocation-free traverse launch");
-        if (capacity > 0 && (e = hrr_launch_compact(d_item, 1, error, stream)) != hipSuccess)
+        if (capacity > 0 && !dense && (e = hrr_launch_compact(d_item, 1, error, stream)) != hipSuccess)
             return hip_fail(e, "allocation-free output compaction");
     }
     if ((e = hrr_launch_noalloc_finish(base, result_dev, stream)) != hipSuccess)
@@ -551,11 +551,11 @@ hrr_status finish_items(hrr_ctx*, LaunchScratch& S) {
     S.counts.assign(n, 0);
     S.stored.assign(n, 0);
     const unsigned long long* rd = S.h_pinned;
-    S.error = (uint32_t)rd[n * CNT_STRIDE];
-    for (int q = 0; q < ST_N; ++q) S.stat[q] = rd[n * CNT_STRIDE + 1 + q];
+    S.error = (uint32_t)rd[n * CNT_STRIDE + 1];
+    for (int q = 0; q < ST_N; ++q) S.stat[q] = rd[n * CNT_STRIDE + 2 + q];
     for (size_t k = 0; k < n; ++k) {
         S.counts[k] = rd[k * CNT_STRIDE + CNT_PAIRS];
-        S.stored[k] = rd[k * CNT_STRIDE + CNT_STORED];
+        S.stored[k] = S.dense ? std::min(S.counts[k], S.meta[k].capacity) : rd[k * CNT_STRIDE + CNT_STORED];
     }
     return HRR_OK;
 }

@@ -65,13 +65,6 @@ inline uint32_t queue_interleave_shift(uint64_t n, uint64_t tasks) {
 // number); an s outside it runs the node walk, whose tests fall back to the
 // IEEE division.
 inline bool block_walk_takes(float s) { return s >= 0x1p-60f && s <= 0x1p60f; }
-// Whether a call of that much work (the sum of virtual eyes x eye_cost) runs
-// the block walk: below, the call is bound by its set-up and its waves'
-// counters, and the node walk's eight eyes per wave leave fewer of those
-// (4096 eyes x 1024 lights, 2.6e5: 212 against 240 us a call with its sort;
-// 5001 eyes x 2^20 lights, 2e7: 486 against 298).
-inline bool block_walk_pays(double launch_cost) { return launch_cost >= 2097152.0; }
-
 // Estimated work of one eye against n_lights lights, in arbitrary units (the
 // growth of the walk's steps).
 inline double eye_cost(uint32_t n_lights) { return pow((double)(n_lights > 1u ? n_lights : 1u), 0.6); }
@@ -83,13 +76,36 @@ inline double eye_cost(uint32_t n_lights) { return pow((double)(n_lights > 1u ? 
 // last task), but at least kMinTaskCost each (a task costs an atomic and an
 // eye upload, and a wave that leaves an item two or three more) and at most
 // 64 eyes, a wave's eye slots.
+//
+// A launch with dense output is small: it aims at kDenseTasks tasks, one per
+// wave, and where whole eyes make fewer than a quarter of that, an eye's walk is
+// cut into the 4 or 16 blocks of the tree's first levels.
 constexpr double kTasksPerWave = 32.0;
 constexpr double kMinTaskCost = 16384.0;
-inline uint32_t block_task_shift(uint32_t n_lights, double launch_cost, uint64_t resident_waves) {
-    const double target = fmax(launch_cost / (kTasksPerWave * (double)resident_waves), kMinTaskCost) / eye_cost(n_lights);
-    uint32_t shift = 0;
-    while (shift < 6u && (double)(2u << shift) <= target) ++shift;
-    return shift;
+constexpr double kDenseTasks = 4096.0;
+inline void block_task_split(uint32_t n_lights, double launch_cost, uint64_t resident_waves, bool dense,
+                             uint32_t* task_shift, uint32_t* sub_log) {
+    const double want = dense ? fmin(launch_cost / kDenseTasks, kMinTaskCost) : fmax(launch_cost / (kTasksPerWave * (double)resident_waves), kMinTaskCost);
+    const double target = want / eye_cost(n_lights);   // eyes per task
+    uint32_t shift = 0, sub = 0;
+    if (dense) {
+        while (shift < 6u && (double)(1u << shift) < target) ++shift;
+        const uint32_t log = block_tree_log(n_lights);
+        while (sub < 4u && target * (double)(4u << sub) <= 1.0 && log - block_leaf_log(log) >= sub + 6u) sub += 2;
+    } else {
+        while (shift < 6u && (double)(2u << shift) <= target) ++shift;
+    }
+    *task_shift = shift;
+    *sub_log = sub;
+}
+// Whether a block-walk launch writes its output dense, one atomic per 512
+// pairs or wave (see cull_kernel).  us a call, dense / chunks and compaction:
+// 5001 eyes x 2^20 lights, 1.4e5 pairs 83 / 201; 9.4e6 pairs 300 / 413; 1.8e7
+// pairs 892 / 988; 3.8e7 pairs 1087 / 869, bound by the atomics.  Counting
+// calls take it for its set-up, up to the size where resident waves count more
+// (its LDS leaves 5 blocks to a CU against 8).
+inline bool block_walk_dense(uint64_t capacity, double launch_cost) {
+    return capacity ? capacity <= (1ull << 24) : launch_cost < 268435456.0;
 }
 
 // How often one wave can leave one item (publishing a partly filled chunk).
@@ -134,11 +150,29 @@ inline void tune_stack_candidates(uint32_t eyes_per_wave, uint32_t out[3]) {
     }
 }
 
+// Whether a block-walk launch orders its eyes: `cost` is the work of its items
+// whose light blocks outgrow an XCD's 4 MB L2 (2^18 lights and more).  ms a
+// call, ordered / in index order: 2^16 eyes x 2^20 lights at s = 1e-6 (cost
+// 2^28) 0.21 / 0.19, 2^18 eyes 0.51 / 0.57, at s = 1e-4 3.6 / 9.1; 2^20 eyes x
+// 2^18 lights at s = 1e-4 4.3 / 4.8; with 2^16 lights and fewer the ordering
+// pass is never won back (2^20 eyes x 2^16 lights 2.46 / 2.33).
+inline bool block_order_pays(double cost) { return cost >= 268435456.0; }
+inline bool block_order_counts(uint32_t n_lights) { return n_lights >= (1u << 18); }
+
 // Output chunk size of an item: about sixteen chunks per wave that touches
 // the item, 2^kMinChunkShift .. 2^kMaxChunkShift pairs.
 inline uint32_t chunk_shift_for(uint64_t capacity, uint64_t touching_waves) {
     uint32_t shift = kMinChunkShift;
     while (shift < kMaxChunkShift && (capacity >> (shift + 1)) >= 16 * touching_waves) ++shift;
+    return shift;
+}
+// The same for the block walk: about four chunks per wave.  Its launches end
+// sooner, so the chunk atomics of one address, 13 ns each, weigh more than the
+// compaction of larger tails (2^18 eyes x 2^16 lights, 3.8e7 pairs: 2.01 ms at
+// sixteen, 0.87 at four; 1.5e8 pairs 2.2 and 1.74; the frame does not change).
+inline uint32_t block_chunk_shift(uint64_t capacity, uint64_t touching_waves) {
+    uint32_t shift = kMinChunkShift;
+    while (shift < kMaxChunkShift && (capacity >> (shift + 1)) >= 4 * touching_waves) ++shift;
     return shift;
 }
 

@@ -59,8 +59,8 @@ struct ItemDesc {
     uint32_t psi_s0, task_begin;
     uint32_t n_frontier;
     uint32_t block_log;           // log2 of the block tree's root block
-    uint32_t task_shift;          // block walk: a task is up to 2^task_shift eyes
-    uint32_t pad;
+    uint32_t task_shift;          // block walk: a task is up to 2^task_shift eyes ...
+    uint32_t sub_log;             // ... against one of the 2^sub_log blocks of that level (0, 2 or 4)
     float s;
     // product-form keep test (set by the host): v is culled when
     // float(v) * d2 > t_cull, kept (one light) when < t_keep, for d2 <= d2_fast
@@ -113,11 +113,13 @@ struct OrderItem {
     uint32_t n_samples, width, pixel_base, pad;
 };
 
-// Per-item device counters, one 128-byte line per item.
+// Per-item device counters, three 128-byte lines per item: atomics on one line
+// wait for each other (about 13 ns each), and a wave that leaves an item adds to
+// two of the first three.
 // CNT_STORED / CNT_MOVED / CNT_ND are written by the compaction after the
 // traversal: pairs dense at the front of the slice, pairs moved, data chunks.
 enum CounterIdx {
-    CNT_PAIRS = 0, CNT_CHUNKS = 1, CNT_PARTIALS = 2, CNT_STORED = 3, CNT_MOVED = 4, CNT_ND = 5, CNT_STRIDE = 16
+    CNT_PAIRS = 0, CNT_CHUNKS = 16, CNT_PARTIALS = 32, CNT_STORED = 3, CNT_MOVED = 4, CNT_ND = 5, CNT_STRIDE = 48
 };
 
 // Kernel arguments of the persistent traversal launch.
@@ -132,6 +134,7 @@ struct TravArgs {
     uint32_t spill_cap;           // entries per wave
     uint32_t stack_cap;           // LDS stack entries per wave (a multiple of 64, >= 192)
     uint32_t lds_per_wave;        // bytes
+    uint32_t static_tasks;        // non-zero: wave w takes task w alone (no queues)
     uint32_t interleave_shift;    // ... or, if > 0, chunks q, q + 8, q + 16, ... of 2^shift tasks
     unsigned long long* stats;    // 8 counters or null
     uint32_t* error;              // set non-zero on an internal failure
@@ -167,17 +170,20 @@ constexpr unsigned long long kNoAllocScratchBytes = 128ull << 20;
 constexpr unsigned long long kNoAllocHeaderBytes = 4096;
 constexpr unsigned long long kNoAllocQueues = 0;        // kQueues * kQueueStride u32
 constexpr unsigned long long kNoAllocCounters = 1024;   // CNT_STRIDE u64
-constexpr unsigned long long kNoAllocMisc = 1152;       // 16 u64: [1] = error word
-constexpr unsigned long long kNoAllocItem = 1280;       // one ItemDesc
-constexpr unsigned long long kNoAllocTasks = 1792;      // task table {0, n_tasks}
+constexpr unsigned long long kNoAllocMisc = 1536;       // 16 u64: [1] = error word
+constexpr unsigned long long kNoAllocItem = 1664;       // one ItemDesc
+constexpr unsigned long long kNoAllocTasks = 2176;      // task table {0, n_tasks}
 constexpr uint32_t kNoAllocMaxChunkShift = 10;          // output chunks of at most 1024 pairs
 
+// Status words of a launch: [1] = error word, [2 ..] = statistics.
+constexpr uint32_t kStatusWords = 16;
 enum StatIdx { ST_EYES = 0, ST_PAIRS, ST_VISITS, ST_RMQ, ST_LEAF, ST_SPILLS, ST_MAXSTACK, ST_N };
 
 // Kernel-reported (1, 2) and host-detected (4) internal failures.
 enum ErrCode { ERR_NONE = 0, ERR_SPILL_OVERFLOW = 1, ERR_PARTIALS_OVERFLOW = 2, ERR_UNFILLED = 4 };
 
 static_assert(sizeof(ItemDesc) <= kNoAllocTasks - kNoAllocItem, "item table slot");
+static_assert(CNT_STRIDE * 8 <= kNoAllocMisc - kNoAllocCounters, "counter slot");
 static_assert(kQueues * kQueueStride * sizeof(uint32_t) <= kNoAllocCounters, "queue heads slot");
 
 }  // namespace hrr
