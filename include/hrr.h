@@ -175,9 +175,10 @@ hrr_status hrr_build_hierarchy(hrr_ctx* ctx, const float* lights_xyz,
  * memory, 3*n_lights fp32; box and leaf_size (with its split flag) as above.  The result is the
  * one hrr_build_hierarchy returns for the same lights, record for record
  * (same order, splits, exact boxes and record numbering): Morton codes,
- * a stable radix sort, one launch per tree level for the splits, then a
- * bottom-up refit.  Work is ordered on `stream`; the call returns when the
- * hierarchy is complete.  Non-finite coordinates return HRR_E_INVALID. */
+ * a stable radix sort, then every node from its split position.  Work is
+ * ordered on `stream`; the call returns when the hierarchy is complete.  The
+ * context keeps the build's scratch and the memory of freed hierarchies for
+ * later builds, at most 512 MiB of each.  Non-finite coordinates return HRR_E_INVALID. */
 hrr_status hrr_build_hierarchy_device(hrr_ctx* ctx, const float* lights_xyz_dev,
                                       uint32_t n_lights, uint32_t leaf_size,
                                       const float* box, void* stream, hrr_hierarchy** out);

@@ -81,6 +81,60 @@ void DevBuf::release() {
     bytes = 0;
 }
 
+hipError_t BlockCache::get(void** p, size_t bytes) {
+    *p = nullptr;
+    bytes = std::max<size_t>(bytes, 256);
+    std::lock_guard<std::mutex> g(mu);
+    size_t best = idle.size();
+    for (size_t q = 0; q < idle.size(); ++q)   // the smallest that fits, no more than twice as large
+        if (idle[q].bytes >= bytes && idle[q].bytes / 2 <= bytes && (best == idle.size() || idle[q].bytes < idle[best].bytes))
+            best = q;
+    if (best < idle.size()) {
+        *p = idle[best].p;
+        live[*p] = idle[best].bytes;
+        idle_bytes -= idle[best].bytes;
+        idle.erase(idle.begin() + best);
+        return hipSuccess;
+    }
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory && !idle.empty()) {
+        for (auto& x : idle) (void)hipFree(x.p);
+        idle.clear();
+        idle_bytes = 0;
+        (void)hipGetLastError();
+        e = hipMalloc(p, bytes);
+    }
+    if (e == hipSuccess) live[*p] = bytes;
+    else *p = nullptr;
+    return e;
+}
+
+void BlockCache::put(void* p) {
+    if (!p) return;
+    std::lock_guard<std::mutex> g(mu);
+    auto it = live.find(p);
+    const size_t bytes = it == live.end() ? 0 : it->second;
+    if (it != live.end()) live.erase(it);
+    if (bytes == 0 || bytes > kBlockCacheBytes / 2 || hipDeviceSynchronize() != hipSuccess) {
+        (void)hipFree(p);
+        return;
+    }
+    idle.push_back({p, bytes});
+    idle_bytes += bytes;
+    while (idle_bytes > kBlockCacheBytes) {
+        (void)hipFree(idle.front().p);
+        idle_bytes -= idle.front().bytes;
+        idle.erase(idle.begin());
+    }
+}
+
+void BlockCache::release() {
+    std::lock_guard<std::mutex> g(mu);
+    for (auto& x : idle) (void)hipFree(x.p);
+    idle.clear();
+    idle_bytes = 0;
+}
+
 void release_scratch(LaunchScratch& S) {
     S.tables.release();
     S.spill.release();
@@ -271,6 +325,9 @@ HRR_EXPORT void hrr_destroy(hrr_ctx* ctx) {
     hrr_server_shutdown(ctx);
     release_scratch(ctx->scratch);
     for (auto& g : ctx->group_scratch) release_scratch(g);
+    ctx->blocks.release();
+    ctx->build_scratch.release();
+    if (ctx->build_pin) (void)hipHostFree(ctx->build_pin);
     if (ctx->d_tile) (void)hipFree(ctx->d_tile);
     delete ctx;
 }
@@ -395,37 +452,33 @@ HRR_EXPORT hrr_status hrr_hierarchy_get_info(const hrr_hierarchy* h, hrr_hierarc
     return HRR_OK;
 }
 
-// Host copies of a device-built hierarchy's order and sorted positions.
-static hrr_status ensure_host_copies(const hrr_hierarchy* h) {
-    if (h->host_copies) return HRR_OK;
-    hipError_t e = hipSetDevice(h->owner->device);
-    if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
-    const size_t n = h->n_lights;
-    std::vector<float> l4(4 * n);
-    h->perm.resize(n);
-    if (n && ((e = hipMemcpy(h->perm.data(), h->d_perm, n * sizeof(uint32_t), hipMemcpyDeviceToHost)) != hipSuccess ||
-              (e = hipMemcpy(l4.data(), h->d_lights, 4 * n * sizeof(float), hipMemcpyDeviceToHost)) != hipSuccess))
-        return hip_fail(e, "hierarchy download");
-    h->sorted_xyz.resize(3 * n);
-    for (size_t i = 0; i < n; ++i)
-        for (int k = 0; k < 3; ++k) h->sorted_xyz[3 * i + k] = l4[4 * i + k];
-    h->host_copies = true;
-    return HRR_OK;
-}
-
 HRR_EXPORT hrr_status hrr_hierarchy_permutation(const hrr_hierarchy* h, uint32_t* perm_out) {
     if (!h || (!perm_out && h->n_lights)) return fail(HRR_E_INVALID, "hrr_hierarchy_permutation: null argument");
-    hrr_status st = ensure_host_copies(h);
-    if (st != HRR_OK) return st;
-    if (h->n_lights) memcpy(perm_out, h->perm.data(), h->n_lights * sizeof(uint32_t));
-    return HRR_OK;
+    if (!h->n_lights) return HRR_OK;
+    const size_t bytes = h->n_lights * sizeof(uint32_t);
+    if (h->host_copies) {
+        memcpy(perm_out, h->perm.data(), bytes);
+        return HRR_OK;
+    }
+    hipError_t e = hipSetDevice(h->owner->device);
+    if (e == hipSuccess) e = hipMemcpy(perm_out, h->d_perm, bytes, hipMemcpyDeviceToHost);
+    return e == hipSuccess ? HRR_OK : hip_fail(e, "hierarchy download");
 }
 
 HRR_EXPORT hrr_status hrr_hierarchy_sorted_lights(const hrr_hierarchy* h, float* sorted_xyz_out) {
     if (!h || (!sorted_xyz_out && h->n_lights)) return fail(HRR_E_INVALID, "hrr_hierarchy_sorted_lights: null argument");
-    hrr_status st = ensure_host_copies(h);
-    if (st != HRR_OK) return st;
-    if (h->n_lights) memcpy(sorted_xyz_out, h->sorted_xyz.data(), 3 * (size_t)h->n_lights * sizeof(float));
+    const size_t n = h->n_lights;
+    if (!n) return HRR_OK;
+    if (h->host_copies) {
+        memcpy(sorted_xyz_out, h->sorted_xyz.data(), 3 * n * sizeof(float));
+        return HRR_OK;
+    }
+    hipError_t e = hipSetDevice(h->owner->device);
+    std::vector<float> l4(4 * n);
+    if (e == hipSuccess) e = hipMemcpy(l4.data(), h->d_lights, 4 * n * sizeof(float), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return hip_fail(e, "hierarchy download");
+    for (size_t i = 0; i < n; ++i)
+        for (int k = 0; k < 3; ++k) sorted_xyz_out[3 * i + k] = l4[4 * i + k];
     return HRR_OK;
 }
 
@@ -441,11 +494,22 @@ HRR_EXPORT hrr_status hrr_hierarchy_records(const hrr_hierarchy* h, void* nodes_
 HRR_EXPORT void hrr_free_hierarchy(hrr_ctx* ctx, hrr_hierarchy* h) {
     if (!h) return;
     if (ctx) (void)hipSetDevice(ctx->device);
-    if (h->d_nodes) (void)hipFree(h->d_nodes);
-    if (h->d_frontier) (void)hipFree(h->d_frontier);
-    if (h->d_blocks) (void)hipFree(h->d_blocks);
-    if (h->d_lights) (void)hipFree(h->d_lights);
-    if (h->d_perm) (void)hipFree(h->d_perm);
+    if (h->d_base) {   // one allocation, with the records inside it or beside it
+        void* const records = h->n_nodes ? h->d_nodes : nullptr;
+        if (ctx) {
+            ctx->blocks.put(records);
+            ctx->blocks.put(h->d_base);
+        } else {
+            if (records) (void)hipFree(records);
+            (void)hipFree(h->d_base);
+        }
+    } else {
+        if (h->d_nodes) (void)hipFree(h->d_nodes);
+        if (h->d_frontier) (void)hipFree(h->d_frontier);
+        if (h->d_blocks) (void)hipFree(h->d_blocks);
+        if (h->d_lights) (void)hipFree(h->d_lights);
+        if (h->d_perm) (void)hipFree(h->d_perm);
+    }
     delete h;
 }
 

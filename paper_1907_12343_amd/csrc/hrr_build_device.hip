@@ -8,20 +8,22 @@
 // with every node a contiguous index range; building it on the device lets a
 // renderer rebuild per-frame light caches without a host round trip.
 //
-// Steps (all stream-ordered; the host reads back one count per level):
+// Steps (all stream-ordered; the host waits twice, for the record count and
+// for the end):
 //   1. codes   : 63-bit Morton code per light (21-bit cells, x highest)
 //   2. sort    : stable LSD radix sort of (code, index) pairs, 8-bit digits
-//   3. gather  : lights in sequence order as float4, codes in sequence order
-//   4. levels  : breadth-first, one launch per level: split every internal
-//                node of the level, append its internal children to the next
-//                level (exclusive scan of the child counts)
-//   5. refit   : deepest level first, each node's children boxes (a leaf
-//                child from its <= leaf_size lights, an internal child as
-//                the union of its own children) and the number of pair
-//                owners (nodes with an internal child) in its subtree
-//   6. records : root level first, record numbers (a node's children take
-//                the sibling pair 2 (1 + owners before it in preorder) and
-//                the next record) and the 64-byte records at those numbers
+//   3. gather  : lights and original indices in sequence order, then the
+//                block tree of the lights (block_leaf_kernel, hrr_kernels.hip)
+//   4. nodes   : one thread per index c in (0, n): a full binary tree over n
+//                lights has one node per split position, and both split rules
+//                give that node's range [a, b) and its parent from c alone
+//                (see node_of)
+//   5. ranks   : record numbers.  Owners (nodes with an internal child) before
+//                a node in preorder are those that start at a smaller index,
+//                an exclusive scan, and the ancestors that start at the same
+//                one, its chain of left-child steps up
+//   6. records : the 64-byte records, children's boxes from the lights of
+//                small children and from the block tree of large ones
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -65,195 +67,203 @@ __global__ void codes_kernel(const float* __restrict__ xyz, uint32_t n, QBox qb,
     idx[i] = i;
 }
 
-__global__ void gather_kernel(const float* __restrict__ xyz, const uint32_t* __restrict__ perm, uint32_t n,
-                              float4* __restrict__ lights) {
+__global__ void gather_kernel(const float* __restrict__ xyz, const uint32_t* __restrict__ order, uint32_t n,
+                              float4* __restrict__ lights, uint32_t* __restrict__ perm) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const uint32_t j = perm[i];
+    const uint32_t j = order[i];
     lights[i] = make_float4(xyz[3 * (size_t)j], xyz[3 * (size_t)j + 1], xyz[3 * (size_t)j + 2], 0.0f);
+    perm[i] = j;
 }
 
-// ---- breadth-first split ----------------------------------------------
+// ---- nodes by split position ----------------------------------------------
 //
-// Internal nodes are numbered breadth-first (t); level l holds
-// [off[l], off[l+1]).  Bfs (hrr_devbuild.hpp) holds, per node, the range a,
-// split c, end b, children t (or -1 for a leaf child), subtree counts of
-// pair owners, record numbers, owners before the node in preorder and the
-// node's own box.
+// Radix split: the node that is cut between c - 1 and c at code bit h holds
+// exactly the lights that share the code bits above h with light c, a range
+// around c found by galloping outwards (most nodes are small).  Lights of one
+// code form a run [p, q), whose subtree is cut at midpoints: there the node is
+// found by descending from [p, q).  The parent of a node [a, b) is cut at a or
+// at b, at the position whose codes differ in the lower bit (the two never
+// tie: between two cuts at one bit lies one at a higher bit).
+// Power-of-two split: with 2^t the lowest set bit of c the node is
+// [c - 2^t, min(c + 2^t, n)), and its parent's cut follows from the next bit.
 
-__device__ __forceinline__ uint32_t split_of(const uint64_t* __restrict__ code, uint32_t a, uint32_t b,
-                                             uint32_t pow2) {
-    if (pow2) return a + (1u << (31 - __clz((int)(b - a - 1u))));   // largest 2^k < b - a (b - a >= 2)
-    const uint64_t ca = code[a], cb = code[b - 1];
-    if (ca == cb) return a + (b - a) / 2;
-    const int h = 63 - __clzll((long long)(ca ^ cb));
-    // first index in (a, b) whose code has bit h set (the codes agree above h)
-    uint32_t lo = a, hi = b - 1;
-    while (hi - lo > 1) {
-        const uint32_t mid = lo + (hi - lo) / 2;
-        if ((code[mid] >> h) & 1u) hi = mid; else lo = mid;
-    }
-    return hi;
+// Parent of a node: its split position << 1 | 1 for a right child.
+constexpr uint32_t kNoParent = 0xFFFFFFFFu;
+
+struct NodeAt {
+    uint32_t a, b, parent;
+};
+
+// bit in which the codes on both sides of boundary x differ (-1: equal codes)
+__device__ __forceinline__ int cut_bit(const uint64_t* __restrict__ code, uint32_t n, uint32_t x) {
+    if (x == 0u || x == n) return 64;
+    const uint64_t d = code[x - 1u] ^ code[x];
+    return d ? 63 - __clzll((long long)d) : -1;
 }
 
-// Pass 1 of a level: split, count internal children.
-__global__ void split_kernel(Bfs T, const uint64_t* __restrict__ code, uint32_t t0, uint32_t t1, uint32_t leaf,
-                             uint32_t pow2, uint32_t* __restrict__ kids) {
-    const uint32_t t = t0 + blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= t1) return;
-    const uint32_t a = T.a[t], b = T.b[t];
-    const uint32_t c = split_of(code, a, b, pow2);
-    T.c[t] = c;
-    kids[t - t0] = (c - a > leaf ? 1u : 0u) + (b - c > leaf ? 1u : 0u);
+// The largest range around c (c - 1 and c inside) whose codes >> shift equal
+// code[c] >> shift.
+__device__ __forceinline__ void same_prefix_range(const uint64_t* __restrict__ code, uint32_t n, uint32_t c,
+                                                  uint32_t shift, uint32_t* a, uint32_t* b) {
+    const uint64_t prefix = code[c] >> shift;
+    uint32_t lo = c - 1u, hi = c, step = 1;
+    while (lo >= step && (code[lo - step] >> shift) == prefix) {
+        lo -= step;
+        step <<= 1;
+    }
+    for (; step; step >>= 1)
+        if (lo >= step && (code[lo - step] >> shift) == prefix) lo -= step;
+    step = 1;
+    while (n - hi > step && (code[hi + step] >> shift) == prefix) {
+        hi += step;
+        step <<= 1;
+    }
+    for (; step; step >>= 1)
+        if (n - hi > step && (code[hi + step] >> shift) == prefix) hi += step;
+    *a = lo;
+    *b = hi + 1u;
 }
 
-// Pass 2 of a level: place the internal children at t1 + exclusive prefix.
-// Every split leaves both sides non-empty, so a build has at most n - 1
-// internal nodes; `cap` (that bound) only guards the tables.
-__global__ void place_kernel(Bfs T, uint32_t t0, uint32_t t1, uint32_t leaf, const uint32_t* __restrict__ prefix,
-                             uint32_t cap) {
-    const uint32_t t = t0 + blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= t1) return;
-    const uint32_t a = T.a[t], c = T.c[t], b = T.b[t];
-    uint32_t at = t1 + prefix[t - t0];
-    int32_t l = -1, r = -1;
-    if (c - a > leaf && at < cap) {
-        l = (int32_t)at;
-        T.a[at] = a;
-        T.b[at] = c;
-        ++at;
+__device__ __forceinline__ NodeAt node_of(const uint64_t* __restrict__ code, uint32_t n, uint32_t c, uint32_t pow2) {
+    NodeAt r;
+    if (pow2) {
+        const uint32_t t = 1u << (uint32_t)__builtin_ctz(c);
+        r.a = c - t;
+        r.b = n - c > t ? c + t : n;
+        if (r.a == 0u && r.b == n) r.parent = kNoParent;
+        else if (r.b < n && !(r.a & (2u * t))) r.parent = r.b << 1;
+        else r.parent = (r.a << 1) | 1u;
+        return r;
     }
-    if (b - c > leaf && at < cap) {
-        r = (int32_t)at;
-        T.a[at] = c;
-        T.b[at] = b;
+    const int h = cut_bit(code, n, c);
+    same_prefix_range(code, n, c, (uint32_t)(h + 1), &r.a, &r.b);
+    const int l = cut_bit(code, n, r.a), u = cut_bit(code, n, r.b);
+    r.parent = r.a == 0u && r.b == n ? kNoParent : (l < u ? (r.a << 1) | 1u : r.b << 1);
+    if (h < 0) {
+        for (;;) {
+            const uint32_t mid = r.a + (r.b - r.a) / 2u;
+            if (mid == c) break;
+            if (c < mid) {
+                r.b = mid;
+                r.parent = mid << 1;
+            } else {
+                r.a = mid;
+                r.parent = (mid << 1) | 1u;
+            }
+        }
     }
-    T.l[t] = l;
-    T.r[t] = r;
+    return r;
 }
 
-// min / max with the host builder's tie rule (std::min / std::max keep the
-// first operand unless the second is strictly smaller / larger), so that
-// signed zeros come out the same.
-__device__ __forceinline__ float min_first(float x, float y) { return y < x ? y : x; }
-__device__ __forceinline__ float max_first(float x, float y) { return x < y ? y : x; }
+// Tables by split position c: range (b = 0: not an internal node), parent,
+// record number of the children's pair; owners by first index.
+__global__ __launch_bounds__(256) void nodes_kernel(const uint64_t* __restrict__ code, uint32_t n, uint32_t leaf,
+                                                    uint32_t pow2, uint2* __restrict__ range,
+                                                    uint32_t* __restrict__ parent, uint32_t* __restrict__ owners) {
+    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x + 1u;
+    if (c >= n) return;
+    const NodeAt r = node_of(code, n, c, pow2);
+    const bool internal = r.b - r.a > leaf;
+    range[c] = internal ? make_uint2(r.a, r.b) : make_uint2(0u, 0u);
+    parent[c] = r.parent;
+    if (internal && (c - r.a > leaf || r.b - c > leaf)) atomicAdd(owners + r.a, 1u);
+}
 
-__device__ __forceinline__ void leaf_box(const float4* __restrict__ lights, uint32_t a, uint32_t b, float* lo,
-                                         float* hi) {
+// before: the exclusive scan of the owners by first index (n + 1 entries).
+// out[0] = all owners, out[1] = the deepest node's depth (zero before).
+__global__ __launch_bounds__(256) void ranks_kernel(const uint2* __restrict__ range, const uint32_t* __restrict__ parent,
+                                                    const uint32_t* __restrict__ before, uint32_t n, uint32_t leaf,
+                                                    uint32_t* __restrict__ first, uint32_t* __restrict__ out) {
+    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x + 1u;
+    if (c == 1u) out[0] = before[n];
+    uint32_t depth = 0;
+    if (c < n && range[c].y != 0u) {
+        const uint2 r = range[c];
+        const bool owner = c - r.x > leaf || r.y - c > leaf;
+        uint32_t p = parent[c], chain = 0;
+        for (; p != kNoParent && !(p & 1u); ++chain) p = parent[p >> 1];   // every one of them is an owner
+        first[c] = owner ? 2u * (1u + before[r.x] + chain) : 0xFFFFFFFFu;
+        if (!owner)
+            for (depth = chain; p != kNoParent; ++depth) p = parent[p >> 1];
+    }
+    for (int o = 32; o > 0; o >>= 1) depth = max(depth, (uint32_t)__shfl_xor((int)depth, o));
+    // few waves raise the maximum: look before adding to the one address
+    if ((threadIdx.x & 63u) == 0u && depth > __hip_atomic_load(out + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(out + 1, depth);
+}
+
+__device__ __forceinline__ void widen(float* lo, float* hi, const float4& l, const float4& h) {
+    lo[0] = min_first(lo[0], l.x); hi[0] = max_first(hi[0], h.x);
+    lo[1] = min_first(lo[1], l.y); hi[1] = max_first(hi[1], h.y);
+    lo[2] = min_first(lo[2], l.z); hi[2] = max_first(hi[2], h.z);
+}
+
+// Box of the lights [a, b), which the host builder computes light by light and
+// child by child: the first light (in sequence order) that attains each bound
+// gives it, so lights and whole blocks are taken in order here.
+__device__ __forceinline__ void range_box(const float4* __restrict__ lights, const float4* __restrict__ blocks,
+                                          uint32_t block_log, uint32_t a, uint32_t b, float* lo, float* hi) {
+    const uint32_t leaf_log = block_leaf_log(block_log), small = 1u << leaf_log;
     const float4 p = lights[a];
     lo[0] = hi[0] = p.x;
     lo[1] = hi[1] = p.y;
     lo[2] = hi[2] = p.z;
-    for (uint32_t i = a + 1; i < b; ++i) {
-        const float4 q = lights[i];
-        lo[0] = min_first(lo[0], q.x); hi[0] = max_first(hi[0], q.x);
-        lo[1] = min_first(lo[1], q.y); hi[1] = max_first(hi[1], q.y);
-        lo[2] = min_first(lo[2], q.z); hi[2] = max_first(hi[2], q.z);
-    }
-}
-
-// Children boxes of a node: a leaf child from its lights, an internal child
-// from its own box (computed one level deeper, earlier).
-__device__ __forceinline__ void child_box(const Bfs& T, const float4* __restrict__ lights, int32_t child, uint32_t a,
-                                          uint32_t b, float* lo, float* hi) {
-    if (child < 0) {
-        leaf_box(lights, a, b, lo, hi);
-    } else {
-        const float* bx = T.box + 6 * (size_t)child;
-        for (int k = 0; k < 3; ++k) {
-            lo[k] = bx[k];
-            hi[k] = bx[3 + k];
+    for (uint32_t i = b - a < small ? a + 1u : a; i < b;) {
+        if ((i & (small - 1u)) == 0u && b - i >= small) {
+            uint32_t v = leaf_log;
+            while (v + 2u < block_log && (i & ((4u << v) - 1u)) == 0u && (b - i) >> v >= 4u) v += 2u;
+            const uint32_t id = (1u << (block_log - v)) + (i >> v);
+            widen(lo, hi, blocks[2u * id], blocks[2u * id + 1u]);
+            i += 1u << v;
+        } else {
+            const float4 q = lights[i];
+            widen(lo, hi, q, q);
+            ++i;
         }
     }
 }
 
-// Refit one level (deepest first): own box and the pair owners in the subtree.
-__global__ void refit_kernel(Bfs T, const float4* __restrict__ lights, uint32_t t0, uint32_t t1) {
-    const uint32_t t = t0 + blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= t1) return;
-    const uint32_t a = T.a[t], c = T.c[t], b = T.b[t];
-    const int32_t l = T.l[t], r = T.r[t];
-    float llo[3], lhi[3], rlo[3], rhi[3];
-    child_box(T, lights, l, a, c, llo, lhi);
-    child_box(T, lights, r, c, b, rlo, rhi);
-    float* bx = T.box + 6 * (size_t)t;
-    for (int k = 0; k < 3; ++k) {
-        bx[k] = min_first(llo[k], rlo[k]);
-        bx[3 + k] = max_first(lhi[k], rhi[k]);
-    }
-    T.cnt[t] = (l >= 0 || r >= 0 ? 1u : 0u) + (l >= 0 ? T.cnt[l] : 0u) + (r >= 0 ? T.cnt[r] : 0u);
-}
-
-// Records of one level (root level first): the children's record numbers
-// and owner ranks, and the 64-byte record at this node's number.
-__global__ void record_kernel(Bfs T, const float4* __restrict__ lights, uint32_t t0, uint32_t t1,
-                              Node* __restrict__ nodes) {
-    const uint32_t t = t0 + blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= t1) return;
-    const uint32_t me = T.pre[t];
-    const uint32_t a = T.a[t], c = T.c[t], b = T.b[t];
-    const int32_t l = T.l[t], r = T.r[t];
-    uint32_t first = 0xFFFFFFFFu;
-    if (l >= 0 || r >= 0) {
-        const uint32_t rank = T.own[t];   // owners before this node in preorder
-        first = 2u * (1u + rank);
-        if (l >= 0) {
-            T.pre[l] = first;
-            T.own[l] = rank + 1u;
-        }
-        if (r >= 0) {
-            T.pre[r] = first + 1u;
-            T.own[r] = rank + 1u + (l >= 0 ? T.cnt[l] : 0u);
-        }
-    }
-    float llo[3], lhi[3], rlo[3], rhi[3];
-    child_box(T, lights, l, a, c, llo, lhi);
-    child_box(T, lights, r, c, b, rlo, rhi);
+// Bound by the scattered 64-byte stores and the lights' loads: 83 us for 2^20
+// lights (67 MB of records); the nodes and ranks before it 43 and 48 us, the
+// sort 230 us.  A build of 2^20 lights takes 0.54 ms against 3.9 ms with one
+// launch and one host wait per tree level.
+__global__ __launch_bounds__(256) void records_kernel(const uint2* __restrict__ range, const uint32_t* __restrict__ parent,
+                                                      const uint32_t* __restrict__ first,
+                                                      const float4* __restrict__ lights,
+                                                      const float4* __restrict__ blocks, uint32_t block_log, uint32_t n,
+                                                      Node* __restrict__ nodes) {
+    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x + 1u;
+    if (c >= n) return;
+    const uint2 r = range[c];
+    if (r.y == 0u) return;
+    const uint32_t p = parent[c];
     Node nd;
-    for (int k = 0; k < 3; ++k) {
-        nd.lo_l[k] = llo[k];
-        nd.hi_l[k] = lhi[k];
-        nd.lo_r[k] = rlo[k];
-        nd.hi_r[k] = rhi[k];
-    }
-    nd.a = a;
+    range_box(lights, blocks, block_log, r.x, c, nd.lo_l, nd.hi_l);
+    range_box(lights, blocks, block_log, c, r.y, nd.lo_r, nd.hi_r);
+    nd.a = r.x;
     nd.c = c;
-    nd.b = b;
-    nd.first = first;
-    nodes[me] = nd;
+    nd.b = r.y;
+    nd.first = first[c];
+    nodes[p == kNoParent ? 0u : first[p >> 1] + (p & 1u)] = nd;
 }
-
-__global__ void root_leaf_box_kernel(const float4* __restrict__ lights, uint32_t n, float* __restrict__ box) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) leaf_box(lights, 0, n, box, box + 3);
-}
-
-__global__ void init_root_kernel(Bfs T, uint32_t n) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        T.a[0] = 0u;
-        T.b[0] = n;
-        T.pre[0] = 0u;
-        T.own[0] = 0u;
-    }
-}
-
 
 // ---- stable LSD radix sort of (code, index) pairs ----------------------
 //
 // Eight passes of 8-bit digits cover the 63 code bits, least significant
-// digit first.  One pass is three steps: the digit counts of every tile of
-// kSortTile keys, an exclusive scan of those counts laid out digit-major
-// (digit d of tile b at d * n_tiles + b, so the scan hands every (digit,
-// tile) pair the first output position of its keys), and a scatter that
-// ranks each tile's keys stably.  A tile is read in kSortRounds rounds of
-// 256 consecutive keys; a key's rank is its digit's next free position in the
-// tile, plus the keys of its round with the same digit in earlier waves, plus
-// those in earlier lanes of its own wave (found with eight ballots, one per
-// digit bit).  Keys of one digit therefore leave in index order, which makes
-// every pass stable and the result ordered by (code, original index).
+// digit first.  One pass counts the digits of every tile of 256 ROUNDS keys
+// and scatters each tile's keys stably.  A wave owns a run of 64 ROUNDS
+// consecutive keys of its tile and takes them 64 at a time: a key's rank in the
+// run is the number of its digit's keys in earlier rounds (an LDS count that
+// only this wave touches) plus those in earlier lanes (found with eight
+// ballots, one per digit bit).  The keys stay in registers while the waves'
+// counts become first positions, so a tile needs two barriers however many
+// rounds it has (2^20 keys: 20 us a scatter with two barriers a round).  Keys
+// of one digit leave in index order, which makes every pass stable and the
+// result ordered by (code, original index).
 
 constexpr uint32_t kSortThreads = 256;
-constexpr uint32_t kSortRounds = 16;
-constexpr uint32_t kSortTile = kSortThreads * kSortRounds;
+constexpr uint32_t kSortWaves = kSortThreads / 64;
 constexpr uint32_t kSortDigits = 256;
 constexpr uint32_t kSortPasses = 8;
 
@@ -273,68 +283,91 @@ __device__ __forceinline__ uint64_t same_digit_lanes(uint32_t d, uint64_t valid)
     return peers;
 }
 
+// counts: tile-major with FUSED (see sort_pass), digit-major else.
+template <uint32_t ROUNDS, bool FUSED>
 __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(const uint64_t* __restrict__ key, uint32_t n,
                                                                   uint32_t shift, uint32_t n_tiles,
                                                                   uint32_t* __restrict__ counts) {
-    __shared__ uint32_t hist[kSortDigits];
-    const uint32_t t = threadIdx.x;
-    hist[t] = 0u;
+    __shared__ uint32_t hist[kSortWaves][kSortDigits];   // a wave's own counts
+    const uint32_t t = threadIdx.x, w = t >> 6;
+    for (uint32_t q = 0; q < kSortWaves; ++q) hist[q][t] = 0u;
     __syncthreads();
-    const uint32_t base = blockIdx.x * kSortTile;
-    for (uint32_t r = 0; r < kSortRounds; ++r) {
+    const uint32_t base = blockIdx.x * kSortThreads * ROUNDS;
+#pragma unroll
+    for (uint32_t r = 0; r < ROUNDS; ++r) {
         const uint32_t i = base + r * kSortThreads + t;
-        const bool ok = i < n;
-        const uint32_t d = ok ? (uint32_t)(key[i] >> shift) & (kSortDigits - 1u) : 0u;
-        const uint64_t peers = same_digit_lanes(d, __builtin_amdgcn_ballot_w64(ok));
-        if (ok && lanes_below(peers) == 0u) atomicAdd(&hist[d], (uint32_t)__popcll(peers));
+        if (i < n) atomicAdd(&hist[w][(uint32_t)(key[i] >> shift) & (kSortDigits - 1u)], 1u);
     }
     __syncthreads();
-    counts[(size_t)t * n_tiles + blockIdx.x] = hist[t];
+    uint32_t sum = 0;
+    for (uint32_t q = 0; q < kSortWaves; ++q) sum += hist[q][t];
+    counts[FUSED ? (size_t)blockIdx.x * kSortDigits + t : (size_t)t * n_tiles + blockIdx.x] = sum;
 }
 
+template <uint32_t ROUNDS, bool FUSED>
 __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(const uint64_t* __restrict__ kin,
                                                                     const uint32_t* __restrict__ vin, uint32_t n,
                                                                     uint32_t shift, uint32_t n_tiles,
                                                                     const uint32_t* __restrict__ first,
                                                                     uint64_t* __restrict__ kout,
                                                                     uint32_t* __restrict__ vout) {
-    // next[d]: the tile's next output position for digit d (thread d owns it).
-    // pos[r & 1][w][d]: keys of digit d in wave w of round r, then the first
-    // position of those keys; the other parity is cleared for the next round.
-    __shared__ uint32_t next[kSortDigits];
-    __shared__ uint32_t pos[2][kSortThreads / 64][kSortDigits];
-    const uint32_t t = threadIdx.x, w = t >> 6;
-    next[t] = first[(size_t)t * n_tiles + blockIdx.x];
-    for (uint32_t q = 0; q < kSortThreads / 64; ++q) {
-        pos[0][q][t] = 0u;
-        pos[1][q][t] = 0u;
-    }
+    // pos[w][d]: keys of digit d in wave w's run, then their first position
+    __shared__ uint32_t pos[kSortWaves][kSortDigits];
+    const uint32_t t = threadIdx.x, w = t >> 6, lane = t & 63u;
+    for (uint32_t q = 0; q < kSortWaves; ++q) pos[q][t] = 0u;
     __syncthreads();
-    const uint32_t base = blockIdx.x * kSortTile;
-    for (uint32_t r = 0; r < kSortRounds; ++r) {
-        const uint32_t p = r & 1u;
-        const uint32_t i = base + r * kSortThreads + t;
-        const bool ok = i < n;
-        const uint64_t k = ok ? kin[i] : 0ull;
-        const uint32_t v = ok ? vin[i] : 0u;
-        const uint32_t d = (uint32_t)(k >> shift) & (kSortDigits - 1u);
+    const uint32_t base = (blockIdx.x * kSortWaves + w) * 64u * ROUNDS;
+    uint64_t k[ROUNDS];
+    uint32_t v[ROUNDS], rank[ROUNDS];
+#pragma unroll
+    for (uint32_t r = 0; r < ROUNDS; ++r) {
+        const uint32_t i = base + r * 64u + lane;
+        k[r] = i < n ? kin[i] : 0ull;
+        v[r] = i < n ? vin[i] : 0u;
+    }
+    // this tile's first position of digit t (the loads overlap the ranking)
+    uint32_t start;
+    if (FUSED) {
+        // the keys of smaller digits, and those of digit t in earlier tiles
+        __shared__ uint32_t lds[4];
+        uint32_t all = 0, before = 0, total;
+#pragma unroll 8
+        for (uint32_t b = 0; b < n_tiles; ++b) {
+            const uint32_t x = first[(size_t)b * kSortDigits + t];
+            all += x;
+            before += b < blockIdx.x ? x : 0u;
+        }
+        start = scan::block_inclusive_256(all, lds, &total) - all + before;
+    } else {
+        start = first[(size_t)t * n_tiles + blockIdx.x];
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < ROUNDS; ++r) {
+        const bool ok = base + r * 64u + lane < n;
+        const uint32_t d = (uint32_t)(k[r] >> shift) & (kSortDigits - 1u);
         const uint64_t peers = same_digit_lanes(d, __builtin_amdgcn_ballot_w64(ok));
         const uint32_t below = lanes_below(peers);
-        if (ok && below == 0u) pos[p][w][d] = (uint32_t)__popcll(peers);
-        __syncthreads();
-        uint32_t run = next[t];
-        for (uint32_t q = 0; q < kSortThreads / 64; ++q) {
-            const uint32_t c = pos[p][q][t];
-            pos[p][q][t] = run;
-            run += c;
-            pos[p ^ 1u][q][t] = 0u;
-        }
-        next[t] = run;
-        __syncthreads();
-        if (ok) {
-            const uint32_t at = pos[p][w][d] + below;
-            kout[at] = k;
-            vout[at] = v;
+        const uint32_t seen = pos[w][d];
+        rank[r] = seen + below;
+        // every lane has read its digit's count (one wave runs in lock step,
+        // its LDS accesses in order) before the first lane of each digit adds
+        __builtin_amdgcn_wave_barrier();
+        if (ok && below == 0u) pos[w][d] = seen + (uint32_t)__popcll(peers);
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    for (uint32_t q = 0; q < kSortWaves; ++q) {
+        const uint32_t c = pos[q][t];
+        pos[q][t] = start;
+        start += c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < ROUNDS; ++r) {
+        if (base + r * 64u + lane < n) {
+            const uint32_t at = pos[w][(uint32_t)(k[r] >> shift) & (kSortDigits - 1u)] + rank[r];
+            kout[at] = k[r];
+            vout[at] = v[r];
         }
     }
 }
@@ -369,6 +402,34 @@ extern "C" hipError_t hrr_dev_codes(const float* xyz, uint32_t n, const float* q
 
 size_t align256(size_t b) { return (b + 255u) & ~(size_t)255u; }
 
+// Rounds of 256 keys per tile of the sort: 8 for large inputs, fewer where that
+// would leave CUs without a tile.  us a build at 2 / 4 / 8 / 16 rounds: 20,011
+// lights 188 / 199 / 214 / 263, 2^17 291 / 254 / 252 / 287, 2^18 415 / 330 /
+// 303 / 329, 2^20 607 / 553 / 543 / 573.
+uint32_t sort_rounds(uint32_t n) { return n >= (1u << 18) ? 8u : n >= (1u << 16) ? 4u : 2u; }
+
+// FUSED: up to kSortFused tiles every scatter block adds up the tile counts it
+// needs itself (tile-major counts, 1 KB per tile out of L2) instead of three
+// scan launches between the two (12 us of a pass of 20 at 20,011 keys); beyond,
+// that reading grows with the square of the tiles (2^20 keys in 512 tiles: 613
+// us a build against 543 with the scan).
+constexpr uint32_t kSortFused = 128;
+
+template <uint32_t ROUNDS>
+hipError_t sort_pass(const uint64_t* ks, const uint32_t* vs, uint32_t n, uint32_t shift, uint32_t n_tiles,
+                     uint32_t* counts, uint32_t* sums, uint64_t* kd, uint32_t* vd, hipStream_t stream) {
+    if (n_tiles <= kSortFused) {
+        sort_count_kernel<ROUNDS, true><<<n_tiles, kSortThreads, 0, stream>>>(ks, n, shift, n_tiles, counts);
+        sort_scatter_kernel<ROUNDS, true><<<n_tiles, kSortThreads, 0, stream>>>(ks, vs, n, shift, n_tiles, counts, kd, vd);
+        return hipGetLastError();
+    }
+    sort_count_kernel<ROUNDS, false><<<n_tiles, kSortThreads, 0, stream>>>(ks, n, shift, n_tiles, counts);
+    hipError_t e = scan::exclusive_sum(counts, counts, n_tiles * kSortDigits, sums, stream);
+    if (e != hipSuccess) return e;
+    sort_scatter_kernel<ROUNDS, false><<<n_tiles, kSortThreads, 0, stream>>>(ks, vs, n, shift, n_tiles, counts, kd, vd);
+    return hipGetLastError();
+}
+
 // Stable radix sort of (code, index) by code (63 low bits); temp == nullptr
 // queries temp_bytes.  Scratch: a second key and index buffer (the passes
 // alternate between it and the outputs, the last pass landing in the
@@ -377,7 +438,8 @@ extern "C" hipError_t hrr_dev_sort(void* temp, size_t* temp_bytes, const uint64_
                                    const uint32_t* idx_in, uint32_t* idx_out, uint32_t n, hipStream_t stream) {
     static_assert(kSortPasses % 2 == 0, "the last pass must write the outputs");
     if (!temp_bytes) return hipErrorInvalidValue;
-    const uint32_t n_tiles = (n + kSortTile - 1u) / kSortTile;
+    const uint32_t rounds = sort_rounds(n), tile = kSortThreads * rounds;
+    const uint32_t n_tiles = (n + tile - 1u) / tile;
     const uint32_t n_counts = n_tiles * kSortDigits;
     const size_t b_keys = align256((size_t)n * 8u), b_idx = align256((size_t)n * 4u);
     const size_t b_counts = align256((size_t)n_counts * 4u), b_sums = align256((size_t)scan::chunk_count(n_counts) * 4u);
@@ -399,66 +461,59 @@ extern "C" hipError_t hrr_dev_sort(void* temp, size_t* temp_bytes, const uint64_
         uint64_t* kd = (pass & 1u) ? code_out : k_tmp;
         uint32_t* vd = (pass & 1u) ? idx_out : v_tmp;
         const uint32_t shift = 8u * pass;
-        sort_count_kernel<<<n_tiles, kSortThreads, 0, stream>>>(ks, n, shift, n_tiles, counts);
-        hipError_t e = scan::exclusive_sum(counts, counts, n_counts, sums, stream);
+        const hipError_t e = rounds == 4u ? sort_pass<4>(ks, vs, n, shift, n_tiles, counts, sums, kd, vd, stream)
+                             : rounds == 8u ? sort_pass<8>(ks, vs, n, shift, n_tiles, counts, sums, kd, vd, stream)
+                                          : sort_pass<2>(ks, vs, n, shift, n_tiles, counts, sums, kd, vd, stream);
         if (e != hipSuccess) return e;
-        sort_scatter_kernel<<<n_tiles, kSortThreads, 0, stream>>>(ks, vs, n, shift, n_tiles, counts, kd, vd);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
         ks = kd;
         vs = vd;
     }
     return hipSuccess;
 }
 
-// out[i] = in[0] + ... + in[i - 1]; temp == nullptr queries temp_bytes.
-extern "C" hipError_t hrr_dev_exclusive_sum(void* temp, size_t* temp_bytes, const uint32_t* in, uint32_t* out,
-                                            uint32_t n, hipStream_t stream) {
-    if (!temp_bytes) return hipErrorInvalidValue;
-    const size_t need = std::max<size_t>(align256((size_t)scan::chunk_count(n) * 4u), 256u);
-    if (!temp) {
-        *temp_bytes = need;
-        return hipSuccess;
-    }
-    if (*temp_bytes < need) return hipErrorInvalidValue;
-    return scan::exclusive_sum(in, out, n, static_cast<uint32_t*>(temp), stream);
-}
-
-extern "C" hipError_t hrr_dev_gather(const float* xyz, const uint32_t* perm, uint32_t n, float4* lights,
-                                     hipStream_t stream) {
+extern "C" hipError_t hrr_dev_gather(const float* xyz, const uint32_t* order, uint32_t n, float* lights,
+                                     uint32_t* perm, hipStream_t stream) {
     if (n == 0) return hipSuccess;
-    gather_kernel<<<blocks_for(n), kThreads, 0, stream>>>(xyz, perm, n, lights);
+    gather_kernel<<<blocks_for(n), kThreads, 0, stream>>>(xyz, order, n, reinterpret_cast<float4*>(lights), perm);
     return hipGetLastError();
 }
 
-extern "C" hipError_t hrr_dev_init_root(Bfs T, uint32_t n, hipStream_t stream) {
-    init_root_kernel<<<1, 64, 0, stream>>>(T, n);
+// Words of scratch behind the node tables (see hrr_dev_nodes), n >= 2.
+extern "C" size_t hrr_dev_nodes_words(uint32_t n) {
+    // range (2), parent, first: n each; owners n + 1; chunk sums of the scan
+    return 5 * (size_t)n + 1 + scan::chunk_count(n + 1u) + 8;
+}
+
+namespace {
+struct NodeTables {
+    uint2* range;
+    uint32_t *parent, *first, *owners, *sums;
+    NodeTables(uint32_t* words, uint32_t n)
+        : range(reinterpret_cast<uint2*>(words)), parent(words + 2 * (size_t)n), first(parent + n), owners(first + n),
+          sums(owners + n + 1) {}
+};
+}  // namespace
+
+// Ranges, parents and record numbers of the internal nodes of n >= 2 lights
+// with the given sorted codes; out[0] = owners, out[1] = depth (both zeroed by
+// the caller).
+extern "C" hipError_t hrr_dev_nodes(const uint64_t* code, uint32_t n, uint32_t leaf, uint32_t pow2, uint32_t* words,
+                                    uint32_t* out, hipStream_t stream) {
+    const NodeTables T(words, n);
+    hipError_t e = hipMemsetAsync(T.owners, 0, ((size_t)n + 1) * sizeof(uint32_t), stream);
+    if (e != hipSuccess) return e;
+    nodes_kernel<<<blocks_for(n - 1), kThreads, 0, stream>>>(code, n, leaf, pow2, T.range, T.parent, T.owners);
+    if ((e = scan::exclusive_sum(T.owners, T.owners, n + 1u, T.sums, stream)) != hipSuccess) return e;
+    ranks_kernel<<<blocks_for(n - 1), kThreads, 0, stream>>>(T.range, T.parent, T.owners, n, leaf, T.first, out);
     return hipGetLastError();
 }
 
-extern "C" hipError_t hrr_dev_split(Bfs T, const uint64_t* code, uint32_t t0, uint32_t t1, uint32_t leaf,
-                                    uint32_t pow2, uint32_t* kids, hipStream_t stream) {
-    split_kernel<<<blocks_for(t1 - t0), kThreads, 0, stream>>>(T, code, t0, t1, leaf, pow2, kids);
-    return hipGetLastError();
-}
-
-extern "C" hipError_t hrr_dev_place(Bfs T, uint32_t t0, uint32_t t1, uint32_t leaf, const uint32_t* prefix,
-                                    uint32_t cap, hipStream_t stream) {
-    place_kernel<<<blocks_for(t1 - t0), kThreads, 0, stream>>>(T, t0, t1, leaf, prefix, cap);
-    return hipGetLastError();
-}
-
-extern "C" hipError_t hrr_dev_refit(Bfs T, const float4* lights, uint32_t t0, uint32_t t1, hipStream_t stream) {
-    refit_kernel<<<blocks_for(t1 - t0), kThreads, 0, stream>>>(T, lights, t0, t1);
-    return hipGetLastError();
-}
-
-extern "C" hipError_t hrr_dev_records(Bfs T, const float4* lights, uint32_t t0, uint32_t t1, Node* nodes,
-                                      hipStream_t stream) {
-    record_kernel<<<blocks_for(t1 - t0), kThreads, 0, stream>>>(T, lights, t0, t1, nodes);
-    return hipGetLastError();
-}
-
-extern "C" hipError_t hrr_dev_root_leaf_box(const float4* lights, uint32_t n, float* box, hipStream_t stream) {
-    root_leaf_box_kernel<<<1, 64, 0, stream>>>(lights, n, box);
+// The records of those nodes (zeroed by the caller where no node writes).
+extern "C" hipError_t hrr_dev_records(const uint32_t* words, uint32_t n, const float* lights, const float* blocks,
+                                      Node* nodes, hipStream_t stream) {
+    const NodeTables T(const_cast<uint32_t*>(words), n);
+    records_kernel<<<blocks_for(n - 1), kThreads, 0, stream>>>(
+        T.range, T.parent, T.first, reinterpret_cast<const float4*>(lights), reinterpret_cast<const float4*>(blocks),
+        block_tree_log(n), n, nodes);
     return hipGetLastError();
 }

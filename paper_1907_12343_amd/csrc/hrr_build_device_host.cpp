@@ -14,44 +14,52 @@
 #define HRR_EXPORT extern "C" __attribute__((visibility("default")))
 
 using hrr::Node;
-using hrr::devbuild::Bfs;
 
 extern "C" hipError_t hrr_dev_codes(const float* xyz, uint32_t n, const float* qbox, uint64_t* code, uint32_t* idx,
                                     uint32_t* bad, hipStream_t stream);
 extern "C" hipError_t hrr_dev_sort(void* temp, size_t* temp_bytes, const uint64_t* code_in, uint64_t* code_out,
                                    const uint32_t* idx_in, uint32_t* idx_out, uint32_t n, hipStream_t stream);
-extern "C" hipError_t hrr_dev_exclusive_sum(void* temp, size_t* temp_bytes, const uint32_t* in, uint32_t* out,
-                                            uint32_t n, hipStream_t stream);
-extern "C" hipError_t hrr_dev_gather(const float* xyz, const uint32_t* perm, uint32_t n, float4* lights,
-                                     hipStream_t stream);
-extern "C" hipError_t hrr_dev_init_root(Bfs T, uint32_t n, hipStream_t stream);
-extern "C" hipError_t hrr_dev_split(Bfs T, const uint64_t* code, uint32_t t0, uint32_t t1, uint32_t leaf,
-                                    uint32_t pow2, uint32_t* kids, hipStream_t stream);
-extern "C" hipError_t hrr_dev_place(Bfs T, uint32_t t0, uint32_t t1, uint32_t leaf, const uint32_t* prefix,
-                                    uint32_t cap, hipStream_t stream);
-extern "C" hipError_t hrr_dev_refit(Bfs T, const float4* lights, uint32_t t0, uint32_t t1, hipStream_t stream);
-extern "C" hipError_t hrr_dev_records(Bfs T, const float4* lights, uint32_t t0, uint32_t t1, Node* nodes,
-                                      hipStream_t stream);
-extern "C" hipError_t hrr_dev_root_leaf_box(const float4* lights, uint32_t n, float* box, hipStream_t stream);
+extern "C" hipError_t hrr_dev_gather(const float* xyz, const uint32_t* order, uint32_t n, float* lights,
+                                     uint32_t* perm, hipStream_t stream);
+extern "C" size_t hrr_dev_nodes_words(uint32_t n);
+extern "C" hipError_t hrr_dev_nodes(const uint64_t* code, uint32_t n, uint32_t leaf, uint32_t pow2, uint32_t* words,
+                                    uint32_t* out, hipStream_t stream);
+extern "C" hipError_t hrr_dev_records(const uint32_t* words, uint32_t n, const float* lights, const float* blocks,
+                                      Node* nodes, hipStream_t stream);
+extern "C" hipError_t hrr_launch_frontier(const Node* nodes, uint32_t n_lights, uint32_t leaf_size, float* out,
+                                          hipStream_t stream);   // hrr_kernels.hip
+extern "C" hipError_t hrr_launch_blocks(const float* lights, uint32_t n_lights, float* blocks, hipStream_t stream);
 
 namespace {
 
-// Device allocations of one build, released on every exit path.
-struct Temps {
-    std::vector<void*> ptrs;
-    ~Temps() {
-        for (void* p : ptrs) (void)hipFree(p);
-    }
+// Carves 256-byte aligned pieces out of one allocation (or, with no base,
+// adds up what they need).
+struct Carver {
+    unsigned char* base;
+    size_t at = 0;
     template <typename T>
-    hipError_t get(T** p, size_t count) {
-        void* q = nullptr;
-        const hipError_t e = hipMalloc(&q, std::max<size_t>(count, 1) * sizeof(T));
-        if (e != hipSuccess) return e;
-        ptrs.push_back(q);
-        *p = static_cast<T*>(q);
-        return hipSuccess;
+    T* take(size_t count) {
+        T* p = base ? reinterpret_cast<T*>(base + at) : nullptr;
+        at += (count * sizeof(T) + 255) / 256 * 256;
+        return p;
     }
 };
+
+// Build scratch of n lights.
+struct Scratch {
+    uint32_t* status;   // [0] owners, [1] depth, [2] non-finite coordinate seen
+    uint64_t *code_in, *code;
+    uint32_t *idx_in, *order, *nodes;
+    unsigned char* sort;
+    Scratch(Carver& c, uint32_t n, size_t sort_bytes)
+        : status(c.take<uint32_t>(8)), code_in(c.take<uint64_t>(n)), code(c.take<uint64_t>(n)),
+          idx_in(c.take<uint32_t>(n)), order(c.take<uint32_t>(n)), nodes(c.take<uint32_t>(hrr_dev_nodes_words(n))),
+          sort(c.take<unsigned char>(sort_bytes)) {}
+};
+
+// Scratch kept between builds is at most this much (2^22 lights need 0.3 GB);
+// a larger build gives its own back.
+constexpr size_t kKeepScratch = (size_t)512 << 20;
 
 }  // namespace
 
@@ -85,130 +93,95 @@ HRR_EXPORT hrr_status hrr_build_hierarchy_device(hrr_ctx* ctx, const float* ligh
     h->leaf_size = leaf_size;
     h->split = split;
     h->host_copies = false;
+    struct Release {   // of a scratch too large to keep, on every path
+        DevBuf& b;
+        ~Release() {
+            if (b.bytes > kKeepScratch) b.release();
+        }
+    } release{ctx->build_scratch};
     auto fail_free = [&](hrr_status st) {
+        (void)hipStreamSynchronize(stream);   // the scratch is the context's
         hrr_free_hierarchy(ctx, h);
         return st;
     };
-    // node records: allocated once their number is known (after the refit)
-    if ((max_internal == 0 && (e = hipMalloc((void**)&h->d_nodes, sizeof(Node))) != hipSuccess) ||
-        (e = hipMalloc((void**)&h->d_lights, std::max<size_t>(n, 1) * 4 * sizeof(float))) != hipSuccess ||
-        (e = hipMalloc((void**)&h->d_perm, std::max<size_t>(n, 1) * sizeof(uint32_t))) != hipSuccess)
-        return fail_free(hip_fail(e, "hierarchy allocation"));
-    h->device_bytes = (max_internal == 0 ? sizeof(Node) : 0) + std::max<size_t>(n, 1) * 20;
-
-    Temps tmp;
-    uint64_t *code_in = nullptr, *code = nullptr;
-    uint32_t *idx_in = nullptr, *bad = nullptr, *kids = nullptr, *prefix = nullptr, *pin = nullptr;
-    float* d_box = nullptr;
-    Bfs T{};
-    if ((e = tmp.get(&code_in, n)) != hipSuccess || (e = tmp.get(&code, n)) != hipSuccess ||
-        (e = tmp.get(&idx_in, n)) != hipSuccess || (e = tmp.get(&bad, 1)) != hipSuccess ||
-        (e = tmp.get(&d_box, 6)) != hipSuccess)
-        return fail_free(hip_fail(e, "build scratch"));
-    if (max_internal &&
-        ((e = tmp.get(&T.a, max_internal)) != hipSuccess || (e = tmp.get(&T.c, max_internal)) != hipSuccess ||
-         (e = tmp.get(&T.b, max_internal)) != hipSuccess || (e = tmp.get(&T.l, max_internal)) != hipSuccess ||
-         (e = tmp.get(&T.r, max_internal)) != hipSuccess || (e = tmp.get(&T.cnt, max_internal)) != hipSuccess ||
-         (e = tmp.get(&T.pre, max_internal)) != hipSuccess || (e = tmp.get(&T.own, max_internal)) != hipSuccess || (e = tmp.get(&T.box, 6 * (size_t)max_internal)) != hipSuccess ||
-         (e = tmp.get(&kids, max_internal)) != hipSuccess || (e = tmp.get(&prefix, max_internal)) != hipSuccess))
-        return fail_free(hip_fail(e, "build scratch"));
-    if ((e = hipHostMalloc((void**)&pin, 16 * sizeof(uint32_t), hipHostMallocDefault)) != hipSuccess)
+    if (!ctx->build_pin && (e = hipHostMalloc((void**)&ctx->build_pin, 16 * sizeof(uint32_t), hipHostMallocDefault)) != hipSuccess)
         return fail_free(hip_fail(e, "build staging"));
-    struct PinFree {
-        uint32_t* p;
-        ~PinFree() { (void)hipHostFree(p); }
-    } pin_free{pin};
+    uint32_t* const pin = ctx->build_pin;
 
-    // 1-3: codes, sort, gather
-    if ((e = hipMemsetAsync(bad, 0, sizeof(uint32_t), stream)) != hipSuccess) return fail_free(hip_fail(e, "build"));
+    // everything that is known before the records: one allocation, the records another
+    const uint32_t block_log = block_tree_log(n);
+    size_t sort_bytes = 0;
+    if ((e = hrr_dev_sort(nullptr, &sort_bytes, nullptr, nullptr, nullptr, nullptr, n, stream)) != hipSuccess)
+        return fail_free(hip_fail(e, "sort size"));
+    Carver size{nullptr};
+    (void)Scratch(size, n, sort_bytes);
+    if ((e = ctx->build_scratch.ensure(size.at)) != hipSuccess) return fail_free(hip_fail(e, "build scratch"));
+    Carver carve{static_cast<unsigned char*>(ctx->build_scratch.p)};
+    const Scratch T(carve, n, sort_bytes);
+    const size_t n_block_floats = n ? (size_t)block_tree_slots(block_log) * kBlockFloats : 0;
+    const size_t n_frontier_floats = max_internal ? (size_t)kFrontierMax * kFrontierFloats + 1 : 0;
+    auto tables = [&](Carver& c) {
+        h->d_lights = c.take<float>(std::max<size_t>(n, 1) * 4);
+        h->d_perm = c.take<uint32_t>(std::max<size_t>(n, 1));
+        float* blocks = c.take<float>(n_block_floats);
+        float* frontier = c.take<float>(n_frontier_floats);
+        h->d_blocks = n ? blocks : nullptr;
+        h->d_frontier = max_internal ? frontier : nullptr;
+        if (!max_internal) h->d_nodes = c.take<Node>(1);
+    };
+    Carver need{nullptr};
+    tables(need);
+    if ((e = ctx->blocks.get(&h->d_base, need.at)) != hipSuccess) return fail_free(hip_fail(e, "hierarchy allocation"));
+    Carver own{static_cast<unsigned char*>(h->d_base)};
+    tables(own);
+    h->device_bytes = need.at;
+
+    // 1-3: codes, sort, gather, block tree
+    if ((e = hipMemsetAsync(T.status, 0, 8 * sizeof(uint32_t), stream)) != hipSuccess) return fail_free(hip_fail(e, "build"));
     if (n) {
-        if ((e = hrr_dev_codes(lights_xyz_dev, n, qbox, code_in, idx_in, bad, stream)) != hipSuccess)
+        if ((e = hrr_dev_codes(lights_xyz_dev, n, qbox, T.code_in, T.idx_in, T.status + 2, stream)) != hipSuccess)
             return fail_free(hip_fail(e, "Morton codes"));
-        size_t sort_bytes = 0;
-        if ((e = hrr_dev_sort(nullptr, &sort_bytes, code_in, code, idx_in, h->d_perm, n, stream)) != hipSuccess)
-            return fail_free(hip_fail(e, "sort size"));
-        void* sort_tmp = nullptr;
-        if ((e = tmp.get((unsigned char**)&sort_tmp, sort_bytes)) != hipSuccess) return fail_free(hip_fail(e, "sort scratch"));
-        if ((e = hrr_dev_sort(sort_tmp, &sort_bytes, code_in, code, idx_in, h->d_perm, n, stream)) != hipSuccess)
+        if ((e = hrr_dev_sort(T.sort, &sort_bytes, T.code_in, T.code, T.idx_in, T.order, n, stream)) != hipSuccess)
             return fail_free(hip_fail(e, "sort"));
-        if ((e = hrr_dev_gather(lights_xyz_dev, h->d_perm, n, reinterpret_cast<float4*>(h->d_lights), stream)) !=
-            hipSuccess)
+        if ((e = hrr_dev_gather(lights_xyz_dev, T.order, n, h->d_lights, h->d_perm, stream)) != hipSuccess)
             return fail_free(hip_fail(e, "gather"));
+        if ((e = hrr_launch_blocks(h->d_lights, n, h->d_blocks, stream)) != hipSuccess)
+            return fail_free(hip_fail(e, "block tree"));
     }
-
-    // 4: breadth-first levels
-    std::vector<uint32_t> off{0};
-    if (max_internal) {
-        size_t scan_bytes = 0;
-        if ((e = hrr_dev_exclusive_sum(nullptr, &scan_bytes, kids, prefix, max_internal, stream)) != hipSuccess)
-            return fail_free(hip_fail(e, "scan size"));
-        void* scan_tmp = nullptr;
-        if ((e = tmp.get((unsigned char**)&scan_tmp, scan_bytes)) != hipSuccess) return fail_free(hip_fail(e, "scan scratch"));
-        if ((e = hrr_dev_init_root(T, n, stream)) != hipSuccess) return fail_free(hip_fail(e, "root"));
-        uint32_t t0 = 0, t1 = 1;
-        off.push_back(1);
-        while (t1 > t0) {
-            const uint32_t m = t1 - t0;
-            if ((e = hrr_dev_split(T, code, t0, t1, leaf_size, split == HRR_SPLIT_POW2 ? 1u : 0u, kids, stream)) != hipSuccess ||
-                (e = hrr_dev_exclusive_sum(scan_tmp, &scan_bytes, kids, prefix, m, stream)) != hipSuccess ||
-                (e = hipMemcpyAsync(pin, prefix + (m - 1), sizeof(uint32_t), hipMemcpyDeviceToHost, stream)) !=
-                    hipSuccess ||
-                (e = hipMemcpyAsync(pin + 1, kids + (m - 1), sizeof(uint32_t), hipMemcpyDeviceToHost, stream)) !=
-                    hipSuccess ||
-                (e = hrr_dev_place(T, t0, t1, leaf_size, prefix, max_internal, stream)) != hipSuccess ||
-                (e = hipStreamSynchronize(stream)) != hipSuccess)
-                return fail_free(hip_fail(e, "level split"));
-            const uint64_t next = (uint64_t)pin[0] + pin[1];
-            if ((uint64_t)t1 + next > max_internal) return fail_free(fail(HRR_E_DEVICE, "device build: node count overflow"));
-            t0 = t1;
-            t1 += (uint32_t)next;
-            if (t1 > t0) off.push_back(t1);
-        }
-        const size_t levels = off.size() - 1;
-        // 5: refit, deepest level first; 6: records, root level first
-        for (size_t L = levels; L-- > 0;)
-            if ((e = hrr_dev_refit(T, reinterpret_cast<const float4*>(h->d_lights), off[L], off[L + 1], stream)) !=
-                hipSuccess)
-                return fail_free(hip_fail(e, "refit"));
-        // records: the root, the unused record 1, then one sibling pair per
-        // node with an internal child (the root's subtree count)
-        if ((e = hipMemcpyAsync(pin + 3, T.cnt, sizeof(uint32_t), hipMemcpyDeviceToHost, stream)) != hipSuccess ||
-            (e = hipStreamSynchronize(stream)) != hipSuccess)
-            return fail_free(hip_fail(e, "record count"));
-        if (pin[3] > max_internal) return fail_free(fail(HRR_E_DEVICE, "device build: record count overflow"));
-        const uint32_t n_records = 2u * (1u + pin[3]);
-        if ((e = hipMalloc((void**)&h->d_nodes, (size_t)n_records * sizeof(Node))) != hipSuccess ||
-            (e = hipMemsetAsync(h->d_nodes, 0, (size_t)n_records * sizeof(Node), stream)) != hipSuccess)
-            return fail_free(hip_fail(e, "node records"));
-        h->device_bytes += (size_t)n_records * sizeof(Node);
-        for (size_t L = 0; L < levels; ++L)
-            if ((e = hrr_dev_records(T, reinterpret_cast<const float4*>(h->d_lights), off[L], off[L + 1], h->d_nodes,
-                                     stream)) != hipSuccess)
-                return fail_free(hip_fail(e, "records"));
-        if ((e = hipMemcpyAsync(d_box, T.box, 6 * sizeof(float), hipMemcpyDeviceToDevice, stream)) != hipSuccess)
-            return fail_free(hip_fail(e, "root box"));
-        h->n_nodes = n_records;
-        h->depth = (uint32_t)(levels - 1);
-        const hrr_status st = attach_frontier(h, stream);
-        if (st != HRR_OK) return fail_free(st);
-        if ((e = hipMemcpyAsync(pin + 4, h->d_frontier + (size_t)kFrontierMax * kFrontierFloats, sizeof(uint32_t),
-                                hipMemcpyDeviceToHost, stream)) != hipSuccess)
-            return fail_free(hip_fail(e, "hierarchy top"));
-    } else if (n) {
-        if ((e = hrr_dev_root_leaf_box(reinterpret_cast<const float4*>(h->d_lights), n, d_box, stream)) != hipSuccess)
-            return fail_free(hip_fail(e, "root box"));
-    }
-    const hrr_status bst = attach_blocks(h, stream);
-    if (bst != HRR_OK) return fail_free(bst);
-    float root_box[6] = {0, 0, 0, 0, 0, 0};
-    if (n && (e = hipMemcpyAsync(root_box, d_box, sizeof root_box, hipMemcpyDeviceToHost, stream)) != hipSuccess)
-        return fail_free(hip_fail(e, "root box"));
-    if ((e = hipMemcpyAsync(pin + 2, bad, sizeof(uint32_t), hipMemcpyDeviceToHost, stream)) != hipSuccess ||
+    // 4-5: nodes and record numbers
+    if (max_internal && (e = hrr_dev_nodes(T.code, n, leaf_size, split == HRR_SPLIT_POW2 ? 1u : 0u, T.nodes, T.status,
+                                           stream)) != hipSuccess)
+        return fail_free(hip_fail(e, "nodes"));
+    // owners, depth, bad input, and the root box (the block tree's first block)
+    float root[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if ((e = hipMemcpyAsync(pin, T.status, 3 * sizeof(uint32_t), hipMemcpyDeviceToHost, stream)) != hipSuccess ||
+        (n && (e = hipMemcpyAsync(pin + 4, h->d_blocks + kBlockFloats, sizeof root, hipMemcpyDeviceToHost, stream)) !=
+                  hipSuccess) ||
         (e = hipStreamSynchronize(stream)) != hipSuccess)
         return fail_free(hip_fail(e, "device build"));
     if (pin[2]) return fail_free(fail(HRR_E_INVALID, "non-finite light coordinate"));
-    if (h->d_frontier) h->n_frontier = pin[4];
-    memcpy(h->box, root_box, sizeof root_box);
+    if (n) memcpy(root, pin + 4, sizeof root);
+    memcpy(h->box, root, 3 * sizeof(float));
+    memcpy(h->box + 3, root + 4, 3 * sizeof(float));
+    if (max_internal) {
+        // 6: the root, the unused record 1, then one sibling pair per owner
+        if (pin[0] > max_internal) return fail_free(fail(HRR_E_DEVICE, "device build: record count overflow"));
+        const uint32_t n_records = 2u * (1u + pin[0]);
+        h->depth = pin[1];
+        if ((e = ctx->blocks.get((void**)&h->d_nodes, (size_t)n_records * sizeof(Node))) != hipSuccess)
+            return fail_free(hip_fail(e, "node records"));
+        h->n_nodes = n_records;
+        h->device_bytes += (size_t)n_records * sizeof(Node);
+        if ((e = hipMemsetAsync(h->d_nodes, 0, (size_t)n_records * sizeof(Node), stream)) != hipSuccess ||
+            (e = hrr_dev_records(T.nodes, n, h->d_lights, h->d_blocks, h->d_nodes, stream)) != hipSuccess)
+            return fail_free(hip_fail(e, "node records"));
+        if ((e = hrr_launch_frontier(h->d_nodes, n, leaf_size, h->d_frontier, stream)) != hipSuccess ||
+            (e = hipMemcpyAsync(pin, h->d_frontier + (size_t)kFrontierMax * kFrontierFloats, sizeof(uint32_t),
+                                hipMemcpyDeviceToHost, stream)) != hipSuccess ||
+            (e = hipStreamSynchronize(stream)) != hipSuccess)
+            return fail_free(hip_fail(e, "hierarchy top"));
+        h->n_frontier = pin[0];
+    }
     *out = h;
     return HRR_OK;
 }

@@ -22,12 +22,13 @@ struct hrr_hierarchy {
     float* d_frontier = nullptr;      // kFrontierMax entries of kFrontierFloats, then the entry count
     uint32_t n_frontier = 0;
     float* d_blocks = nullptr;        // block tree (hrr_types.hpp), for n_lights > 0
+    void* d_base = nullptr;           // device build: the one allocation of every table but d_nodes
     float* d_lights = nullptr;       // float4 per light
     uint32_t* d_perm = nullptr;
-    // host copies (filled on demand for hierarchies built on the device)
-    mutable std::vector<uint32_t> perm;
-    mutable std::vector<float> sorted_xyz;
-    mutable bool host_copies = true;
+    // host copies (hierarchies built on the host; the others read the device's)
+    std::vector<uint32_t> perm;
+    std::vector<float> sorted_xyz;
+    bool host_copies = true;
     uint64_t device_bytes = 0;
 };
 
@@ -39,6 +40,26 @@ struct DevBuf {
     size_t bytes = 0;
     hipError_t ensure(size_t want);
     void release();
+};
+
+// Device blocks of freed hierarchies, for the next builds of about their size
+// (hipMalloc and hipFree of a 2^20-light hierarchy's two blocks cost 0.4 ms, a
+// third of its build).  At most kBlockCacheBytes; given back with the context, or
+// when the device runs out of memory.  A block enters only once the device is
+// idle, as hipFree itself would wait, so no work still reads it.
+constexpr size_t kBlockCacheBytes = (size_t)512 << 20;
+struct BlockCache {
+    struct Entry {
+        void* p;
+        size_t bytes;
+    };
+    std::mutex mu;
+    std::vector<Entry> idle;                 // oldest first
+    std::map<void*, size_t> live;            // blocks handed out
+    size_t idle_bytes = 0;
+    hipError_t get(void** p, size_t bytes);  // at least `bytes`
+    void put(void* p);                       // a block from get(), or null
+    void release();                          // every idle block
 };
 
 struct TuneKey {
@@ -108,6 +129,9 @@ struct hrr_ctx {
     std::map<int, uint32_t> tune_leaf;   // log2 lights -> leaf size
     hrr::Server* server = nullptr;
     std::mutex server_mu;
+    hrr::BlockCache blocks;              // of device-built hierarchies
+    hrr::DevBuf build_scratch;           // of device builds, kept between them up to a bound
+    uint32_t* build_pin = nullptr;       // pinned readback words of device builds
     void* noalloc_scratch = nullptr;   // this device's scratch of hrr_traverse_noalloc
 };
 

@@ -1,24 +1,27 @@
-// hrr_devbuild.hpp -- tables of the device hierarchy build, shared by its
-// kernels (hrr_build_device.hip) and its host driver (hrr_api.cpp).
+// hrr_devbuild.hpp -- shared by the kernels that build a hierarchy and its
+// tables on the GPU (hrr_build_device.hip, hrr_kernels.hip).
 #pragma once
 
 #include <stdint.h>
 
-namespace hrr {
-namespace devbuild {
+#ifndef HRR_HD   // host and device inline functions (also defined by hrr_rmq.hpp)
+#if defined(__HIPCC__)
+#define HRR_HD __host__ __device__ __forceinline__
+#else
+#define HRR_HD inline
+#endif
+#endif
 
-// Internal nodes in breadth-first order (device arrays).
-struct Bfs {
-    uint32_t* a;     // range [a, b) split at c
-    uint32_t* c;
-    uint32_t* b;
-    int32_t* l;      // breadth-first number of the internal left child, or -1
-    int32_t* r;      // same for the right child
-    uint32_t* cnt;   // pair owners (nodes with an internal child) in the subtree
-    uint32_t* pre;   // record number
-    uint32_t* own;   // pair owners before the node in depth-first preorder
-    float* box;      // 6 floats per node: lo xyz, hi xyz of its own box
-};
+namespace hrr {
+
+// min / max with the host builder's tie rule (std::min / std::max keep the
+// first operand unless the second is strictly smaller / larger), so that
+// signed zeros come out the same: merged in sequence order, a bound is the
+// first light's that attains it.
+HRR_HD float min_first(float x, float y) { return y < x ? y : x; }
+HRR_HD float max_first(float x, float y) { return x < y ? y : x; }
+
+namespace devbuild {
 
 // Morton quantisation box, lo xyz and hi xyz.
 struct QBox {

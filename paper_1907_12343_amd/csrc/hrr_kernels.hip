@@ -39,6 +39,7 @@
 #include <mutex>
 
 #include "hrr_compact.hpp"
+#include "hrr_devbuild.hpp"
 #include "hrr_rmq.hpp"
 #include "hrr_scan.hpp"
 #include "hrr_types.hpp"
@@ -1438,8 +1439,8 @@ __device__ __forceinline__ void block_levels(float4* blocks, uint32_t level, Blo
             b = lds[4u * t];
             for (uint32_t q = 1; q < 4u; ++q)
                 for (int k = 0; k < 3; ++k) {
-                    b.lo[k] = fminf(b.lo[k], lds[4u * t + q].lo[k]);
-                    b.hi[k] = fmaxf(b.hi[k], lds[4u * t + q].hi[k]);
+                    b.lo[k] = min_first(b.lo[k], lds[4u * t + q].lo[k]);
+                    b.hi[k] = max_first(b.hi[k], lds[4u * t + q].hi[k]);
                 }
             const uint32_t at = blockIdx.x * n + t, count = 1u << (2u * (level - up));
             if (at < count) store_block(blocks, count + at, b);
@@ -1457,9 +1458,9 @@ __global__ __launch_bounds__(256) void block_leaf_kernel(const float4* __restric
         const uint64_t first = (uint64_t)i << leaf_log;
         for (uint32_t q = 0; q < (1u << leaf_log) && first + q < n_lights; ++q) {
             const float4 p = lights[first + q];
-            b.lo[0] = fminf(b.lo[0], p.x); b.hi[0] = fmaxf(b.hi[0], p.x);
-            b.lo[1] = fminf(b.lo[1], p.y); b.hi[1] = fmaxf(b.hi[1], p.y);
-            b.lo[2] = fminf(b.lo[2], p.z); b.hi[2] = fmaxf(b.hi[2], p.z);
+            b.lo[0] = min_first(b.lo[0], p.x); b.hi[0] = max_first(b.hi[0], p.x);
+            b.lo[1] = min_first(b.lo[1], p.y); b.hi[1] = max_first(b.hi[1], p.y);
+            b.lo[2] = min_first(b.lo[2], p.z); b.hi[2] = max_first(b.hi[2], p.z);
         }
         store_block(blocks, (1u << (2u * level)) + i, b);
     }
