@@ -1034,12 +1034,12 @@ void traverse_kernel(TravArgs A) {
 // step run full lanes also where an eye has little work.  Lanes read their
 // eye (position, rotation) from LDS by slot.
 //
-// Stack bound: g popped parents push at most 4 g children.  g is limited so
-// that a step never leaves more than kCullStack - kCullReserve entries, except
-// by popping one parent at a time, which adds at most 3 entries per level
-// (at most 11 levels) until that parent's subtree is done.
+// Stack bound: a step pops 16 parents and pushes at most 64 children while the
+// stack holds at most kCullWide entries, so it leaves at most kCullWide + 48;
+// above kCullWide it pops one parent at a time, which adds at most 3 entries per
+// level (at most 11 levels) until that parent's subtree is done.
 constexpr uint32_t kCullStack = 256;
-constexpr uint32_t kCullReserve = 48;
+constexpr uint32_t kCullWide = 160;       // entries above which parents are popped one at a time
 constexpr uint32_t kCullQueue = 384;      // at least 64 + 16 (see the listing rounds)
 constexpr uint32_t kCullStage = 2 * kWave;        // staged pairs: chunked output
 constexpr uint32_t kCullStageDense = 8 * kWave;   // ... dense output (see DENSE)
@@ -1066,6 +1066,35 @@ struct CullLds {
     uint2* pairs;      // accepted pairs waiting to be stored
     float* d2;         // their squared distances (weights are computed as pairs are stored)
 };
+
+// The item's descriptor through the constant address space: no kernel of the
+// launch writes it, so its fields come by scalar loads into scalar registers
+// (from the generic address the compiler loads them into vector registers and
+// reads them back lane by lane: two or three instructions per use and step).
+__device__ __forceinline__ void load_item(ItemDesc& D, const ItemDesc* p) {
+    typedef const __attribute__((address_space(4))) uint32_t* cptr;
+    const cptr src = (cptr)(uni64((unsigned long long)(size_t)p));
+    uint32_t w[sizeof(ItemDesc) / 4];
+    static_assert(sizeof(ItemDesc) % 4 == 0, "whole words");
+#pragma unroll
+    for (uint32_t q = 0; q < sizeof(ItemDesc) / 4; ++q) w[q] = src[q];
+    __builtin_memcpy(&D, w, sizeof D);
+}
+
+// 16 bytes at a 32-bit byte offset from a uniform base.
+__device__ __forceinline__ float4 load_at(const float4* base, uint32_t offset) {
+    typedef const __attribute__((address_space(1))) unsigned char* gbytes;
+    const f32x4 v = *(const __attribute__((address_space(1))) f32x4*)((gbytes)(base) + offset);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+
+// x >= 0 to u32, rounded down, saturating (a C++ conversion leaves the result
+// past 2^32 undefined; the instruction saturates).
+__device__ __forceinline__ uint32_t to_u32_sat(float x) {
+    uint32_t r;
+    asm("v_cvt_u32_f32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
 
 // Inclusive sum over the wave's lanes (DPP row shifts, then row broadcasts).
 __device__ __forceinline__ uint32_t wave_sum_inclusive(uint32_t x) {
@@ -1133,8 +1162,9 @@ __device__ __forceinline__ void cull_test(OutState& O, const ItemDesc& D, const 
     wave_sync();
     // lanes past n repeat the last candidate; only the decision is masked
     const uint32_t c = L.queue[end - n + min(lane, n - 1u)];
-    const uint32_t i = c & ((1u << kCullSlotShift) - 1u), slot = c >> kCullSlotShift;
-    const float4 P = load_global4(reinterpret_cast<const float4*>(D.lights), min(i, D.n_lights - 1u));
+    const uint32_t ci = c & ((1u << kCullSlotShift) - 1u), slot = c >> kCullSlotShift;
+    const uint32_t i = c & ((1u << D.block_log) - 1u);
+    const float4 P = load_at(reinterpret_cast<const float4*>(D.lights), min(i, D.n_lights - 1u) << 4);
     const float4 e = L.eyes[slot];
     // |l - e| per axis, 0 where it is NaN: box_d2 of a one-point box
     const float dx = fmaxf(fabsf(P.x - e.x), 0.0f);
@@ -1142,19 +1172,25 @@ __device__ __forceinline__ void cull_test(OutState& O, const ItemDesc& D, const 
     const float dz = fmaxf(fabsf(P.z - e.z), 0.0f);
     const float x2 = dx * dx, y2 = dy * dy, z2 = dz * dz;
     const float d2 = (x2 + y2) + z2;
-    const uint32_t v = rotated(i, __float_as_uint(e.w));
-    bool keep;
-    const bool open = rr_fast(v, D, d2, true, keep);
-    if (ballot(open)) {   // rare: the IEEE decision
-        if (open) keep = keeps(v, accept_p(D.s, d2, 1.0f));
+    const uint32_t v = rotated(ci, __float_as_uint(e.w));   // e.w: the eye's R less the reversal of the tree bit
+    // the product-form test (see rr_test) as lane masks
+    const float prod = (float)v * d2;
+    const uint64_t near = ballot(d2 <= D.d2_fast);
+    const uint64_t sure = ballot(prod < D.t_keep) & near;
+    const uint64_t cull = ballot(prod > D.t_cull) & near;
+    const uint64_t valid = ballot(i < D.n_lights) & (~0ull >> (64u - n));
+    uint64_t m = sure & valid;
+    const uint64_t open = valid & ~(sure | cull);
+    if (open) {   // rare: the IEEE decision
+        bool keep = false;
+        if (__builtin_amdgcn_inverse_ballot_w64(open)) keep = keeps(v, accept_p(D.s, d2, 1.0f));
+        m |= ballot(keep);
     }
-    keep = keep && lane < n && i < D.n_lights;
-    const uint64_t m = ballot(keep);
     if (D.capacity == 0) {   // counting launch: nothing is stored
         O.count += (uint32_t)__popcll(m);
         return;
     }
-    if (keep) {
+    if (__builtin_amdgcn_inverse_ballot_w64(m)) {
         const uint32_t at = staged + count_below(m);
         L.pairs[at] = make_uint2(L.u[slot], i);
         if (W) L.d2[at] = d2;
@@ -1208,7 +1244,7 @@ void cull_kernel(TravArgs A) {
     const uint32_t lane = lane_id();
     CullLds L;
     {
-        unsigned char* base = smem + (threadIdx.x / kWave) * cull_wave_bytes(W, DENSE);
+        unsigned char* base = smem + uni(threadIdx.x / kWave) * cull_wave_bytes(W, DENSE);
         L.eyes = reinterpret_cast<float4*>(base);
         L.pairs = reinterpret_cast<uint2*>(base + kCullEyes * 16);
         L.stack = reinterpret_cast<uint32_t*>(L.pairs + (DENSE ? kCullStageDense : kCullStage));
@@ -1271,7 +1307,7 @@ void cull_kernel(TravArgs A) {
             if (cur != 0xFFFFFFFFu) cull_close<W, DENSE>(O, D, L, staged, A.error);
             if (it == 0xFFFFFFFFu) break;
             cur = it;
-            D = A.items[it];
+            load_item(D, A.items + it);
         }
         const uint32_t part = t - D.task_begin;
         const uint32_t u0 = part >> D.sub_log << D.task_shift;
@@ -1284,7 +1320,9 @@ void cull_kernel(TravArgs A) {
         if (lane < cnt) {
             const uint32_t u = D.order ? D.order[u0 + lane] : u0 + lane;
             const EyeState e = load_eye(D, A.tile, u);
-            L.eyes[lane] = make_float4(e.ex, e.ey, e.ez, __uint_as_float(e.R));
+            // block numbers and candidates carry the tree bit 2^S above their
+            // index; R less that bit's reversal takes it out of every rotation
+            L.eyes[lane] = make_float4(e.ex, e.ey, e.ez, __uint_as_float(e.R - (1u << (31u - S))));
             L.u[lane] = e.u;
         }
         const float4* const blocks = reinterpret_cast<const float4*>(uni64((unsigned long long)(size_t)D.blocks));
@@ -1299,14 +1337,13 @@ void cull_kernel(TravArgs A) {
             }
             if (sn == 0u) break;
             wave_sync();
-            const uint32_t room = kCullStack - kCullReserve;
-            const uint32_t g = min(min(16u, sn), sn < room ? max(1u, (room - sn) / 3u) : 1u);
+            const uint32_t g = sn > kCullWide ? 1u : min(16u, sn);
             sn -= g;
             const bool act = (lane & 15u) < g;
             const uint32_t ent = L.stack[sn + min(lane & 15u, g - 1u)];
             const uint32_t tag = ent & ~((1u << kCullSlotShift) - 1u);
-            const uint32_t id = (ent << (32u - kCullSlotShift) >> (32u - kCullSlotShift)) * 4u + (lane >> 4);
-            const float4 b0 = load_global4(blocks, 2u * id), b1 = load_global4(blocks, 2u * id + 1u);
+            const uint32_t id = (ent & ((1u << kCullSlotShift) - 1u)) * 4u + (lane >> 4);
+            const float4 b0 = load_at(blocks, id << 5), b1 = load_at(blocks, (id << 5) + 16u);
             const float4 e = L.eyes[ent >> kCullSlotShift];
 
             // squared distances to the nearest and the farthest point of the box
@@ -1316,24 +1353,20 @@ void cull_kernel(TravArgs A) {
                         nz = fmaxf(fmaxf(az, bz), 0.0f);
             const float nx2 = nx * nx, ny2 = ny * ny, nz2 = nz * nz;
             const float dn = fmaxf((nx2 + ny2) + nz2, s);
-            const float fx = fmaxf(fabsf(ax), fabsf(bx)), fy = fmaxf(fabsf(ay), fabsf(by)),
-                        fz = fmaxf(fabsf(az), fabsf(bz));
-            const float fx2 = fx * fx, fy2 = fy * fy, fz2 = fz * fz;
+            const float fx2 = fmaxf(ax * ax, bx * bx), fy2 = fmaxf(ay * ay, by * by), fz2 = fmaxf(az * az, bz * bz);
             const float df = fmaxf((fx2 + fy2) + fz2, s);
             // T, at least every light's threshold minus one: t_cull is s 2^32
             // (1 + 2^-18) or more, which covers the reciprocal's and the
             // products' rounding
-            const float x = D.t_cull * __builtin_amdgcn_rcpf(dn);
-            const uint32_t T = x >= 4294967040.0f ? 0xFFFFFFFFu : (uint32_t)x;
+            const uint32_t T = to_u32_sat(D.t_cull * __builtin_amdgcn_rcpf(dn));
 
-            const uint32_t lg = 31u - (uint32_t)__builtin_clz(id);   // 2 x the block's level
-            const uint32_t v = S - lg, rsh = 32u - v;                // 2^v indices
-            const uint32_t p = (id << v) ^ (1u << S);
+            const uint32_t v = (uint32_t)__builtin_clz(id) + (S - 31u), rsh = 32u - v;   // 2^v indices
+            const uint32_t p = id << v;                              // first index, and the tree bit
             const uint32_t u = bit_reverse(p) + __float_as_uint(e.w);
             const uint32_t m0 = u & ((1u << rsh) - 1u);              // the block's minimum
             uint32_t c = act && m0 <= T ? ((T - m0) >> rsh) + 1u : 0u;
-            // a block that holds no light has v = 0 candidates at most, which
-            // lie past N
+            // (a block that holds no light has v = 0 candidates at most, which
+            // lie past N)
             const bool split = c > 1u && v > leaf_log &&
                                (c > kCullMaxRun || !((float)c * (df - dn) < kCullWaste * df));
             const uint64_t ms = ballot(split);
@@ -1346,6 +1379,7 @@ void cull_kernel(TravArgs A) {
             // (a lane lists at most 16, so every round takes some).
             const uint32_t inc = wave_sum_inclusive(c);
             const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+            const uint32_t tagged = p | tag;
             // with no step to come, the queue is drained
             const uint32_t least = sn == 0u && next == cnt ? 1u : (uint32_t)kWave;
             uint32_t done = 0;
@@ -1354,10 +1388,9 @@ void cull_kernel(TravArgs A) {
                 const uint64_t wait = ballot(c != 0u && !fits);
                 const uint32_t upto =
                     wait ? (uint32_t)__builtin_amdgcn_readlane((int)(inc - c), (int)__builtin_ctzll(wait)) : total;
-                uint32_t* dst = L.queue + (qn + (inc - c) - done);
                 uint32_t k = 0u - (u >> rsh);
-                const uint32_t k_end = k + (fits ? c : 0u);
-                for (; k != k_end; ++k) *dst++ = p | (bit_reverse(k) >> rsh) | tag;
+                const uint32_t k_end = k + (fits ? c : 0u), to = qn + (inc - c) - done - k;
+                for (; k != k_end; ++k) L.queue[to + k] = tagged | (bit_reverse(k) >> rsh);
                 c = fits ? 0u : c;
                 qn += upto - done;
                 done = upto;
