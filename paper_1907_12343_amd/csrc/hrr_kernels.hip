@@ -1052,10 +1052,11 @@ constexpr uint32_t cull_wave_bytes(bool weights, bool dense) {
 // A block is split while the candidates that its bound lets through beyond
 // those that must be near enough, cnt * (1 - far bound / near bound), exceed
 // kCullWaste (cost of four more box tests against that of the candidates they
-// save; 4 is the flat minimum of the simulated instruction counts for 23 to
-// 2,300 pairs per eye), or while there are more than kCullMaxRun of them (a
-// lane lists its candidates one per turn).
-constexpr float kCullWaste = 4.0f;
+// save), or while there are more than kCullMaxRun of them (a lane lists its
+// candidates one per turn).  Measured, full frame / quarter frame / batch of 64
+// caches, ms: 4: 22.2 / 7.30 / 3.34, 6: 21.3 / 7.06 / 3.37, 8: 21.0 / 6.95 /
+// 3.44, 12: 21.05 / - / -; runs of 8, 16, 32 at the frame: 21.6, 21.1, 21.3.
+constexpr float kCullWaste = 6.0f;
 constexpr uint32_t kCullMaxRun = 16;
 
 struct CullLds {
@@ -1104,6 +1105,7 @@ __device__ __forceinline__ uint32_t wave_sum_inclusive(uint32_t x) {
     x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);   // row_shr:8
     x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // row_bcast:15
     x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // row_bcast:31
+    asm("" : "+v"(x));   // or `sum - c` takes the last additions apart, two instructions each
     return x;
 }
 
