@@ -1062,7 +1062,8 @@ constexpr uint32_t kCullMaxRun = 16;
 struct CullLds {
     uint32_t* stack;
     uint32_t* queue;
-    float4* eyes;      // x, y, z, R bits
+    float4* eyes;      // x, y, z, bits of R less the reversed tree and slot bits:
+                       // a reversed queue entry plus this is the rotated inverse
     uint32_t* u;       // virtual eye index
     uint2* pairs;      // accepted pairs waiting to be stored
     float* d2;         // their squared distances (weights are computed as pairs are stored)
@@ -1072,9 +1073,14 @@ struct CullLds {
 // launch writes it, so its fields come by scalar loads into scalar registers
 // (from the generic address the compiler loads them into vector registers and
 // reads them back lane by lane: two or three instructions per use and step).
+// The address is opaque to the compiler: each caller loads the fields it uses
+// where it uses them, and the walk's inner loops hold only their own (all of an
+// item's fields held across the loops spill scalar registers to vector lanes).
 __device__ __forceinline__ void load_item(ItemDesc& D, const ItemDesc* p) {
     typedef const __attribute__((address_space(4))) uint32_t* cptr;
-    const cptr src = (cptr)(uni64((unsigned long long)(size_t)p));
+    unsigned long long at = uni64((unsigned long long)(size_t)p);
+    asm volatile("" : "+s"(at));
+    const cptr src = (cptr)at;
     uint32_t w[sizeof(ItemDesc) / 4];
     static_assert(sizeof(ItemDesc) % 4 == 0, "whole words");
 #pragma unroll
@@ -1087,6 +1093,21 @@ __device__ __forceinline__ float4 load_at(const float4* base, uint32_t offset) {
     typedef const __attribute__((address_space(1))) unsigned char* gbytes;
     const f32x4 v = *(const __attribute__((address_space(1))) f32x4*)((gbytes)(base) + offset);
     return make_float4(v.x, v.y, v.z, v.w);
+}
+
+// The larger of two floats that are not negative, by their bits (the float
+// maximum costs one more instruction, which quiets a signalling b).
+__device__ __forceinline__ float max_bits(float a, float b) {
+    return __uint_as_float(max(__float_as_uint(a), __float_as_uint(b)));
+}
+
+// The smaller of two floats, without the instructions that quiet a signalling
+// NaN first (results of arithmetic are none; the compiler no longer knows where
+// they come from another basic block).
+__device__ __forceinline__ float min_plain(float a, float b) {
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
 }
 
 // x >= 0 to u32, rounded down, saturating (a C++ conversion leaves the result
@@ -1109,30 +1130,62 @@ __device__ __forceinline__ uint32_t wave_sum_inclusive(uint32_t x) {
     return x;
 }
 
+// Take a chunk: as alloc_chunk and set_chunk, with the two buffers' addresses in
+// scalar registers (a select between two fields of a descriptor goes through
+// scratch memory).
+template <bool W>
+__device__ __forceinline__ void cull_open(OutState& O, const ItemDesc* item) {
+    ItemDesc D;
+    load_item(D, item);
+    const unsigned long long pairs = uni64((unsigned long long)(size_t)D.pairs);
+    const unsigned long long slack_pairs = uni64((unsigned long long)(size_t)D.slack_pairs);
+    const unsigned long long weights = W ? uni64((unsigned long long)(size_t)D.weights) : 0ull;
+    const unsigned long long slack_weights = W ? uni64((unsigned long long)(size_t)D.slack_weights) : 0ull;
+    O.chunk = alloc_chunk(D);
+    O.fill = 0;
+    const unsigned long long p0 = O.chunk << D.chunk_shift, C = 1ull << D.chunk_shift;
+    const unsigned long long q0 = p0 - D.capacity;
+    unsigned long long wp = 0, ww = 0;
+    if (p0 + C <= D.capacity) {
+        wp = pairs + p0 * 8u;
+        ww = weights + p0 * 4u;
+    } else if (p0 >= D.capacity && q0 + C <= D.slack) {
+        wp = slack_pairs + q0 * 8u;
+        ww = slack_weights + q0 * 4u;
+    }
+    O.wp = reinterpret_cast<uint2*>(uni64(wp));
+    if (W) O.ww = reinterpret_cast<float*>(uni64(ww));
+}
+
 // Store the newest n (1 .. 64) staged pairs, [end - n, end): into the wave's
 // chunk, at O.fill, which is a multiple of 64 here.  Chunks hold a multiple of
 // 64, so a run never crosses one, and whole runs are whole cache lines.
 template <bool W>
-__device__ __forceinline__ void cull_store(OutState& O, const ItemDesc& D, const CullLds& L, uint32_t end, uint32_t n) {
+__device__ __forceinline__ void cull_store(OutState& O, const ItemDesc* item, uint32_t chunk_shift, float s,
+                                           const CullLds& L, uint32_t end, uint32_t n) {
     const uint32_t lane = lane_id();
     wave_sync();
     if (O.chunk == kNoChunk) {
-        set_chunk<W>(O, D, alloc_chunk(D));
-        O.fill = 0;
+        cull_open<W>(O, item);
     }
     if (lane < n) {
         const uint2 pr = L.pairs[end - n + lane];
-        const float w = W ? 1.0f / accept_p(D.s, L.d2[end - n + lane], 1.0f) : 0.0f;
+        const float w = W ? 1.0f / accept_p(s, L.d2[end - n + lane], 1.0f) : 0.0f;
         if (O.wp) {
             put_pair(O.wp, O.fill + lane, pr);
             if (W) put_weight(O.ww, O.fill + lane, w);
-        } else {
-            store_pair<W>(D, (O.chunk << D.chunk_shift) + O.fill + lane, pr, w);
+        } else {   // a chunk across the capacity or past the slack
+            ItemDesc D;
+            load_item(D, item);
+            store_pair<W>(D, (O.chunk << chunk_shift) + O.fill + lane, pr, w);
         }
     }
     O.fill += n;
     O.count += n;
-    if (O.fill >> D.chunk_shift) set_chunk<W>(O, D, kNoChunk);
+    if (O.fill >> chunk_shift) {
+        O.chunk = kNoChunk;
+        O.wp = nullptr;
+    }
 }
 
 // Dense output: the n staged pairs go to positions [base, base + n).
@@ -1158,26 +1211,25 @@ __device__ __forceinline__ unsigned long long take_positions(const ItemDesc& D, 
 // Exact tests of the n (1 .. 64) newest candidates of the queue, which ends at
 // entry `end`, one per lane; `staged` counts the pairs waiting in LDS.
 template <bool W, bool DENSE>
-__device__ __forceinline__ void cull_test(OutState& O, const ItemDesc& D, const CullLds& L, uint32_t end, uint32_t n,
-                                          uint32_t& staged) {
+__device__ __forceinline__ void cull_test(OutState& O, const ItemDesc& D, const ItemDesc* item, const CullLds& L,
+                                          uint32_t end, uint32_t n, uint32_t& staged) {
     const uint32_t lane = lane_id();
     wave_sync();
-    // lanes past n repeat the last candidate; only the decision is masked
-    const uint32_t c = L.queue[end - n + min(lane, n - 1u)];
-    const uint32_t ci = c & ((1u << kCullSlotShift) - 1u), slot = c >> kCullSlotShift;
+    // n < 64 only where the queue holds no more (end == n), so every lane reads
+    // inside it; what lanes past n read is any light and slot (the index is
+    // clamped, the slot has 6 bits), and only their decision is masked
+    const uint32_t r = L.queue[end - n + lane];
+    const uint32_t c = bit_reverse(r), slot = c >> kCullSlotShift;
     const uint32_t i = c & ((1u << D.block_log) - 1u);
     const float4 P = load_at(reinterpret_cast<const float4*>(D.lights), min(i, D.n_lights - 1u) << 4);
     const float4 e = L.eyes[slot];
-    // |l - e| per axis, 0 where it is NaN: box_d2 of a one-point box
-    const float dx = fmaxf(fabsf(P.x - e.x), 0.0f);
-    const float dy = fmaxf(fabsf(P.y - e.y), 0.0f);
-    const float dz = fmaxf(fabsf(P.z - e.z), 0.0f);
+    const float dx = P.x - e.x, dy = P.y - e.y, dz = P.z - e.z;
     const float x2 = dx * dx, y2 = dy * dy, z2 = dz * dz;
-    const float d2 = (x2 + y2) + z2;
-    const uint32_t v = rotated(ci, __float_as_uint(e.w));   // e.w: the eye's R less the reversal of the tree bit
+    float d2 = (x2 + y2) + z2;
+    const uint32_t v = r + __float_as_uint(e.w);   // the rotated inverse (see CullLds)
     // the product-form test (see rr_test) as lane masks
     const float prod = (float)v * d2;
-    const uint64_t near = ballot(d2 <= D.d2_fast);
+    const uint64_t near = ballot(d2 <= D.d2_fast);   // not where d2 is NaN
     const uint64_t sure = ballot(prod < D.t_keep) & near;
     const uint64_t cull = ballot(prod > D.t_cull) & near;
     const uint64_t valid = ballot(i < D.n_lights) & (~0ull >> (64u - n));
@@ -1185,7 +1237,13 @@ __device__ __forceinline__ void cull_test(OutState& O, const ItemDesc& D, const 
     const uint64_t open = valid & ~(sure | cull);
     if (open) {   // rare: the IEEE decision
         bool keep = false;
-        if (__builtin_amdgcn_inverse_ballot_w64(open)) keep = keeps(v, accept_p(D.s, d2, 1.0f));
+        if (__builtin_amdgcn_inverse_ballot_w64(open)) {
+            // |l - e| per axis, 0 where it is NaN: box_d2 of a one-point box
+            const float ax = fmaxf(fabsf(dx), 0.0f), ay = fmaxf(fabsf(dy), 0.0f), az = fmaxf(fabsf(dz), 0.0f);
+            const float ax2 = ax * ax, ay2 = ay * ay, az2 = az * az;
+            d2 = (ax2 + ay2) + az2;
+            keep = keeps(v, accept_p(D.s, d2, 1.0f));
+        }
         m |= ballot(keep);
     }
     if (D.capacity == 0) {   // counting launch: nothing is stored
@@ -1200,19 +1258,23 @@ __device__ __forceinline__ void cull_test(OutState& O, const ItemDesc& D, const 
     staged += (uint32_t)__popcll(m);
     if (DENSE) {
         if (staged > kCullStageDense - (uint32_t)kWave) {   // no room for another test's pairs
-            cull_store_at<W>(D, L, take_positions(D, staged), staged);
+            ItemDesc X;
+            load_item(X, item);
+            cull_store_at<W>(X, L, take_positions(X, staged), staged);
             staged = 0;
         }
     } else if (staged >= (uint32_t)kWave) {
-        cull_store<W>(O, D, L, staged, kWave);
+        cull_store<W>(O, item, D.chunk_shift, D.s, L, staged, kWave);
         staged -= kWave;
     }
 }
 
 // A wave leaves an item: its last staged pairs, then close_item.
 template <bool W, bool DENSE>
-__device__ __forceinline__ void cull_close(OutState& O, const ItemDesc& D, const CullLds& L, uint32_t& staged,
+__device__ __forceinline__ void cull_close(OutState& O, const ItemDesc* item, const CullLds& L, uint32_t& staged,
                                            uint32_t* err) {
+    ItemDesc D;
+    load_item(D, item);
     if (DENSE) {
         const unsigned long long n = D.capacity ? staged : O.count;
         if (n) {
@@ -1221,7 +1283,7 @@ __device__ __forceinline__ void cull_close(OutState& O, const ItemDesc& D, const
         }
         O.count = 0;
     } else {
-        if (staged) cull_store<W>(O, D, L, staged, staged);
+        if (staged) cull_store<W>(O, item, D.chunk_shift, D.s, L, staged, staged);
         close_item(O, D, err);
     }
     staged = 0;
@@ -1256,7 +1318,6 @@ void cull_kernel(TravArgs A) {
     }
     uint32_t staged = 0;
     uint32_t cur = 0xFFFFFFFFu;
-    ItemDesc D;
     OutState O;
     O.chunk = kNoChunk;
     O.wp = nullptr;
@@ -1306,11 +1367,12 @@ void cull_kernel(TravArgs A) {
         }
         if (it != cur || it == 0xFFFFFFFFu) {   // a wave may get no task at all
             if (DENSE && it == 0xFFFFFFFFu) break;   // the block's waves close together, below
-            if (cur != 0xFFFFFFFFu) cull_close<W, DENSE>(O, D, L, staged, A.error);
+            if (cur != 0xFFFFFFFFu) cull_close<W, DENSE>(O, A.items + cur, L, staged, A.error);
             if (it == 0xFFFFFFFFu) break;
             cur = it;
-            load_item(D, A.items + it);
         }
+        ItemDesc D;
+        load_item(D, A.items + it);
         const uint32_t part = t - D.task_begin;
         const uint32_t u0 = part >> D.sub_log << D.task_shift;
         const uint32_t root = (1u << D.sub_log) | (part & ((1u << D.sub_log) - 1u));
@@ -1323,8 +1385,10 @@ void cull_kernel(TravArgs A) {
             const uint32_t u = D.order ? D.order[u0 + lane] : u0 + lane;
             const EyeState e = load_eye(D, A.tile, u);
             // block numbers and candidates carry the tree bit 2^S above their
-            // index; R less that bit's reversal takes it out of every rotation
-            L.eyes[lane] = make_float4(e.ex, e.ey, e.ez, __uint_as_float(e.R - (1u << (31u - S))));
+            // index and the slot above that; R less the reversal of both takes
+            // them out of every rotation
+            L.eyes[lane] = make_float4(e.ex, e.ey, e.ez,
+                                       __uint_as_float(e.R - (1u << (31u - S)) - bit_reverse(lane << kCullSlotShift)));
             L.u[lane] = e.u;
         }
         const float4* const blocks = reinterpret_cast<const float4*>(uni64((unsigned long long)(size_t)D.blocks));
@@ -1344,9 +1408,11 @@ void cull_kernel(TravArgs A) {
             const bool act = (lane & 15u) < g;
             const uint32_t ent = L.stack[sn + min(lane & 15u, g - 1u)];
             const uint32_t tag = ent & ~((1u << kCullSlotShift) - 1u);
-            const uint32_t id = (ent & ((1u << kCullSlotShift) - 1u)) * 4u + (lane >> 4);
+            const uint32_t id = (ent << 2 | lane >> 4) & ((4u << kCullSlotShift) - 1u);
+            uint32_t slot = ent >> kCullSlotShift;
+            asm("" : "+v"(slot));   // or the shift to an address takes an `and`
             const float4 b0 = load_at(blocks, id << 5), b1 = load_at(blocks, (id << 5) + 16u);
-            const float4 e = L.eyes[ent >> kCullSlotShift];
+            const float4 e = L.eyes[slot];
 
             // squared distances to the nearest and the farthest point of the box
             const float ax = b0.x - e.x, ay = b0.y - e.y, az = b0.z - e.z;
@@ -1354,9 +1420,7 @@ void cull_kernel(TravArgs A) {
             const float nx = fmaxf(fmaxf(ax, bx), 0.0f), ny = fmaxf(fmaxf(ay, by), 0.0f),
                         nz = fmaxf(fmaxf(az, bz), 0.0f);
             const float nx2 = nx * nx, ny2 = ny * ny, nz2 = nz * nz;
-            const float dn = fmaxf((nx2 + ny2) + nz2, s);
-            const float fx2 = fmaxf(ax * ax, bx * bx), fy2 = fmaxf(ay * ay, by * by), fz2 = fmaxf(az * az, bz * bz);
-            const float df = fmaxf((fx2 + fy2) + fz2, s);
+            const float dn = max_bits((nx2 + ny2) + nz2, s);
             // T, at least every light's threshold minus one: t_cull is s 2^32
             // (1 + 2^-18) or more, which covers the reciprocal's and the
             // products' rounding
@@ -1364,41 +1428,55 @@ void cull_kernel(TravArgs A) {
 
             const uint32_t v = (uint32_t)__builtin_clz(id) + (S - 31u), rsh = 32u - v;   // 2^v indices
             const uint32_t p = id << v;                              // first index, and the tree bit
-            const uint32_t u = bit_reverse(p) + __float_as_uint(e.w);
-            const uint32_t m0 = u & ((1u << rsh) - 1u);              // the block's minimum
+            const uint32_t u = bit_reverse(p | tag) + __float_as_uint(e.w);
+            const uint32_t m0 = __builtin_amdgcn_ubfe(u, 0u, rsh);   // the block's minimum
             uint32_t c = act && m0 <= T ? ((T - m0) >> rsh) + 1u : 0u;
             // (a block that holds no light has v = 0 candidates at most, which
             // lie past N)
-            const bool split = c > 1u && v > leaf_log &&
-                               (c > kCullMaxRun || !((float)c * (df - dn) < kCullWaste * df));
-            const uint64_t ms = ballot(split);
-            if (split) L.stack[sn + count_below(ms)] = id | tag;
-            sn += (uint32_t)__popcll(ms);
-            c = split ? 0u : c;
+            const uint64_t wide = ballot(c > 1u) & ballot(v > leaf_log);
+            uint64_t ms = 0;
+            if (wide) {
+                // (to the far side, lo - e and e - hi are negative)
+                const float fx = min_plain(ax, bx), fy = min_plain(ay, by), fz = min_plain(az, bz);
+                const float df = max_bits((fx * fx + fy * fy) + fz * fz, s);
+                ms = wide & (ballot(c > kCullMaxRun) | ~ballot((float)c * (df - dn) < kCullWaste * df));
+                if (__builtin_amdgcn_inverse_ballot_w64(ms)) {
+                    L.stack[sn + count_below(ms)] = id | tag;
+                    c = 0;
+                }
+                sn += (uint32_t)__popcll(ms);
+            }
 
-            // List the candidates.  A lane's start in the queue is its prefix
-            // sum; lanes whose candidates do not fit wait for the next round
-            // (a lane lists at most 16, so every round takes some).
+            // List the candidates, as reversals: the first is m0 less e.w, and
+            // the rotated inverses of the others are 2^rsh apart.  A lane's
+            // start in the queue is its prefix sum.
             const uint32_t inc = wave_sum_inclusive(c);
             const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-            const uint32_t tagged = p | tag;
+            const uint32_t first = m0 - __float_as_uint(e.w);
             // with no step to come, the queue is drained
             const uint32_t least = sn == 0u && next == cnt ? 1u : (uint32_t)kWave;
             uint32_t done = 0;
             do {
-                const bool fits = inc - done <= kCullQueue - qn;
-                const uint64_t wait = ballot(c != 0u && !fits);
-                const uint32_t upto =
-                    wait ? (uint32_t)__builtin_amdgcn_readlane((int)(inc - c), (int)__builtin_ctzll(wait)) : total;
-                uint32_t k = 0u - (u >> rsh);
-                const uint32_t k_end = k + (fits ? c : 0u), to = qn + (inc - c) - done - k;
-                for (; k != k_end; ++k) L.queue[to + k] = tagged | (bit_reverse(k) >> rsh);
-                c = fits ? 0u : c;
+                uint32_t upto = total, take = c;
+                if (total - done > kCullQueue - qn) {
+                    // lanes whose candidates do not fit wait for the next round
+                    // (a lane lists at most 16, so every round takes some)
+                    const uint64_t wait = ballot(inc - done > kCullQueue - qn) & ballot(c != 0u);
+                    upto = (uint32_t)__builtin_amdgcn_readlane((int)(inc - c), (int)__builtin_ctzll(wait));
+                    if (__builtin_amdgcn_inverse_ballot_w64(wait)) take = 0;
+                }
+                uint32_t* at = L.queue + (qn + (inc - c) - done);
+                uint32_t* const at_end = at + take;
+                for (uint32_t r = first; at != at_end; ++at) {
+                    *at = r;
+                    r += 1u << rsh;
+                }
+                c -= take;
                 qn += upto - done;
                 done = upto;
                 while (qn >= least) {
                     const uint32_t n = min(qn, (uint32_t)kWave);
-                    cull_test<W, DENSE>(O, D, L, qn, n, staged);
+                    cull_test<W, DENSE>(O, D, A.items + cur, L, qn, n, staged);
                     qn -= n;
                 }
             } while (done < total);
@@ -1412,6 +1490,8 @@ void cull_kernel(TravArgs A) {
         __shared__ uint32_t held[kWavesPerBlock];
         __shared__ unsigned long long first;
         const uint32_t wv = threadIdx.x / kWave;
+        ItemDesc D;
+        load_item(D, A.items + (cur == 0xFFFFFFFFu ? 0u : cur));
         const unsigned long long mine = cur == 0xFFFFFFFFu ? 0ull : (D.capacity ? staged : O.count);
         if (lane == 0) {
             sums[wv] = mine;
@@ -1433,7 +1513,7 @@ void cull_kernel(TravArgs A) {
             __syncthreads();
             if (mine && D.capacity) cull_store_at<W>(D, L, uni64(first) + before, staged);
         } else if (mine) {
-            cull_close<W, true>(O, D, L, staged, A.error);
+            cull_close<W, true>(O, A.items + cur, L, staged, A.error);
         }
     }
 }
