@@ -368,7 +368,7 @@ hrr_status attach_frontier(hrr_hierarchy* h, hipStream_t stream) {
 
 hrr_status attach_blocks(hrr_hierarchy* h, hipStream_t stream) {
     if (!h->n_lights) return HRR_OK;
-    const size_t bytes = (size_t)block_tree_slots(block_tree_log(h->n_lights)) * kBlockFloats * sizeof(float);
+    const size_t bytes = block_tree_floats(h->n_lights) * sizeof(float);
     hipError_t e = hipMalloc((void**)&h->d_blocks, bytes);
     if (e == hipSuccess) e = hrr_launch_blocks(h->d_lights, h->n_lights, h->d_blocks, stream);
     if (e != hipSuccess) return hip_fail(e, "block tree");

@@ -118,7 +118,7 @@ HRR_EXPORT hrr_status hrr_build_hierarchy_device(hrr_ctx* ctx, const float* ligh
     if ((e = ctx->build_scratch.ensure(size.at)) != hipSuccess) return fail_free(hip_fail(e, "build scratch"));
     Carver carve{static_cast<unsigned char*>(ctx->build_scratch.p)};
     const Scratch T(carve, n, sort_bytes);
-    const size_t n_block_floats = n ? (size_t)block_tree_slots(block_log) * kBlockFloats : 0;
+    const size_t n_block_floats = n ? block_tree_floats(n) : 0;
     const size_t n_frontier_floats = max_internal ? (size_t)kFrontierMax * kFrontierFloats + 1 : 0;
     auto tables = [&](Carver& c) {
         h->d_lights = c.take<float>(std::max<size_t>(n, 1) * 4);

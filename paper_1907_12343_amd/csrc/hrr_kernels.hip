@@ -1012,11 +1012,10 @@ void traverse_kernel(TravArgs A) {
 // it lists the candidates, and each is tested exactly like a one-light leaf.
 // On the 1920x1080 x 2^20 frame an eye's 2,305 accepted pairs take 1,512 box
 // tests and 3,930 candidate tests (simulated), where the node walk tests
-// 25,500 children, each with a range minimum: 7,600 wave instructions an eye
-// against 33,900, 23.3 ms a frame against 106.6.  What bounds it: instruction
-// issue (0.26 vector instructions per SIMD-cycle and 0.55 scalar ones per
-// CU-cycle) behind the L1's line accesses (0.74 per CU-cycle), most of them
-// candidates' lights, one line per lane where neighbouring lanes' eyes do not
+// 25,500 children, each with a range minimum: 4,500 vector instructions an eye
+// a wave, 19.3 ms a frame against 106.6.  What bounds it: the L1's line accesses
+// (9.8e9 a frame, 0.9 per CU-cycle; one per cycle is its rate), four fifths of
+// them candidates' lights, one line per lane where neighbouring lanes do not
 // share it; hence the eye order by shift class, and 16 eyes of that order to
 // a step (below).
 //
@@ -1026,12 +1025,13 @@ void traverse_kernel(TravArgs A) {
 // of the j-th: 16 eyes that stand at the same block read one line, and their
 // children are pushed child by child, so the 16 go on together (frame 38.8 ->
 // 35.4 ms against four adjacent lanes to a parent).  `queue` holds candidates
-// (light | eye slot << 26): whenever it holds 64 they are tested, one per
-// lane.  Accepted pairs wait in LDS and leave 64 at a time, in whole cache
-// lines (35.4 -> 27.5 ms together with the listing by prefix sums: 38.0
-// instead of 41.5 GB written).  Eyes enter one root at a time as the stack
-// drains, so both kinds of
-// step run full lanes also where an eye has little work.  Lanes read their
+// (light | eye slot << 26, bit-reversed: a block's candidates are 2^(32-v)
+// apart in that form, and one add from their random numbers): whenever it holds
+// 64 they are tested, one per lane.  Accepted pairs wait in LDS and leave 64 at
+// a time, in whole cache lines (35.4 -> 27.5 ms together with the listing by
+// prefix sums: 38.0 instead of 41.5 GB written).  Eyes enter one root at a time
+// as the stack drains, so both kinds of step run full lanes also where an eye
+// has little work.  Lanes read their
 // eye (position, rotation) from LDS by slot.
 //
 // Stack bound: a step pops 16 parents and pushes at most 64 children while the
@@ -1221,7 +1221,13 @@ __device__ __forceinline__ void cull_test(OutState& O, const ItemDesc& D, const 
     const uint32_t r = L.queue[end - n + lane];
     const uint32_t c = bit_reverse(r), slot = c >> kCullSlotShift;
     const uint32_t i = c & ((1u << D.block_log) - 1u);
-    const float4 P = load_at(reinterpret_cast<const float4*>(D.lights), min(i, D.n_lights - 1u) << 4);
+    // the light's place: the low bits of its index reversed (see
+    // block_tree_lights; 1.07e10 -> 9.8e9 line accesses a frame, 19.5 -> 19.3 ms,
+    // batch of 64 caches 3.30 -> 3.14 ms)
+    const uint32_t leaf_log = block_leaf_log(D.block_log);
+    const uint32_t place = (i & (0u - (1u << leaf_log))) | r >> (32u - leaf_log);
+    const uint32_t last = (D.n_lights - 1u) | ((1u << leaf_log) - 1u);
+    const float4 P = load_at(reinterpret_cast<const float4*>(D.lights), min(place, last) << 4);
     const float4 e = L.eyes[slot];
     const float dx = P.x - e.x, dy = P.y - e.y, dz = P.z - e.z;
     const float x2 = dx * dx, y2 = dy * dy, z2 = dz * dz;
@@ -1520,7 +1526,9 @@ void cull_kernel(TravArgs A) {
 
 // ---- building the block tree ----
 //
-// block_leaf_kernel: one thread per smallest block, and in the same launch the
+// block_leaf_kernel: one thread per smallest block (which also writes its lights
+// in their second order; with neighbouring threads on neighbouring lights
+// instead, 2^20 lights build in the same 0.79 ms), and in the same launch the
 // four levels above it inside each thread block (256 blocks -> 64 -> 16 -> 4
 // -> 1); block_up_kernel: the next four levels from a finished one.
 struct BlockBox {
@@ -1565,14 +1573,21 @@ __device__ __forceinline__ void block_levels(float4* blocks, uint32_t level, Blo
 }
 
 __global__ __launch_bounds__(256) void block_leaf_kernel(const float4* __restrict__ lights, uint32_t n_lights,
-                                                         uint32_t block_log, float4* __restrict__ blocks) {
+                                                         uint32_t block_log, float4* __restrict__ blocks,
+                                                         float4* __restrict__ reversed) {
     const uint32_t leaf_log = block_leaf_log(block_log), level = (block_log - leaf_log) / 2u;
     const uint32_t i = blockIdx.x * 256u + threadIdx.x;
     BlockBox b = empty_block();
     if (i < (1u << (2u * level))) {
         const uint64_t first = (uint64_t)i << leaf_log;
-        for (uint32_t q = 0; q < (1u << leaf_log) && first + q < n_lights; ++q) {
+        for (uint32_t q = 0; q < (1u << leaf_log) && first < n_lights; ++q) {
+            float4* const copy = reversed + first + (bit_reverse(q) >> (32u - leaf_log));
+            if (first + q >= n_lights) {   // the last smallest block is filled up
+                *copy = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                continue;
+            }
             const float4 p = lights[first + q];
+            *copy = p;
             b.lo[0] = min_first(b.lo[0], p.x); b.hi[0] = max_first(b.hi[0], p.x);
             b.lo[1] = min_first(b.lo[1], p.y); b.hi[1] = max_first(b.hi[1], p.y);
             b.lo[2] = min_first(b.lo[2], p.z); b.hi[2] = max_first(b.hi[2], p.z);
@@ -2085,7 +2100,8 @@ extern "C" hipError_t hrr_launch_blocks(const float* lights, uint32_t n_lights, 
     uint32_t level = (log - hrr::block_leaf_log(log)) / 2u;
     float4* out = reinterpret_cast<float4*>(blocks);
     hipLaunchKernelGGL(hrr::block_leaf_kernel, dim3(((1u << (2u * level)) + 255u) / 256u), dim3(256), 0, stream,
-                       reinterpret_cast<const float4*>(lights), n_lights, log, out);
+                       reinterpret_cast<const float4*>(lights), n_lights, log, out,
+                       reinterpret_cast<float4*>(blocks + hrr::block_lights_at(n_lights)));
     for (; level > 4u; level -= 4u)
         hipLaunchKernelGGL(hrr::block_up_kernel, dim3(((1u << (2u * (level - 4u))) + 255u) / 256u), dim3(256), 0, stream,
                            level - 4u, out);

@@ -260,7 +260,7 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
         D.nodes = h->d_nodes;
         D.frontier = h->d_frontier;
         D.n_frontier = h->n_frontier;
-        D.lights = h->d_lights;
+        D.lights = shape.blocks && h->d_blocks ? h->d_blocks + block_lights_at(h->n_lights) : h->d_lights;
         D.blocks = h->d_blocks;
         D.block_log = block_tree_log(h->n_lights);
         D.task_shift = task_shift[k];
@@ -471,7 +471,7 @@ hrr_status launch_noalloc(hrr_ctx* ctx, const hrr_hierarchy* h, const hrr_eyes& 
     D.nodes = h->d_nodes;
     D.frontier = h->d_frontier;
     D.n_frontier = h->n_frontier;
-    D.lights = h->d_lights;
+    D.lights = block_walk && h->d_blocks ? h->d_blocks + block_lights_at(h->n_lights) : h->d_lights;
     D.blocks = h->d_blocks;
     D.block_log = block_tree_log(h->n_lights);
     D.task_shift = task_shift;

@@ -89,7 +89,8 @@ constexpr uint32_t kFrontierFloats = 12;
 // xyz and hi xyz (lo = +inf, hi = -inf where it holds no light).  It depends
 // on the lights' order alone: the hierarchies of both split rules and all
 // leaf sizes share its layout.  2^20 lights: leaves of 16 lights, 2.8 MB of
-// boxes, which fit one XCD's L2 beside the lights that its eyes touch.
+// boxes, which fit one XCD's L2 beside the lights that its eyes touch, and
+// 16.8 MB of lights in their second order (below).
 constexpr uint32_t kBlockFloats = 8;
 constexpr uint32_t block_tree_log(uint32_t n_lights) {
     uint32_t s = 5;   // at least one level below the root
@@ -100,6 +101,20 @@ constexpr uint32_t block_tree_log(uint32_t n_lights) {
 constexpr uint32_t block_leaf_log(uint32_t block_log) { return 4u - (block_log & 1u); }
 // Slots of a tree's box array (block numbers 0 .. 2 * 4^levels - 1).
 constexpr uint64_t block_tree_slots(uint32_t block_log) { return 2ull << (block_log - block_leaf_log(block_log)); }
+// Behind the boxes stand the lights once more (float4, whole smallest blocks,
+// zeros past the last light), each smallest block's in the bit-reversed order
+// of their offsets: the candidates that a walk lists from such a block are
+// neighbours in that order, and lanes that test them share cache lines.
+constexpr uint32_t block_tree_lights(uint32_t n_lights) {
+    const uint32_t small = 1u << block_leaf_log(block_tree_log(n_lights));
+    return (n_lights + small - 1u) & ~(small - 1u);
+}
+constexpr size_t block_lights_at(uint32_t n_lights) {   // in floats
+    return (size_t)block_tree_slots(block_tree_log(n_lights)) * kBlockFloats;
+}
+constexpr size_t block_tree_floats(uint32_t n_lights) {
+    return block_lights_at(n_lights) + (size_t)block_tree_lights(n_lights) * 4u;
+}
 
 // Eye-ordering description of one item: eyes are bucketed by the Morton
 // cell of their position inside the item's light box (cell = (x - lo) * scale,
