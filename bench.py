@@ -8,8 +8,8 @@ as ONE JSON line whose headline is the frame:
   64-Gaussian mixture (sigma 0.02) in the unit cube, fp32 positions, 64x64
   dither tile, s = 1e-4, Morton hierarchy with leaf size 1 (built once, before
   timing), one persistent launch per step: per-eye shift, rotated radical
-  inverse, range minimum per node (the paper's method), node bound,
-  cull/descend, exact leaf test and pair emission.  Inputs and the output
+  inverse, range minimum and bound per block, cull/descend or list, exact test
+  of every listed light and pair emission.  Inputs and the output
   buffer are resident in HBM before timing starts.  The headline uses the
   hierarchy with power-of-two splits; ``frame_other_split`` is the same frame
   on the radix (highest differing Morton bit) hierarchy;
@@ -20,10 +20,12 @@ as ONE JSON line whose headline is the frame:
 
 ``--workload frame|tiny|rangemin|batched|served`` runs one of them alone.
 
-Rooflines price the work with fixed per-unit figures (lane-operations or
-bytes per unit of work, see OPS_* below) times the units the kernel's
-statistics launch counts, divided by the kernel's own duration (HIP events
-around that kernel on the call's stream).
+Rooflines divide by the kernel's own duration (HIP events around that kernel
+on the call's stream).  The default traversal is priced by the bytes that it
+cannot do without: every accepted pair written once, every eye and light read
+once.  The range-minimum methods other than the default (``--rmq``) walk
+hierarchy records, and are priced in lane-operations: fixed figures per unit of
+work (OPS_* below) times the units that a launch with statistics counts.
 """
 import argparse
 import json
@@ -88,6 +90,18 @@ def alu_roofline(ops, kernel_ms, traffic=None):
     achieved = ops / (kernel_ms * 1e-3) / 1e12
     return {"bound": "alu", "achieved": achieved, "peak": VALU_PEAK_TOPS, "unit": "Tlane-op/s",
             "frac": achieved / VALU_PEAK_TOPS, "traffic": traffic}
+
+
+def pair_bytes(n_pairs, n_eyes, n_lights, weights=False):
+    """Bytes a traversal cannot do without: pairs (and weights) written once,
+    eyes (3 floats) and lights (4 floats as stored) read once."""
+    return n_pairs * (12 if weights else 8) + n_eyes * 12 + n_lights * 16
+
+
+def hbm_roofline(nbytes, kernel_ms, traffic=None):
+    achieved = nbytes / (kernel_ms * 1e-3) / 1e9
+    return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": achieved / HBM_PEAK_GBS, "traffic": traffic}
 
 
 def host_cpu():
@@ -170,8 +184,11 @@ def frame_workload(args, split=None, cpu=True, steps=None, warmup=None):
     pairs = torch.empty((max(n, 1), 2), dtype=torch.int32, device="cuda:0")
     weights = torch.empty((max(n, 1),), dtype=torch.float32, device="cuda:0") if args.weights else None
     kw["weights"] = weights
-    # one untimed launch with counters on: units of work for the roofline
-    st = ctx.traverse(h, eyes, fr["s"], fr["width"], pairs=pairs, stats=True, **kw)[2]
+    # the methods that walk hierarchy records: one untimed launch with counters
+    # on gives the units of work for the roofline
+    st = None
+    if method != 0:
+        st = ctx.traverse(h, eyes, fr["s"], fr["width"], pairs=pairs, stats=True, **kw)[2]
     kernel_ms = []
 
     def step():
@@ -183,7 +200,7 @@ def frame_workload(args, split=None, cpu=True, steps=None, warmup=None):
 
     ms, step_gpu_ms = timed_launches(step, steps, warmup)
     gpu_ms = sum(kernel_ms[warmup:]) / max(len(kernel_ms) - warmup, 1)
-    ops = lane_ops(st, n)
+    nbytes = pair_bytes(n, fr["eyes"].shape[0], int(fr["lights"].shape[0]), args.weights)
     traffic = (_traffic_bytes(args, split=split)
                if (ns == 1 and not args.weights and not tiny and method == 0) else None)
     line = {
@@ -208,18 +225,22 @@ def frame_workload(args, split=None, cpu=True, steps=None, warmup=None):
         "step_gpu_ms": step_gpu_ms,
         "hierarchy_build_s": build_s,
         "hierarchy_build_device_s": build_dev_s,
-        "units": {"node_visits": st["node_visits"], "child_bounds": 2 * st["node_visits"],
-                  "rmq_calls": st["rmq_calls"], "leaf_tests": st["leaf_tests"], "pairs": n,
-                  "stack_spills": st["spills"], "max_stack": st["max_stack"]},
-        "algorithmic_lane_ops": ops,
-        "roofline": alu_roofline(ops, gpu_ms, traffic),
+        "units": {"pairs": n, "bytes": nbytes},
+        "roofline": hbm_roofline(nbytes, gpu_ms, traffic),
     }
+    if st is not None:
+        ops = lane_ops(st, n)
+        line["units"] = {"node_visits": st["node_visits"], "child_bounds": 2 * st["node_visits"],
+                         "rmq_calls": st["rmq_calls"], "leaf_tests": st["leaf_tests"], "pairs": n,
+                         "stack_spills": st["spills"], "max_stack": st["max_stack"]}
+        line["algorithmic_lane_ops"] = ops
+        line["roofline"] = alu_roofline(ops, gpu_ms, traffic)
     if ns > 1:
         line["config"]["samples_per_eye"] = ns
         line["config"]["psi_s0"] = PSI_S0
     if traffic is not None:
         # everything that leaves the L2s (Infinity Cache hits included),
-        # beside the ALU roofline (from the recorded counter runs)
+        # beside the roofline (from the recorded counter runs)
         line["memory_side"] = {"bytes": traffic, "TB_per_s": traffic / (gpu_ms * 1e-3) / 1e12,
                                "frac_of_hbm_peak": traffic / (gpu_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                                "source": "profiles/traverse_frame_traffic.json"}
@@ -371,14 +392,12 @@ def rangemin_workload(args, steps=None, warmup=None):
 
 def batched_workload(args, steps=None, warmup=None):
     """256 independent caches (own mixture, 2^U[10,20] lights, 2^U[10,16]
-    eyes, s = 1e-4) in ONE call -- one persistent launch per eyes-per-wave
-    group of the items -- against 256 plain launches of the same items on the
+    eyes, s = 1e-4) in ONE call (one persistent launch) against 256 plain launches of the same items on the
     same GPU.  Before timing, the batched autotuner runs once per light
     class (log2 of the light count) on all caches of the class together, over
     leaf sizes 1, 2, 4, 8 and the launch shapes; every cache is built with
-    its class's leaf size, and the call groups the items by their classes'
-    eyes per wave.  Every group's own ALU fraction is measured with a call of
-    that group alone."""
+    its class's leaf size.  The items of every tuned launch shape are also
+    measured with a call of their own."""
     import numpy as np
     import torch
     import paper_1907_12343_amd as hrr
@@ -414,7 +433,7 @@ def batched_workload(args, steps=None, warmup=None):
                   out_capacity=int(counts[k]))
              for k, (h, e, d) in enumerate(zip(hs, eyes, caches))]
     n_eyes = int(sum(d["eyes"].shape[0] for d in caches))
-    got, st = ctx.traverse_batched(items, pairs, stats=True)
+    got, _ = ctx.traverse_batched(items, pairs)
     assert [int(x) for x in got] == counts
 
     kms = []
@@ -432,9 +451,9 @@ def batched_workload(args, steps=None, warmup=None):
                          capacity=counts[k])
 
     ms_plain, _ = timed_launches(plain, max(1, steps // 4), 1)
-    ops = lane_ops(st, total)
+    nbytes = pair_bytes(total, n_eyes, int(sizes.sum()))
 
-    # the groups alone (the call's grouping: the eyes per wave tuned for the class)
+    # the groups alone (items whose classes were tuned to the same eyes per wave)
     groups = {}
     for k in range(len(caches)):
         e = tuned[int(lclass[k])]["eyes_per_wave"]
@@ -442,7 +461,6 @@ def batched_workload(args, steps=None, warmup=None):
     per_group = {}
     for g, ks in groups.items():
         sub = [items[k] for k in ks]
-        _, sst = ctx.traverse_batched(sub, pairs, stats=True)
         gk = []
 
         def run_sub():
@@ -452,18 +470,19 @@ def batched_workload(args, steps=None, warmup=None):
         timed_launches(run_sub, steps, warmup)
         g_ms = sum(gk[warmup:]) / max(len(gk) - warmup, 1)
         g_pairs = int(sum(counts[k] for k in ks))
-        per_group[g] = {"items": len(ks), "eyes": int(sum(caches[k]["eyes"].shape[0] for k in ks)),
+        g_eyes = int(sum(caches[k]["eyes"].shape[0] for k in ks))
+        g_bytes = pair_bytes(g_pairs, g_eyes, int(sizes[ks].sum()))
+        per_group[g] = {"items": len(ks), "eyes": g_eyes,
                         "light_classes": sorted({int(lclass[k]) for k in ks}),
                         "pairs": g_pairs, "kernel_ms": g_ms,
-                        "alu_frac": alu_roofline(lane_ops(sst, g_pairs), g_ms)["frac"]}
+                        "hbm_frac": hbm_roofline(g_bytes, g_ms)["frac"]}
     line = {
         "metric": "eye-vertex traversals/s", "value": n_eyes / (ms * 1e-3), "unit": "eyes/s",
         "n_gpus": 1, "steps": steps, "warmup": warmup, "ms_per_step": ms,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "u32+f32",
         "data": "synthetic",
         "config": {"workload": "batched: 256 caches, own 64-Gaussian mixture each, 2^U[10,20] "
-                               "lights, 2^U[10,16] eyes, s=1e-4, one call (a launch per "
-                               "eyes-per-wave group)",
+                               "lights, 2^U[10,16] eyes, s=1e-4, one call",
                    "n_eyes": n_eyes, "n_lights": int(sizes.sum()), "split": args.split,
                    "tuned_per_light_class": {"2^%d" % c: v for c, v in sorted(tuned.items())},
                    "parallelism": "1 GPU"},
@@ -471,10 +490,8 @@ def batched_workload(args, steps=None, warmup=None):
         "step_gpu_ms": step_gpu_ms, "setup_s": setup_s,
         "plain_launches": {"ms_per_step": ms_plain, "eyes_per_s": n_eyes / (ms_plain * 1e-3),
                            "speedup_of_batched": ms_plain / ms},
-        "units": {"node_visits": st["node_visits"], "child_bounds": 2 * st["node_visits"],
-                  "rmq_calls": st["rmq_calls"], "leaf_tests": st["leaf_tests"], "pairs": total},
-        "algorithmic_lane_ops": ops,
-        "roofline": alu_roofline(ops, gpu_ms),
+        "units": {"pairs": total, "bytes": nbytes},
+        "roofline": hbm_roofline(nbytes, gpu_ms),
         "groups": per_group,
     }
     del pairs, eyes
