@@ -226,7 +226,7 @@ __device__ __forceinline__ void range_box(const float4* __restrict__ lights, con
 
 // Bound by the scattered 64-byte stores and the lights' loads: 83 us for 2^20
 // lights (67 MB of records); the nodes and ranks before it 43 and 48 us, the
-// sort 230 us.  A build of 2^20 lights takes 0.54 ms against 3.9 ms with one
+// sort 210 us.  A build of 2^20 lights takes 0.49 ms against 3.9 ms with one
 // launch and one host wait per tree level.
 __global__ __launch_bounds__(256) void records_kernel(const uint2* __restrict__ range, const uint32_t* __restrict__ parent,
                                                       const uint32_t* __restrict__ first,
@@ -304,11 +304,39 @@ __global__ __launch_bounds__(kSortThreads) void sort_count_kernel(const uint64_t
     counts[FUSED ? (size_t)blockIdx.x * kSortDigits + t : (size_t)t * n_tiles + blockIdx.x] = sum;
 }
 
+// One block per digit: its counts (digit-major, n_tiles of them) become their
+// exclusive prefix sums in tile order, totals[d] their sum.
+constexpr uint32_t kRowCounts = 8;   // a thread's counts per step
+__global__ __launch_bounds__(kSortThreads) void sort_rows_kernel(uint32_t* __restrict__ counts, uint32_t n_tiles,
+                                                                 uint32_t* __restrict__ totals) {
+    __shared__ uint32_t lds[4];
+    uint32_t* const row = counts + (size_t)blockIdx.x * n_tiles;
+    uint32_t carry = 0;
+    for (uint32_t b = threadIdx.x * kRowCounts; b - threadIdx.x * kRowCounts < n_tiles; b += kSortThreads * kRowCounts) {
+        uint32_t x[kRowCounts], sum = 0, total;
+#pragma unroll
+        for (uint32_t q = 0; q < kRowCounts; ++q) {
+            x[q] = b + q < n_tiles ? row[b + q] : 0u;
+            sum += x[q];
+        }
+        uint32_t run = carry + scan::block_inclusive_256(sum, lds, &total) - sum;
+#pragma unroll
+        for (uint32_t q = 0; q < kRowCounts; ++q) {
+            if (b + q < n_tiles) row[b + q] = run;
+            run += x[q];
+        }
+        carry += total;
+    }
+    if (threadIdx.x == 0) totals[blockIdx.x] = carry;
+}
+
+// first, totals: the tiles' counts with FUSED, else what sort_rows_kernel wrote.
 template <uint32_t ROUNDS, bool FUSED>
 __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(const uint64_t* __restrict__ kin,
                                                                     const uint32_t* __restrict__ vin, uint32_t n,
                                                                     uint32_t shift, uint32_t n_tiles,
                                                                     const uint32_t* __restrict__ first,
+                                                                    const uint32_t* __restrict__ totals,
                                                                     uint64_t* __restrict__ kout,
                                                                     uint32_t* __restrict__ vout) {
     // pos[w][d]: keys of digit d in wave w's run, then their first position
@@ -339,7 +367,10 @@ __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(const uint64
         }
         start = scan::block_inclusive_256(all, lds, &total) - all + before;
     } else {
-        start = first[(size_t)t * n_tiles + blockIdx.x];
+        __shared__ uint32_t lds[4];
+        uint32_t total;
+        const uint32_t all = totals[t], before = first[(size_t)t * n_tiles + blockIdx.x];
+        start = scan::block_inclusive_256(all, lds, &total) - all + before;
     }
 #pragma unroll
     for (uint32_t r = 0; r < ROUNDS; ++r) {
@@ -409,31 +440,35 @@ size_t align256(size_t b) { return (b + 255u) & ~(size_t)255u; }
 uint32_t sort_rounds(uint32_t n) { return n >= (1u << 18) ? 8u : n >= (1u << 16) ? 4u : 2u; }
 
 // FUSED: up to kSortFused tiles every scatter block adds up the tile counts it
-// needs itself (tile-major counts, 1 KB per tile out of L2) instead of three
-// scan launches between the two (12 us of a pass of 20 at 20,011 keys); beyond,
-// that reading grows with the square of the tiles (2^20 keys in 512 tiles: 613
-// us a build against 543 with the scan).
-constexpr uint32_t kSortFused = 128;
+// needs itself (tile-major counts, 1 KB per tile out of L2) instead of launches
+// between the two that scan them (three: 12 us of a pass of 20 at 20,011 keys);
+// beyond, that reading grows with the square of the tiles.  There one launch
+// scans each digit's counts, and the scatter blocks scan the 256 totals (2^20
+// keys: 490 us a build against 560 with a three-launch scan of all counts).
+// us a build, fused / with the scan: 40 tiles 186 / 195, 64 225 / 222, 128 (2^17
+// keys) 252 / 236, 128 (2^18) 308 / 291.
+constexpr uint32_t kSortFused = 48;
 
 template <uint32_t ROUNDS>
 hipError_t sort_pass(const uint64_t* ks, const uint32_t* vs, uint32_t n, uint32_t shift, uint32_t n_tiles,
-                     uint32_t* counts, uint32_t* sums, uint64_t* kd, uint32_t* vd, hipStream_t stream) {
+                     uint32_t* counts, uint32_t* totals, uint64_t* kd, uint32_t* vd, hipStream_t stream) {
     if (n_tiles <= kSortFused) {
         sort_count_kernel<ROUNDS, true><<<n_tiles, kSortThreads, 0, stream>>>(ks, n, shift, n_tiles, counts);
-        sort_scatter_kernel<ROUNDS, true><<<n_tiles, kSortThreads, 0, stream>>>(ks, vs, n, shift, n_tiles, counts, kd, vd);
+        sort_scatter_kernel<ROUNDS, true><<<n_tiles, kSortThreads, 0, stream>>>(ks, vs, n, shift, n_tiles, counts, totals,
+                                                                               kd, vd);
         return hipGetLastError();
     }
     sort_count_kernel<ROUNDS, false><<<n_tiles, kSortThreads, 0, stream>>>(ks, n, shift, n_tiles, counts);
-    hipError_t e = scan::exclusive_sum(counts, counts, n_tiles * kSortDigits, sums, stream);
-    if (e != hipSuccess) return e;
-    sort_scatter_kernel<ROUNDS, false><<<n_tiles, kSortThreads, 0, stream>>>(ks, vs, n, shift, n_tiles, counts, kd, vd);
+    sort_rows_kernel<<<kSortDigits, kSortThreads, 0, stream>>>(counts, n_tiles, totals);
+    sort_scatter_kernel<ROUNDS, false><<<n_tiles, kSortThreads, 0, stream>>>(ks, vs, n, shift, n_tiles, counts, totals,
+                                                                            kd, vd);
     return hipGetLastError();
 }
 
 // Stable radix sort of (code, index) by code (63 low bits); temp == nullptr
 // queries temp_bytes.  Scratch: a second key and index buffer (the passes
 // alternate between it and the outputs, the last pass landing in the
-// outputs), the per-tile digit counts and the scan's chunk sums.
+// outputs), the per-tile digit counts and the digits' totals.
 extern "C" hipError_t hrr_dev_sort(void* temp, size_t* temp_bytes, const uint64_t* code_in, uint64_t* code_out,
                                    const uint32_t* idx_in, uint32_t* idx_out, uint32_t n, hipStream_t stream) {
     static_assert(kSortPasses % 2 == 0, "the last pass must write the outputs");
@@ -442,8 +477,8 @@ extern "C" hipError_t hrr_dev_sort(void* temp, size_t* temp_bytes, const uint64_
     const uint32_t n_tiles = (n + tile - 1u) / tile;
     const uint32_t n_counts = n_tiles * kSortDigits;
     const size_t b_keys = align256((size_t)n * 8u), b_idx = align256((size_t)n * 4u);
-    const size_t b_counts = align256((size_t)n_counts * 4u), b_sums = align256((size_t)scan::chunk_count(n_counts) * 4u);
-    const size_t need = std::max<size_t>(b_keys + b_idx + b_counts + b_sums, 256u);
+    const size_t b_counts = align256((size_t)n_counts * 4u), b_totals = kSortDigits * 4u;
+    const size_t need = std::max<size_t>(b_keys + b_idx + b_counts + b_totals, 256u);
     if (!temp) {
         *temp_bytes = need;
         return hipSuccess;
@@ -454,16 +489,16 @@ extern "C" hipError_t hrr_dev_sort(void* temp, size_t* temp_bytes, const uint64_
     uint64_t* k_tmp = reinterpret_cast<uint64_t*>(tp);
     uint32_t* v_tmp = reinterpret_cast<uint32_t*>(tp + b_keys);
     uint32_t* counts = reinterpret_cast<uint32_t*>(tp + b_keys + b_idx);
-    uint32_t* sums = reinterpret_cast<uint32_t*>(tp + b_keys + b_idx + b_counts);
+    uint32_t* totals = reinterpret_cast<uint32_t*>(tp + b_keys + b_idx + b_counts);
     const uint64_t* ks = code_in;
     const uint32_t* vs = idx_in;
     for (uint32_t pass = 0; pass < kSortPasses; ++pass) {
         uint64_t* kd = (pass & 1u) ? code_out : k_tmp;
         uint32_t* vd = (pass & 1u) ? idx_out : v_tmp;
         const uint32_t shift = 8u * pass;
-        const hipError_t e = rounds == 4u ? sort_pass<4>(ks, vs, n, shift, n_tiles, counts, sums, kd, vd, stream)
-                             : rounds == 8u ? sort_pass<8>(ks, vs, n, shift, n_tiles, counts, sums, kd, vd, stream)
-                                          : sort_pass<2>(ks, vs, n, shift, n_tiles, counts, sums, kd, vd, stream);
+        const hipError_t e = rounds == 4u ? sort_pass<4>(ks, vs, n, shift, n_tiles, counts, totals, kd, vd, stream)
+                             : rounds == 8u ? sort_pass<8>(ks, vs, n, shift, n_tiles, counts, totals, kd, vd, stream)
+                                          : sort_pass<2>(ks, vs, n, shift, n_tiles, counts, totals, kd, vd, stream);
         if (e != hipSuccess) return e;
         ks = kd;
         vs = vd;

@@ -1,6 +1,6 @@
 // hrr_scan.hpp -- exclusive prefix sum of u32 counts on a gfx950 device, used
-// by the eye ordering (bucket offsets) and by the device hierarchy build
-// (radix-sort digit offsets, child slots of a level).
+// by the eye ordering (bucket offsets) and by the device hierarchy build (record
+// numbers).
 //
 // Three stream-ordered launches: every block sums one chunk of kScanChunk
 // counts, one block scans the chunk sums (1024 per step, any number of

@@ -19,8 +19,10 @@ def ctx():
 
 
 # 2 rounds of 256 keys a tile below 2^16 lights, 4 below 2^18, then 8; fused
-# offsets up to 128 tiles (2^17 lights in tiles of 1024, 2^18 in tiles of 2048)
-@pytest.mark.parametrize("n", [511, 512, 513, 65535, 65536, 131072, 131073, 262143, 262144, 262145])
+# offsets up to 48 tiles (24,576 lights in tiles of 512), beyond them each
+# digit's tile counts are scanned 2048 at a time (2^22 lights in tiles of 2048)
+@pytest.mark.parametrize("n", [511, 512, 513, 24576, 24577, 65535, 65536, 131072, 131073, 262143, 262144, 262145,
+                               (1 << 22) + 1])
 def test_sort_tiles(ctx, n):
     import torch
     lights = synth.mixture_points(n, synth.mixture_centers(n), n + 1)
