@@ -289,9 +289,11 @@ hrr_status hrr_traverse(hrr_ctx* ctx, const hrr_hierarchy* h, const hrr_eyes* ey
  *     result_dev[0] > capacity).
  *   opts: as hrr_traverse; HRR_F_STATS and HRR_F_TIMING are rejected
  *     (HRR_E_INVALID), and eyes are processed in index order.
- * The grid is cut to as many whole blocks as the scratch holds: with the
- * stack spill area sized for the hierarchy's depth, about 23 KB per wave at
- * depth 20; a hierarchy too deep for one block returns HRR_E_INVALID.
+ * The grid is cut to as many whole blocks as the scratch holds.  The default
+ * method needs little of it; methods that walk records (and s outside [2^-60,
+ * 2^60]) need the stack spill area sized for the hierarchy's depth, about
+ * 23 KB per wave at depth 20, and a hierarchy too deep for one block returns
+ * HRR_E_INVALID.
  * Output chunks hold at most 1024 pairs.  All calls on one GPU share its
  * scratch: calls that overlap in time on one GPU (several streams, several
  * threads) race and must be serialised by the caller. */
