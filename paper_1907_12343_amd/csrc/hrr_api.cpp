@@ -201,15 +201,49 @@ void group_by_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, const std::vect
         }
         resolve_shape(ctx, opts, max_lights, max_eyes, epw, cap, fixed_epw);
     };
+    constexpr uint32_t kShapes[] = {1u, 2u, 4u, 8u};
+    const bool many = items.size() > kMaxItemsPerLaunch;
+    std::vector<uint32_t> item_epw(items.size(), 1u);
+    auto resolve = [&](size_t k) {
+        uint32_t kc = 0;
+        if (items[k].h) resolve_shape(ctx, opts, items[k].h->n_lights, items[k].eyes.n, &item_epw[k], &kc);
+        const uint32_t ke = item_epw[k];
+        if (!(ke == 1 || ke == 2 || ke == 4 || ke == 8)) item_epw[k] = 1;
+    };
+    if (many) {
+        // Only items of different shapes make more than one launch: a call with
+        // more of one shape than a launch holds, whichever walk takes them, stays
+        // one group, which launch_items refuses.
+        bool fits = per_item;
+        size_t of_shape[9] = {};
+        for (size_t k = 0; per_item && k < items.size(); ++k) {
+            resolve(k);
+            fits = fits && ++of_shape[item_epw[k]] <= kMaxItemsPerLaunch;
+        }
+        if (!fits) {
+            LaunchGroup g;
+            g.items.resize(items.size());
+            for (size_t k = 0; k < items.size(); ++k) g.items[k] = k;
+            shape_of(g.items, &g.epw, &g.cap, 0);
+            out.push_back(std::move(g));
+            return;
+        }
+    }
     std::vector<size_t> rest;   // items of the node walk
     if (block_walk) {
-        LaunchGroup g;
-        g.blocks = true;
+        std::vector<size_t> taken;
         for (size_t k = 0; k < items.size(); ++k)
-            (items[k].h && block_walk_takes(items[k].s) ? g.items : rest).push_back(k);
-        if (!g.items.empty()) {
-            shape_of(g.items, &g.epw, &g.cap, 0);   // for the check of the options alone
+            (items[k].h && block_walk_takes(items[k].s) ? taken : rest).push_back(k);
+        // one launch; of more items than it holds, one per shape as below
+        for (uint32_t ge : kShapes) {
+            LaunchGroup g;
+            g.blocks = true;
+            for (size_t k : taken)
+                if (!many || item_epw[k] == ge) g.items.push_back(k);
+            if (g.items.empty()) continue;
+            shape_of(g.items, &g.epw, &g.cap, many ? ge : 0);   // for the check of the options alone
             out.push_back(std::move(g));
+            if (!many) break;
         }
     } else {
         rest.resize(items.size());
@@ -223,14 +257,8 @@ void group_by_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, const std::vect
         out.push_back(std::move(g));
         return;
     }
-    std::vector<uint32_t> item_epw(items.size(), 1u);
-    for (size_t k : rest) {
-        uint32_t kc = 0;
-        if (items[k].h) resolve_shape(ctx, opts, items[k].h->n_lights, items[k].eyes.n, &item_epw[k], &kc);
-        const uint32_t ke = item_epw[k];
-        if (!(ke == 1 || ke == 2 || ke == 4 || ke == 8)) item_epw[k] = 1;
-    }
-    for (uint32_t ge : {1u, 2u, 4u, 8u}) {
+    for (size_t k : rest) resolve(k);
+    for (uint32_t ge : kShapes) {
         LaunchGroup g;
         for (size_t k : rest)
             if (item_epw[k] == ge) g.items.push_back(k);
@@ -541,8 +569,8 @@ static hrr_status run_sync(hrr_ctx* ctx, const std::vector<HostItem>& items, con
         if (cap_override) g.cap = cap_override;
     }
     const int n_groups = (int)groups.size();
-    LaunchScratch* scr[kMaxGroups] = {&ctx->scratch, &ctx->group_scratch[0], &ctx->group_scratch[1],
-                                      &ctx->group_scratch[2], &ctx->group_scratch[3]};
+    LaunchScratch* scr[kMaxGroups] = {&ctx->scratch};
+    for (int g = 1; g < kMaxGroups; ++g) scr[g] = &ctx->group_scratch[g - 1];
 
     const uint32_t ns = opts && opts->n_samples > 1 ? opts->n_samples : 1;
     const uint32_t s0 = opts ? opts->psi_s0 : 0;

@@ -115,6 +115,8 @@ struct LaunchScratch {
 
 struct Server;
 
+constexpr int kMaxGroups = 8;   // launches of one call: each walk's, one per eyes per wave (see group_by_shape)
+
 }  // namespace hrr
 
 struct hrr_ctx {
@@ -123,7 +125,7 @@ struct hrr_ctx {
     uint32_t* d_tile = nullptr;
     uint32_t tile_tz = 32, tile_bits = 0;   // shared trailing zeros / significant bits of the tile values
     hrr::LaunchScratch scratch;   // scratch of the synchronous entry points
-    hrr::LaunchScratch group_scratch[4];   // further launches of one batched call (items grouped by walk and shape)
+    hrr::LaunchScratch group_scratch[hrr::kMaxGroups - 1];   // further launches of one batched call (items grouped by walk and shape)
     std::mutex tune_mu;
     std::map<hrr::TuneKey, hrr::TuneVal> tune;
     std::map<int, uint32_t> tune_leaf;   // log2 lights -> leaf size
@@ -168,13 +170,14 @@ void resolve_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, uint32_t n_light
 // hierarchies first) and every group takes the stack size resolved for its
 // own largest hierarchy and eye set; otherwise one group holds every item
 // with the shape resolved for the largest of them.  Items without a
-// hierarchy go to the one-eye-per-wave group (their launch rejects them).
+// hierarchy go to the one-eye-per-wave group (their launch rejects them).  A
+// call of more items than one launch holds groups the block walk's items by
+// shape as well; more than kMaxItemsPerLaunch items of one shape are refused.
 struct LaunchGroup {
     std::vector<size_t> items;
     uint32_t epw = 1, cap = 512;
     bool blocks = false;   // one launch of the block walk, where epw and cap do not apply
 };
-constexpr int kMaxGroups = 5;   // the block walk's, then one per eyes per wave
 void group_by_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, const std::vector<HostItem>& items, bool block_walk,
                     bool per_item, std::vector<LaunchGroup>& out);
 

@@ -1,0 +1,46 @@
+"""What the host side of a call launches and refuses, on a replaced HIP runtime."""
+import re
+
+import pytest
+
+import paper_1907_12343_amd as hrr
+from _host_runtime import HostContext, build
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    return build(tmp_path_factory.mktemp("host_launches"))
+
+
+@pytest.fixture
+def ctx(lib):
+    c = HostContext(lib)
+    yield c
+    c.close()
+
+
+def test_more_items_than_a_launch_holds(ctx):
+    """A batched call of more than 1024 items runs when no shape (eyes per wave of
+    an item's own hierarchy) has more than 1024 of them, one launch per shape,
+    and is refused otherwise."""
+    small, large = ctx.hierarchy(100), ctx.hierarchy(1 << 16)      # 8 and 4 eyes per wave
+    for method in (0, 1):
+        for n_s, n_l, ok in ((600, 600, True), (1024, 1024, True), (1025, 0, False), (1025, 3, False), (3, 1025, False)):
+            st, counts = ctx.batched([(small, 7, 1e-4, 0)] * n_s + [(large, 5, 1e-4, 0)] * n_l, rmq_method=method)
+            launches = [int(re.search(r"items=(\d+)", x).group(1)) for x in ctx.log() if "items=" in x]
+            if ok:
+                assert st == hrr.HRR_E_OVERFLOW                     # a counting call: no room for the pairs found
+                assert launches == [n_l, n_s] and counts.tolist() == [7] * n_s + [5] * n_l
+            else:
+                assert st == hrr.HRR_E_INVALID and launches == []
+        # a fixed shape, or one shape over both walks, is one launch
+        assert ctx.batched([(small, 7, 1e-4, 0)] * 600 + [(large, 5, 1e-4, 0)] * 600, eyes_per_wave=4,
+                           rmq_method=method)[0] == hrr.HRR_E_INVALID
+        assert ctx.batched([(small, 7, 1e-4, 0)] * 600 + [(small, 5, 1e-30, 0)] * 600, rmq_method=method)[0] == \
+            hrr.HRR_E_INVALID
+        assert ctx.log() == []
+    # up to 1024 items the default method is one launch
+    st, _ = ctx.batched([(small, 7, 1e-4, 0)] * 512 + [(large, 5, 1e-4, 0)] * 512)
+    assert [x.split()[0] for x in ctx.log()] == ["blocks"]
+    ctx.free(small)
+    ctx.free(large)
