@@ -341,7 +341,8 @@ typedef struct hrr_tune_result {
     float ms;               /* best measured time of the probe launch */
 } hrr_tune_result;
 
-/* Time candidate launch shapes (eyes per wave x stack entries) for eyes of
+/* Time candidate launch shapes of the node walk (eyes per wave x stack
+ * entries; the default method's block walk has none) for eyes of
  * `eyes` against each hierarchy in hs[0..n_h) -- normally the same lights
  * built with different leaf sizes -- and remember the fastest for hierarchies
  * of this size class (log2 of the light count) and this eye count class.
@@ -356,7 +357,7 @@ typedef struct hrr_tune_result {
 hrr_status hrr_autotune(hrr_ctx* ctx, const hrr_hierarchy* const* hs, uint32_t n_h,
                         const hrr_eyes* eyes, float s, uint32_t max_probe_eyes,
                         hrr_tune_result* best, void* stream);
-/* Batched autotuner.  sets holds n_sets x n_items work items (host array,
+/* Batched autotuner of the node walk.  sets holds n_sets x n_items work items (host array,
  * set-major): the same eye sets against the same lights in every set, set q
  * built with its own leaf size (normally 1, 2, 4, 8).  For every set the
  * call times ONE launch of all its items (their own eyes, a scratch output

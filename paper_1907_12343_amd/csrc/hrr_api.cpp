@@ -546,7 +546,8 @@ HRR_EXPORT void hrr_free_hierarchy(hrr_ctx* ctx, hrr_hierarchy* h) {
 // ---------------------------------------------------------------------------
 
 // One synchronous traversal call.  The default method runs one launch of the
-// block walk.  Other methods, and launches that count statistics, run the node
+// block walk.  Other methods, launches that count statistics, and the tuner's
+// probes (epw_override: the shapes it times are the node walk's) run the node
 // walk: with the shape left to the library
 // (eyes_per_wave = 0, no override) a call of several items groups them by
 // their own shape -- hierarchies of different sizes want different numbers of
@@ -563,7 +564,7 @@ static hrr_status run_sync(hrr_ctx* ctx, const std::vector<HostItem>& items, con
     const bool want_stats = opts && (opts->flags & HRR_F_STATS);
     const bool per_item = n > 1 && epw_override == 0 && !(opts && opts->eyes_per_wave);
     std::vector<LaunchGroup> groups;
-    group_by_shape(ctx, opts, items, method == HRR_RMQ_PAPER && !want_stats, per_item, groups);
+    group_by_shape(ctx, opts, items, method == HRR_RMQ_PAPER && !want_stats && !epw_override, per_item, groups);
     for (auto& g : groups) {
         if (epw_override) g.epw = epw_override;
         if (cap_override) g.cap = cap_override;

@@ -44,3 +44,30 @@ def test_more_items_than_a_launch_holds(ctx):
     assert [x.split()[0] for x in ctx.log()] == ["blocks"]
     ctx.free(small)
     ctx.free(large)
+
+
+SHAPES = [(1, 192), (1, 256), (1, 512)] + [(e, c) for e in (2, 4, 8) for c in (512, 256, 1024)]
+
+
+def test_autotuner_times_the_walk_whose_shape_it_chooses(ctx):
+    """Every probe of both autotuners is a launch of the node walk in the shape
+    that is tried (the block walk, which has no shape, takes no part)."""
+    import ctypes
+    hs = [ctx.hierarchy(5000, leaf=leaf) for leaf in (1, 4)]
+    ctx.log()
+    E, best = ctx.eyes(3000), hrr.HrrTuneResult()
+    arr = (ctypes.c_void_p * 2)(*hs)
+    assert ctx.lib.hrr_autotune(ctx.handle, arr, 2, ctypes.byref(E), 1e-4, 1000, ctypes.byref(best), None) == hrr.HRR_OK
+    lines = [x for x in ctx.log() if "tasks=" in x]
+    shapes = [tuple(int(v) for v in re.search(r"epw=(\d+) stack=(\d+)", x).groups()) for x in lines]
+    per_leaf = [(1, 192)] + [q for q in SHAPES for _ in range(2)]     # a counting call, then two runs a shape
+    assert shapes == per_leaf * 2 and all(x.startswith("nodes") and "method=0" in x for x in lines)
+    items = (hrr.HrrWorkItem * 4)()
+    for k in range(4):
+        items[k] = hrr.HrrWorkItem(hs[k // 2], ctx.eyes(700 + 100 * (k % 2)), 1e-4, 0, 0, 0)
+    assert ctx.lib.hrr_autotune_batched(ctx.handle, items, 2, 2, ctypes.byref(best), None) == hrr.HRR_OK
+    lines = [x for x in ctx.log() if "tasks=" in x]
+    shapes = [tuple(int(v) for v in re.search(r"epw=(\d+) stack=(\d+)", x).groups()) for x in lines]
+    assert shapes == per_leaf * 2 and all(x.startswith("nodes") and "items=2" in x for x in lines)
+    for h in hs:
+        ctx.free(h)
