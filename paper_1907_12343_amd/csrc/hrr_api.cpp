@@ -577,6 +577,11 @@ static hrr_status run_sync(hrr_ctx* ctx, const std::vector<HostItem>& items, con
     const uint32_t s0 = opts ? opts->psi_s0 : 0;
     const bool reorder = !(opts && (opts->flags & HRR_F_NO_REORDER));
     const bool timing = opts && (opts->flags & HRR_F_TIMING);
+    // a call with an item that cannot be launched launches none of its groups
+    for (size_t k = 0; n_groups > 1 && k < n; ++k) {
+        const hrr_status st = check_item(ctx, items[k], k, pairs != nullptr, ns);
+        if (st != HRR_OK) return st;
+    }
     std::vector<HostItem> sub;
     for (int g = 0; g < n_groups; ++g) {
         sub.clear();

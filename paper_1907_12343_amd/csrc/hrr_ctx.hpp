@@ -181,6 +181,9 @@ struct LaunchGroup {
 void group_by_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, const std::vector<HostItem>& items, bool block_walk,
                     bool per_item, std::vector<LaunchGroup>& out);
 
+// Whether the k-th item of a call can be launched (have_pairs: the call has an output buffer).
+hrr_status check_item(const hrr_ctx* ctx, const HostItem& it, size_t k, bool have_pairs, uint32_t n_samples);
+
 // Enqueue one persistent launch of a set of items on `stream` with scratch
 // `S`: the eye order, the traversal, the compaction that makes every item's
 // stored pairs dense (on the device), and the readback of the counters.

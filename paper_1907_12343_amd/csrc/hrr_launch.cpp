@@ -52,6 +52,18 @@ void product_test_bounds(float s, float* t_cull, float* t_keep, float* d2_fast) 
 
 }  // namespace
 
+hrr_status check_item(const hrr_ctx* ctx, const HostItem& it, size_t k, bool have_pairs, uint32_t n_samples) {
+    if (!it.h) return fail(HRR_E_INVALID, "item %zu: null hierarchy", k);
+    if (it.h->owner != ctx) return fail(HRR_E_INVALID, "item %zu: hierarchy belongs to another context", k);
+    if (!(it.s > 0.0f) || !isfinite(it.s)) return fail(HRR_E_INVALID, "item %zu: s must be finite and > 0", k);
+    if (it.eyes.n > 0 && !it.eyes.xyz) return fail(HRR_E_INVALID, "item %zu: null eye positions", k);
+    if (it.eyes.width == 0) return fail(HRR_E_INVALID, "item %zu: width must be >= 1", k);
+    if (it.out_capacity > 0 && !have_pairs) return fail(HRR_E_INVALID, "item %zu: null pairs buffer", k);
+    if ((uint64_t)it.eyes.n * n_samples > 0xFFFFFFFFull)
+        return fail(HRR_E_INVALID, "item %zu: eyes x samples exceeds 2^32 - 1", k);
+    return HRR_OK;
+}
+
 hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostItem>& items, const LaunchGroup& shape,
                         uint32_t method, uint32_t n_samples, uint32_t psi_s0, bool stats,
                         bool reorder, uint32_t* pairs, float* weights, hipStream_t stream, bool timing) {
@@ -94,14 +106,9 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
     for (size_t k = 0; k < n; ++k) {
         const HostItem& it = items[k];
         const hrr_hierarchy* h = it.h;
-        if (!h) return fail(HRR_E_INVALID, "item %zu: null hierarchy", k);
-        if (h->owner != ctx) return fail(HRR_E_INVALID, "item %zu: hierarchy belongs to another context", k);
-        if (!(it.s > 0.0f) || !isfinite(it.s)) return fail(HRR_E_INVALID, "item %zu: s must be finite and > 0", k);
-        if (it.eyes.n > 0 && !it.eyes.xyz) return fail(HRR_E_INVALID, "item %zu: null eye positions", k);
-        if (it.eyes.width == 0) return fail(HRR_E_INVALID, "item %zu: width must be >= 1", k);
-        if (it.out_capacity > 0 && !pairs) return fail(HRR_E_INVALID, "item %zu: null pairs buffer", k);
+        const hrr_status bad = check_item(ctx, it, k, pairs != nullptr, n_samples);
+        if (bad != HRR_OK) return bad;
         const uint64_t nv = (uint64_t)it.eyes.n * n_samples;
-        if (nv > 0xFFFFFFFFull) return fail(HRR_E_INVALID, "item %zu: eyes x samples exceeds 2^32 - 1", k);
         if (shape.blocks)
             block_task_split(h->n_lights, launch_cost, resident, dense, &task_shift[k], &sub_log[k]);
         const uint64_t task_eyes = shape.blocks ? 1ull << task_shift[k] : epw;

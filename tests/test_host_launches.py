@@ -71,3 +71,22 @@ def test_autotuner_times_the_walk_whose_shape_it_chooses(ctx):
     assert shapes == per_leaf * 2 and all(x.startswith("nodes") and "items=2" in x for x in lines)
     for h in hs:
         ctx.free(h)
+
+
+@pytest.mark.parametrize("epw", [0, 1])
+def test_a_bad_item_is_refused_before_anything_runs(ctx, epw):
+    """One bad item among good ones: the call names it by its place in the call,
+    and no item is launched (the output stays as it was)."""
+    h, other = ctx.hierarchy(5000), HostContext(ctx.lib)
+    foreign = other.hierarchy(10)
+    good = (h, 7, 1e-4, 100)
+    for bad, text in (((h, 7, float("nan"), 100), "s must be finite"), ((h, 7, 0.0, 100), "s must be finite"),
+                      ((None, 7, 1e-4, 100), "null hierarchy"), ((foreign, 7, 1e-4, 100), "another context")):
+        st, counts = ctx.batched([good, good, bad, (h, 7, 1e-30, 100)], eyes_per_wave=epw)
+        assert st == hrr.HRR_E_INVALID and ctx.error().startswith("item 2: ") and text in ctx.error()
+        assert [x for x in ctx.log() if "tasks=" in x] == [] and not counts.any()
+    assert ctx.batched([good, good, (h, 7, 1e-30, 100)], eyes_per_wave=epw)[0] == hrr.HRR_OK
+    assert [x.split()[0] for x in ctx.log() if "tasks=" in x] == ["blocks", "nodes"]
+    other.free(foreign)
+    other.close()
+    ctx.free(h)
