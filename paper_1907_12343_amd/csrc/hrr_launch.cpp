@@ -86,8 +86,10 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
     double launch_cost = 0.0;
     uint64_t room = 0;
     for (const HostItem& it : items) {
-        if (it.h) launch_cost += (double)it.eyes.n * n_samples * eye_cost(it.h->n_lights);
-        room = it.out_capacity > ~0ull - room ? ~0ull : room + it.out_capacity;
+        if (!it.h) continue;   // refused below
+        launch_cost += (double)it.eyes.n * n_samples * eye_cost(it.h->n_lights);
+        const uint64_t r = item_room(it.out_capacity, (uint64_t)it.eyes.n * n_samples, it.h->n_lights);
+        room = r > ~0ull - room ? ~0ull : room + r;
     }
     const bool dense = shape.blocks && block_walk_dense(room, launch_cost);
     int bpc = 0;
@@ -426,7 +428,7 @@ hrr_status launch_noalloc(hrr_ctx* ctx, const hrr_hierarchy* h, const hrr_eyes& 
     const size_t lds_wave = block_walk ? 0 : hrr_trav_lds_per_wave(cap, epw);
     int bpc = 0;
     const double cost = (double)nv * eye_cost(h->n_lights);
-    const bool dense = block_walk && block_walk_dense(capacity, cost);
+    const bool dense = block_walk && block_walk_dense(item_room(capacity, nv, h->n_lights), cost);
     e = block_walk ? hrr_cull_occupancy(with_w, dense, 1, &bpc)
                    : hrr_traverse_occupancy(epw, method, 0, with_w, hrr_trav_lds_per_block(1, lds_wave), &bpc);
     if (e != hipSuccess) return hip_fail(e, "occupancy");

@@ -75,17 +75,27 @@ inline double eye_cost(uint32_t n_lights) { return pow((double)(n_lights > 1u ? 
 // work by far more than the estimate says, and a launch ends with its longest
 // last task), but at least kMinTaskCost each (a task costs an atomic and an
 // eye upload, and a wave that leaves an item two or three more) and at most
-// 64 eyes, a wave's eye slots.
+// 64 eyes, a wave's eye slots.  A launch of less than kFewTasks times
+// kMinTaskCost still makes about kFewTasks tasks, or one per eye: it would else
+// leave the GPU to a few waves (us a call into a buffer of 2^26 pairs, tasks of
+// kMinTaskCost / kFewTasks of them / the node walk: 300 eyes x 2^18 lights at s
+// = 1e-2 1724 / 326 / 1611, at s = 1e-8 60 / 75 / 112; 3000 eyes x 2^14 lights
+// at s = 1e-4 146 / 130 / 169).  More of them cost more in the compaction of
+// their partly filled chunks than they gain (one task per resident wave: 307 us
+// for 30,000 eyes x 2^10 lights, 101 as it is).
 //
 // A launch with dense output is small: it aims at kDenseTasks tasks, one per
 // wave, and where whole eyes make fewer than a quarter of that, an eye's walk is
 // cut into the 4 or 16 blocks of the tree's first levels.
 constexpr double kTasksPerWave = 32.0;
 constexpr double kMinTaskCost = 16384.0;
+constexpr double kFewTasks = 512.0;
 constexpr double kDenseTasks = 4096.0;
 inline void block_task_split(uint32_t n_lights, double launch_cost, uint64_t resident_waves, bool dense,
                              uint32_t* task_shift, uint32_t* sub_log) {
-    const double want = dense ? fmin(launch_cost / kDenseTasks, kMinTaskCost) : fmax(launch_cost / (kTasksPerWave * (double)resident_waves), kMinTaskCost);
+    const double want = dense ? fmin(launch_cost / kDenseTasks, kMinTaskCost)
+                              : fmax(launch_cost / (kTasksPerWave * (double)resident_waves),
+                                     fmin(launch_cost / kFewTasks, kMinTaskCost));
     const double target = want / eye_cost(n_lights);   // eyes per task
     uint32_t shift = 0, sub = 0;
     if (dense) {
@@ -106,6 +116,13 @@ inline void block_task_split(uint32_t n_lights, double launch_cost, uint64_t res
 // (its LDS leaves 5 blocks to a CU against 8).
 inline bool block_walk_dense(uint64_t capacity, double launch_cost) {
     return capacity ? capacity <= (1ull << 24) : launch_cost < 268435456.0;
+}
+// The pairs that an item can store: no more than its eyes have lights, however
+// large its buffer.  A small launch into a large buffer is dense by this (300
+// eyes x 2^12 lights into 2^25 pairs: 118 us in chunks, 37 dense).
+inline uint64_t item_room(uint64_t capacity, uint64_t virtual_eyes, uint32_t n_lights) {
+    const uint64_t all = virtual_eyes * n_lights;   // below 2^32 * 2^25
+    return capacity < all ? capacity : all;
 }
 
 // How often one wave can leave one item (publishing a partly filled chunk).

@@ -90,3 +90,29 @@ def test_a_bad_item_is_refused_before_anything_runs(ctx, epw):
     other.free(foreign)
     other.close()
     ctx.free(h)
+
+
+def _fields(line):
+    return {k: int(v) for k, v in re.findall(r"(\w+)=(\d+)", line)}
+
+
+@pytest.mark.parametrize("n_lights", [64, 4099, 16387, 262147])
+@pytest.mark.parametrize("n_eyes", [1, 30, 300, 3000])
+def test_a_large_buffer_does_not_idle_the_gpu(ctx, n_lights, n_eyes):
+    """Few eyes into a buffer far larger than their pairs: the output is dense
+    where the eyes have at most 2^24 lights in all, and a chunked launch makes a
+    hundred tasks or one per eye.  Allocation-free calls follow the same rule."""
+    import ctypes
+    h = ctx.hierarchy(n_lights, leaf=8)
+    ctx.log()
+    E, o = ctx.eyes(n_eyes), hrr._opts()
+    assert ctx.traverse(h, n_eyes, 1 << 26) == hrr.HRR_OK
+    result = (ctypes.c_uint64 * 2)()
+    assert ctx.lib.hrr_traverse_noalloc(ctx.handle, h, ctypes.byref(E), 1e-4, ctypes.byref(o), 0x2000, None, 1 << 26,
+                                        ctypes.cast(result, ctypes.c_void_p), None) == hrr.HRR_OK
+    lines = [_fields(x) for x in ctx.log() if x.startswith("blocks")]
+    assert len(lines) == 2
+    for f in lines:
+        assert f["dense"] == (n_eyes * n_lights <= 1 << 24)
+        assert f["tasks"] >= min(n_eyes, 100)
+    ctx.free(h)
