@@ -16,8 +16,8 @@
 #include "hrr_layout.hpp"
 
 extern "C" hipError_t hrr_noalloc_scratch(int device, void** out);   // hrr_kernels.hip
-extern "C" hipError_t hrr_launch_frontier(const hrr::Node* nodes, uint32_t n_lights, uint32_t leaf_size, float* out,
-                                          hipStream_t stream);   // hrr_kernels.hip
+extern "C" hipError_t hrr_launch_frontier(const hrr::Node* nodes, uint32_t n_lights, uint32_t leaf_size,
+                                          const float* blocks, float* out, hipStream_t stream);   // hrr_kernels.hip
 extern "C" hipError_t hrr_launch_blocks(const float* lights, uint32_t n_lights, float* blocks, hipStream_t stream);
 
 #define HRR_EXPORT extern "C" __attribute__((visibility("default")))
@@ -231,9 +231,17 @@ void group_by_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, const std::vect
     }
     std::vector<size_t> rest;   // items of the node walk
     if (block_walk) {
+        const uint64_t ns = opts && opts->n_samples > 1 ? opts->n_samples : 1;
+        auto takes = [&](const HostItem& it) { return it.h && block_walk_takes(it.s); };
+        LaunchSize size;
+        for (const HostItem& it : items)
+            if (takes(it)) size.add(it.eyes.n * ns, it.h->n_lights, it.out_capacity);
+        const bool dense = block_walk_dense(size.room, size.cost);
         std::vector<size_t> taken;
-        for (size_t k = 0; k < items.size(); ++k)
-            (items[k].h && block_walk_takes(items[k].s) ? taken : rest).push_back(k);
+        for (size_t k = 0; k < items.size(); ++k) {
+            const HostItem& it = items[k];
+            (takes(it) && !node_walk_scattered(it.h->spread, it.h->n_lights, size, dense) ? taken : rest).push_back(k);
+        }
         // one launch; of more items than it holds, one per shape as below
         for (uint32_t ge : kShapes) {
             LaunchGroup g;
@@ -386,9 +394,9 @@ namespace hrr {
 
 hrr_status attach_frontier(hrr_hierarchy* h, hipStream_t stream) {
     if (!h->n_nodes) return HRR_OK;
-    const size_t fb = ((size_t)kFrontierMax * kFrontierFloats + 1) * sizeof(float);
+    const size_t fb = kFrontierWords * sizeof(float);
     hipError_t e = hipMalloc((void**)&h->d_frontier, fb);
-    if (e == hipSuccess) e = hrr_launch_frontier(h->d_nodes, h->n_lights, h->leaf_size, h->d_frontier, stream);
+    if (e == hipSuccess) e = hrr_launch_frontier(h->d_nodes, h->n_lights, h->leaf_size, h->d_blocks, h->d_frontier, stream);
     if (e != hipSuccess) return hip_fail(e, "hierarchy top");
     h->device_bytes += fb;
     return HRR_OK;
@@ -451,13 +459,15 @@ HRR_EXPORT hrr_status hrr_build_hierarchy(hrr_ctx* ctx, const float* lights_xyz,
         return hip_fail(e, "hierarchy upload");
     }
     h->device_bytes = nb + lb + pb;
-    hrr_status st = attach_frontier(h, nullptr);
-    if (st == HRR_OK) st = attach_blocks(h, nullptr);
+    hrr_status st = attach_blocks(h, nullptr);
+    if (st == HRR_OK) st = attach_frontier(h, nullptr);
     if (st == HRR_OK && (e = hipStreamSynchronize(nullptr)) != hipSuccess) st = hip_fail(e, "block tree");
+    uint32_t top[2] = {0, 0};
     if (st == HRR_OK && h->d_frontier &&
-        (e = hipMemcpy(&h->n_frontier, h->d_frontier + (size_t)kFrontierMax * kFrontierFloats, sizeof(uint32_t),
-                       hipMemcpyDeviceToHost)) != hipSuccess)
+        (e = hipMemcpy(top, h->d_frontier + kFrontierCount, sizeof top, hipMemcpyDeviceToHost)) != hipSuccess)
         st = hip_fail(e, "hierarchy top");
+    h->n_frontier = top[0];
+    memcpy(&h->spread, &top[1], sizeof h->spread);
     if (st != HRR_OK) {
         hrr_free_hierarchy(ctx, h);
         return st;

@@ -26,8 +26,8 @@ extern "C" hipError_t hrr_dev_nodes(const uint64_t* code, uint32_t n, uint32_t l
                                     uint32_t* out, hipStream_t stream);
 extern "C" hipError_t hrr_dev_records(const uint32_t* words, uint32_t n, const float* lights, const float* blocks,
                                       Node* nodes, hipStream_t stream);
-extern "C" hipError_t hrr_launch_frontier(const Node* nodes, uint32_t n_lights, uint32_t leaf_size, float* out,
-                                          hipStream_t stream);   // hrr_kernels.hip
+extern "C" hipError_t hrr_launch_frontier(const Node* nodes, uint32_t n_lights, uint32_t leaf_size,
+                                          const float* blocks, float* out, hipStream_t stream);   // hrr_kernels.hip
 extern "C" hipError_t hrr_launch_blocks(const float* lights, uint32_t n_lights, float* blocks, hipStream_t stream);
 
 namespace {
@@ -119,7 +119,7 @@ HRR_EXPORT hrr_status hrr_build_hierarchy_device(hrr_ctx* ctx, const float* ligh
     Carver carve{static_cast<unsigned char*>(ctx->build_scratch.p)};
     const Scratch T(carve, n, sort_bytes);
     const size_t n_block_floats = n ? block_tree_floats(n) : 0;
-    const size_t n_frontier_floats = max_internal ? (size_t)kFrontierMax * kFrontierFloats + 1 : 0;
+    const size_t n_frontier_floats = max_internal ? kFrontierWords : 0;
     auto tables = [&](Carver& c) {
         h->d_lights = c.take<float>(std::max<size_t>(n, 1) * 4);
         h->d_perm = c.take<uint32_t>(std::max<size_t>(n, 1));
@@ -175,12 +175,13 @@ HRR_EXPORT hrr_status hrr_build_hierarchy_device(hrr_ctx* ctx, const float* ligh
         if ((e = hipMemsetAsync(h->d_nodes, 0, (size_t)n_records * sizeof(Node), stream)) != hipSuccess ||
             (e = hrr_dev_records(T.nodes, n, h->d_lights, h->d_blocks, h->d_nodes, stream)) != hipSuccess)
             return fail_free(hip_fail(e, "node records"));
-        if ((e = hrr_launch_frontier(h->d_nodes, n, leaf_size, h->d_frontier, stream)) != hipSuccess ||
-            (e = hipMemcpyAsync(pin, h->d_frontier + (size_t)kFrontierMax * kFrontierFloats, sizeof(uint32_t),
-                                hipMemcpyDeviceToHost, stream)) != hipSuccess ||
+        if ((e = hrr_launch_frontier(h->d_nodes, n, leaf_size, h->d_blocks, h->d_frontier, stream)) != hipSuccess ||
+            (e = hipMemcpyAsync(pin, h->d_frontier + kFrontierCount, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, stream)) !=
+                hipSuccess ||
             (e = hipStreamSynchronize(stream)) != hipSuccess)
             return fail_free(hip_fail(e, "hierarchy top"));
         h->n_frontier = pin[0];
+        memcpy(&h->spread, pin + 1, sizeof h->spread);
     }
     *out = h;
     return HRR_OK;

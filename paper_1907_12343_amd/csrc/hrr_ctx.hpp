@@ -19,8 +19,9 @@ struct hrr_hierarchy {
     uint32_t split = HRR_SPLIT_RADIX;
     float box[6] = {0, 0, 0, 0, 0, 0};
     hrr::Node* d_nodes = nullptr;
-    float* d_frontier = nullptr;      // kFrontierMax entries of kFrontierFloats, then the entry count
+    float* d_frontier = nullptr;      // kFrontierMax entries of kFrontierFloats, then their number and the spread
     uint32_t n_frontier = 0;
+    float spread = 0.0f;              // of the block tree (hrr_types.hpp)
     float* d_blocks = nullptr;        // block tree (hrr_types.hpp), for n_lights > 0
     void* d_base = nullptr;           // device build: the one allocation of every table but d_nodes
     float* d_lights = nullptr;       // float4 per light
@@ -162,8 +163,9 @@ void resolve_shape(hrr_ctx* ctx, const hrr_traverse_opts* opts, uint32_t n_light
                    uint32_t* epw, uint32_t* cap, uint32_t fixed_epw = 0);
 
 // The launches of a call.  With block_walk (the default method, no
-// statistics), every item that the block walk takes (block_walk_takes in
-// hrr_layout.hpp) goes into one launch of that walk; the others run the node
+// statistics), every item that the block walk takes (block_walk_takes and
+// node_walk_scattered in hrr_layout.hpp) goes into one launch of that walk; the
+// others run the node
 // walk: with per_item, they are
 // grouped by the eyes per wave of their own shape (tuned or by hierarchy
 // size; groups in the order 1, 2, 4, 8 eyes per wave, i.e. largest
@@ -198,11 +200,12 @@ hrr_status finish_items(hrr_ctx* ctx, LaunchScratch& S);
 
 void release_scratch(LaunchScratch& S);
 
-// Allocate h->d_frontier and enqueue the computation of the hierarchy's top
-// (the entry count lands in the table's last word) on `stream`.
-hrr_status attach_frontier(hrr_hierarchy* h, hipStream_t stream);
-// The same for the block tree of h->d_lights, which the default traversal walks.
+// Allocate h->d_blocks and enqueue the computation of the block tree of
+// h->d_lights, which the default traversal walks, on `stream`.
 hrr_status attach_blocks(hrr_hierarchy* h, hipStream_t stream);
+// The same for the hierarchy's top, h->d_frontier, once the block tree is
+// enqueued (its spread lands in the table's last word).
+hrr_status attach_frontier(hrr_hierarchy* h, hipStream_t stream);
 
 // The allocation-free traversal of one eye set (hrr_traverse_noalloc): every
 // launch on `stream`, nothing allocated, nothing read back.

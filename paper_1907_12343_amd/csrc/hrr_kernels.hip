@@ -1620,8 +1620,35 @@ __global__ __launch_bounds__(256) void block_up_kernel(uint32_t level, float4* _
 // Entries keep index order; after level l there are at most 2^l of them.
 // The root's own box is never needed: the root is internal (the caller only
 // runs this for hierarchies with records) and is always expanded.
+// A second block of the launch measures the spread of the lights' block tree
+// (hrr_types.hpp) while the first one waits for its records.
+__device__ __forceinline__ float block_spread(const float4* __restrict__ blocks, uint32_t n_lights) {
+    const uint32_t log = block_tree_log(n_lights), leaf_log = block_leaf_log(log);
+    const uint32_t n_blocks = ((n_lights - 1u) >> leaf_log) + 1u, first = 1u << (log - leaf_log);
+    const uint32_t samples = min(n_blocks, kSpreadSamples);
+    const float4 rlo = blocks[2], rhi = blocks[3];
+    const float rl[3] = {rlo.x, rlo.y, rlo.z}, rh[3] = {rhi.x, rhi.y, rhi.z};
+    float sum = 0.0f;
+#pragma unroll   // the loads at once
+    for (uint32_t r = 0; r < kSpreadSamples / 64u; ++r) {
+        const uint32_t q = r * 64u + threadIdx.x;
+        const uint32_t id = first + (uint32_t)((uint64_t)min(q, samples - 1u) * n_blocks / samples);
+        const float4 lo = blocks[2u * id], hi = blocks[2u * id + 1u];
+        const float l[3] = {lo.x, lo.y, lo.z}, h[3] = {hi.x, hi.y, hi.z};
+        sum += q < samples ? block_share(l, h, rl, rh) : 0.0f;
+    }
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    return sum * ((float)n_blocks / (float)samples);
+}
+
 __global__ __launch_bounds__(64) void frontier_kernel(const Node* __restrict__ nodes, uint32_t n_lights,
-                                                      uint32_t leaf, float* __restrict__ out) {
+                                                      uint32_t leaf, const float4* __restrict__ blocks,
+                                                      float* __restrict__ out) {
+    if (blockIdx.x == 1u) {
+        const float spread = block_spread(blocks, n_lights);
+        if (threadIdx.x == 0) out[kFrontierSpread] = spread;
+        return;
+    }
     struct Entry { uint32_t a, b, rec; float lo[3], hi[3]; };
     __shared__ Entry next[kFrontierMax];
     const uint32_t t = threadIdx.x;
@@ -1666,7 +1693,7 @@ __global__ __launch_bounds__(64) void frontier_kernel(const Node* __restrict__ n
         o[4] = e.hi[0]; o[5] = e.hi[1]; o[6] = e.hi[2]; o[7] = __uint_as_float(e.b);
         o[8] = __uint_as_float(e.rec); o[9] = 0.0f; o[10] = 0.0f; o[11] = 0.0f;
     }
-    if (t == 0) reinterpret_cast<uint32_t*>(out)[kFrontierMax * kFrontierFloats] = n;
+    if (t == 0) reinterpret_cast<uint32_t*>(out)[kFrontierCount] = n;
 }
 
 // ---------------------------------------------------------------------------
@@ -2111,10 +2138,11 @@ extern "C" hipError_t hrr_launch_blocks(const float* lights, uint32_t n_lights, 
 }
 
 // The top of a hierarchy with records (see frontier_kernel): out holds
-// kFrontierMax * kFrontierFloats floats, then the entry count.
-extern "C" hipError_t hrr_launch_frontier(const hrr::Node* nodes, uint32_t n_lights, uint32_t leaf_size, float* out,
-                                          hipStream_t stream) {
-    hipLaunchKernelGGL(hrr::frontier_kernel, dim3(1), dim3(64), 0, stream, nodes, n_lights, leaf_size, out);
+// kFrontierWords words; blocks is the lights' block tree.
+extern "C" hipError_t hrr_launch_frontier(const hrr::Node* nodes, uint32_t n_lights, uint32_t leaf_size,
+                                          const float* blocks, float* out, hipStream_t stream) {
+    hipLaunchKernelGGL(hrr::frontier_kernel, dim3(2), dim3(64), 0, stream, nodes, n_lights, leaf_size,
+                       reinterpret_cast<const float4*>(blocks), out);
     return hipGetLastError();
 }
 

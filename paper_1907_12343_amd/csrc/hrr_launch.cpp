@@ -83,15 +83,11 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
     // ---- grid: persistent waves, as many as stay resident ----
     const size_t lds_wave = shape.blocks ? 0 : hrr_trav_lds_per_wave(cap, epw);
     // estimated work of the launch (virtual eyes x eye_cost) and room for its pairs
-    double launch_cost = 0.0;
-    uint64_t room = 0;
-    for (const HostItem& it : items) {
-        if (!it.h) continue;   // refused below
-        launch_cost += (double)it.eyes.n * n_samples * eye_cost(it.h->n_lights);
-        const uint64_t r = item_room(it.out_capacity, (uint64_t)it.eyes.n * n_samples, it.h->n_lights);
-        room = r > ~0ull - room ? ~0ull : room + r;
-    }
-    const bool dense = shape.blocks && block_walk_dense(room, launch_cost);
+    LaunchSize size;
+    for (const HostItem& it : items)
+        if (it.h) size.add((uint64_t)it.eyes.n * n_samples, it.h->n_lights, it.out_capacity);   // others are refused below
+    const double launch_cost = size.cost;
+    const bool dense = shape.blocks && block_walk_dense(size.room, launch_cost);
     int bpc = 0;
     hipError_t e;
     e = shape.blocks ? hrr_cull_occupancy(with_w, dense, (uint32_t)n, &bpc)
@@ -424,11 +420,14 @@ hrr_status launch_noalloc(hrr_ctx* ctx, const hrr_hierarchy* h, const hrr_eyes& 
     hipError_t e = hipSetDevice(ctx->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     const int with_w = weights != nullptr;
-    const bool block_walk = method == HRR_RMQ_PAPER && block_walk_takes(s);
+    LaunchSize size;
+    size.add(nv, h->n_lights, capacity);
+    const double cost = size.cost;
+    const bool block_walk = method == HRR_RMQ_PAPER && block_walk_takes(s) &&
+                            !node_walk_scattered(h->spread, h->n_lights, size, block_walk_dense(size.room, cost));
     const size_t lds_wave = block_walk ? 0 : hrr_trav_lds_per_wave(cap, epw);
     int bpc = 0;
-    const double cost = (double)nv * eye_cost(h->n_lights);
-    const bool dense = block_walk && block_walk_dense(item_room(capacity, nv, h->n_lights), cost);
+    const bool dense = block_walk && block_walk_dense(size.room, cost);
     e = block_walk ? hrr_cull_occupancy(with_w, dense, 1, &bpc)
                    : hrr_traverse_occupancy(epw, method, 0, with_w, hrr_trav_lds_per_block(1, lds_wave), &bpc);
     if (e != hipSuccess) return hip_fail(e, "occupancy");

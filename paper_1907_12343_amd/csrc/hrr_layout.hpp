@@ -125,6 +125,41 @@ inline uint64_t item_room(uint64_t capacity, uint64_t virtual_eyes, uint32_t n_l
     return capacity < all ? capacity : all;
 }
 
+// Estimated work of a launch (the sum over its items of virtual eyes x
+// eye_cost), its virtual eyes and the pairs that it can store.
+struct LaunchSize {
+    double cost = 0.0;
+    uint64_t eyes = 0, room = 0;
+    void add(uint64_t virtual_eyes, uint32_t n_lights, uint64_t capacity) {
+        const uint64_t r = item_room(capacity, virtual_eyes, n_lights);
+        cost += (double)virtual_eyes * eye_cost(n_lights);
+        eyes = virtual_eyes > ~0ull - eyes ? ~0ull : eyes + virtual_eyes;
+        room = r > ~0ull - room ? ~0ull : room + r;
+    }
+};
+
+// Whether lights of this spread (hrr_types.hpp) are too scattered for the block
+// walk: an eye inside a smallest block's box must test all its lights, where the
+// node walk still has the boxes of fewer lights below it.  Speed of the block
+// walk relative to the node walk, scenes 1, 5, 10 and 100 times as large as the
+// box that orders their lights, and beside it:
+//   dense output: spread 1 .. 4 at least 2; 3,000 eyes 2.2 .. 5.5 at spread 2^8,
+//     0.94 .. 1.5 at 2^13 (2^18 lights), 0.71 at 2^15 (2^20); 30,000 eyes 1.03 ..
+//     2.5 at 2^8, 0.98 .. 1.4 at 2^9, 0.43 .. 1.3 from 2^10; below 2^16 lights
+//     and in small launches never under 1, as blocks that are cut among several
+//     waves make up for it;
+//   chunks: 3,000 .. 30,000 eyes 0.9 .. 1.8 at 2^6 and 2^7, 0.6 .. 1.8 at 2^8,
+//     0.17 .. 0.9 from 2^10, and 0.5 with 2^12 lights where an eye is in every
+//     second block; 300,000 eyes 0.9 .. 1.8 up to 2^10, 0.6 .. 0.9 from 2^11;
+//     below 2^12 lights at least 1.
+inline bool node_walk_scattered(float spread, uint32_t n_lights, const LaunchSize& size, bool dense) {
+    if (dense)
+        return n_lights >= (1u << 16) && size.cost >= 1e7 && spread >= 512.0f && (double)spread * (double)size.eyes >= 2.4e7;
+    const uint32_t n_blocks = block_tree_lights(n_lights) >> block_leaf_log(block_tree_log(n_lights));
+    const float bound = size.eyes < (1u << 17) ? fminf(256.0f, (float)n_blocks / 8.0f) : 2048.0f;
+    return n_lights >= (1u << 12) && spread >= bound;
+}
+
 // How often one wave can leave one item (publishing a partly filled chunk).
 // A wave visits each queue once (cyclic order from its own) and takes a
 // queue's tasks in increasing order, so within one queue visit the items it

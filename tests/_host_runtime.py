@@ -28,6 +28,7 @@ def build(directory):
         getattr(lib, name).argtypes = args
     for name in ("host_used", "host_blocks", "host_log"):
         getattr(lib, name).restype = ctypes.c_size_t
+    lib.host_spread.argtypes = [ctypes.c_float]
     lib.host_limit.argtypes = [ctypes.c_size_t]
     lib.host_fail_new.argtypes = [ctypes.c_long]
     lib.host_log.argtypes = [_P, ctypes.c_size_t]
@@ -83,6 +84,11 @@ class HostContext:
         E, o, n = self.eyes(n_eyes), hrr._opts(**opt), ctypes.c_uint64()
         return self.lib.hrr_traverse(self.handle, h, ctypes.byref(E), s, ctypes.byref(o), pairs if capacity else None, None,
                                      capacity, ctypes.byref(n), None, None)
+
+    def noalloc(self, h, n_eyes, capacity, s=1e-4, **opt):
+        E, o = self.eyes(n_eyes), hrr._opts(**opt)
+        return self.lib.hrr_traverse_noalloc(self.handle, h, ctypes.byref(E), s, ctypes.byref(o), 0x2000 if capacity else None,
+                                             None, capacity, 0x3000, None)
 
     def batched(self, items, pairs=0x2000, **opt):
         """items: (hierarchy, eyes, s, capacity); (status, counts)."""

@@ -27,6 +27,7 @@ size_t limit = ~(size_t)0, used = 0;
 std::string log_text;
 hipError_t last_error = hipSuccess;
 bool fail_device_sync = false;
+float spread = 1.0f;
 long new_countdown = -1;   // allocations until operator new fails once; < 0: never
 
 void note(const char* fmt, ...) {
@@ -60,6 +61,7 @@ EXPORT size_t host_used() { return used; }
 EXPORT size_t host_blocks() { return blocks.size(); }
 EXPORT void host_fail_device_sync(int on) { fail_device_sync = on != 0; }
 EXPORT void host_fail_new(long after) { new_countdown = after; }
+EXPORT void host_spread(float x) { spread = x; }   // of the hierarchies built from now on
 EXPORT int host_last_error() { return (int)last_error; }
 EXPORT size_t host_log(char* dst, size_t cap) {   // and clears it
     std::lock_guard<std::mutex> g(mu);
@@ -166,9 +168,10 @@ hipError_t hrr_launch_rmq(const uint32_t*, const uint32_t*, const uint32_t*, uin
                           unsigned long long*, int, hipStream_t) {
     return hipSuccess;
 }
-hipError_t hrr_launch_frontier(const Node*, uint32_t, uint32_t, float* table, hipStream_t) {
+hipError_t hrr_launch_frontier(const Node*, uint32_t, uint32_t, const float*, float* table, hipStream_t) {
     const uint32_t entries = 1;
-    memcpy(table + (size_t)kFrontierMax * kFrontierFloats, &entries, sizeof entries);
+    memcpy(table + kFrontierCount, &entries, sizeof entries);
+    table[kFrontierSpread] = spread;
     return hipSuccess;
 }
 hipError_t hrr_launch_blocks(const float*, uint32_t, float*, hipStream_t) { return hipSuccess; }

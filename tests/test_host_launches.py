@@ -102,17 +102,47 @@ def test_a_large_buffer_does_not_idle_the_gpu(ctx, n_lights, n_eyes):
     """Few eyes into a buffer far larger than their pairs: the output is dense
     where the eyes have at most 2^24 lights in all, and a chunked launch makes a
     hundred tasks or one per eye.  Allocation-free calls follow the same rule."""
-    import ctypes
     h = ctx.hierarchy(n_lights, leaf=8)
     ctx.log()
-    E, o = ctx.eyes(n_eyes), hrr._opts()
     assert ctx.traverse(h, n_eyes, 1 << 26) == hrr.HRR_OK
-    result = (ctypes.c_uint64 * 2)()
-    assert ctx.lib.hrr_traverse_noalloc(ctx.handle, h, ctypes.byref(E), 1e-4, ctypes.byref(o), 0x2000, None, 1 << 26,
-                                        ctypes.cast(result, ctypes.c_void_p), None) == hrr.HRR_OK
+    assert ctx.noalloc(h, n_eyes, 1 << 26) == hrr.HRR_OK
     lines = [_fields(x) for x in ctx.log() if x.startswith("blocks")]
     assert len(lines) == 2
     for f in lines:
         assert f["dense"] == (n_eyes * n_lights <= 1 << 24)
         assert f["tasks"] >= min(n_eyes, 100)
     ctx.free(h)
+
+
+@pytest.mark.parametrize("device", [False, True])
+def test_scattered_lights_take_the_node_walk(ctx, device):
+    """Lights whose order says little about their place: the node walk, where the
+    block walk is the slower one (node_walk_scattered)."""
+    cases = [  # spread, lights, eyes, buffer, node walk
+        (3.0, 1 << 18, 30000, 1 << 26, False), (3.0, 1 << 18, 30000, 1 << 20, False),
+        (255.0, 1 << 18, 30000, 1 << 26, False), (256.0, 1 << 18, 30000, 1 << 26, True),
+        (31.0, 4096, 30000, 1 << 26, False), (32.0, 4096, 30000, 1 << 26, True), (32.0, 4096, 3000, 1 << 26, False),
+        (32.0, 4095, 30000, 1 << 26, False), (2047.0, 1 << 18, 1 << 17, 1 << 26, False),
+        (2048.0, 1 << 18, 1 << 17, 1 << 26, True), (2048.0, 1 << 18, 1 << 17, 1 << 20, True),
+        (1e4, 5000, 1 << 20, 1 << 20, False), (1e4, 1 << 18, 3000, 1 << 20, False), (1e4, 1 << 18, 6000, 1 << 20, True),
+        (1e4, 1 << 18, 6000, 0, True), (511.0, 1 << 18, 300000, 1 << 20, False), (512.0, 1 << 18, 300000, 1 << 20, True),
+        (1000.0, 1 << 18, 23999, 1 << 20, False), (1000.0, 1 << 18, 24000, 1 << 20, True),
+        (float("nan"), 1 << 18, 300000, 1 << 20, False)]
+    hs = {}
+    for spread, n_l, n_e, cap, nodes in cases:
+        key = (spread, n_l)
+        if key not in hs:
+            ctx.lib.host_spread(spread)
+            hs[key] = ctx.hierarchy(n_l, leaf=8, device=device)
+            ctx.log()
+        st = [ctx.traverse(hs[key], n_e, cap), ctx.noalloc(hs[key], n_e, cap)]
+        assert all(q in (hrr.HRR_OK, hrr.HRR_E_OVERFLOW) for q in st)
+        walks = [x.split()[0] for x in ctx.log() if "tasks=" in x]
+        assert walks == ["nodes" if nodes else "blocks"] * 2, (spread, n_l, n_e, cap)
+    # in a batch the two walks' items are launched side by side
+    a, b = hs[(3.0, 1 << 18)], hs[(1e4, 1 << 18)]
+    assert ctx.batched([(a, 3000, 1e-4, 1 << 20), (b, 6000, 1e-4, 1 << 20), (a, 10, 1e-4, 100)])[0] == hrr.HRR_OK
+    assert [(x.split()[0], _fields(x)["items"]) for x in ctx.log() if "tasks=" in x] == [("blocks", 2), ("nodes", 1)]
+    ctx.lib.host_spread(1.0)
+    for h in hs.values():
+        ctx.free(h)
