@@ -492,31 +492,36 @@ HRR_EXPORT hrr_status hrr_hierarchy_get_info(const hrr_hierarchy* h, hrr_hierarc
 
 HRR_EXPORT hrr_status hrr_hierarchy_permutation(const hrr_hierarchy* h, uint32_t* perm_out) {
     if (!h || (!perm_out && h->n_lights)) return fail(HRR_E_INVALID, "hrr_hierarchy_permutation: null argument");
-    if (!h->n_lights) return HRR_OK;
-    const size_t bytes = h->n_lights * sizeof(uint32_t);
-    if (h->host_copies) {
-        memcpy(perm_out, h->perm.data(), bytes);
+    const size_t n = h->n_lights;
+    if (!n) return HRR_OK;
+    if (h->perm.size() != n) {
+        hipError_t e = hipSetDevice(h->owner->device);
+        if (e == hipSuccess) e = hipMemcpy(perm_out, h->d_perm, n * sizeof(uint32_t), hipMemcpyDeviceToHost);
+        if (e != hipSuccess) return hip_fail(e, "hierarchy download");
+        if (h->perm_read) h->perm.assign(perm_out, perm_out + n);
+        h->perm_read = true;
         return HRR_OK;
     }
-    hipError_t e = hipSetDevice(h->owner->device);
-    if (e == hipSuccess) e = hipMemcpy(perm_out, h->d_perm, bytes, hipMemcpyDeviceToHost);
-    return e == hipSuccess ? HRR_OK : hip_fail(e, "hierarchy download");
+    memcpy(perm_out, h->perm.data(), n * sizeof(uint32_t));
+    return HRR_OK;
 }
 
 HRR_EXPORT hrr_status hrr_hierarchy_sorted_lights(const hrr_hierarchy* h, float* sorted_xyz_out) {
     if (!h || (!sorted_xyz_out && h->n_lights)) return fail(HRR_E_INVALID, "hrr_hierarchy_sorted_lights: null argument");
     const size_t n = h->n_lights;
     if (!n) return HRR_OK;
-    if (h->host_copies) {
-        memcpy(sorted_xyz_out, h->sorted_xyz.data(), 3 * n * sizeof(float));
+    if (h->sorted_xyz.size() != 3 * n) {
+        hipError_t e = hipSetDevice(h->owner->device);
+        std::vector<float> l4(4 * n);
+        if (e == hipSuccess) e = hipMemcpy(l4.data(), h->d_lights, 4 * n * sizeof(float), hipMemcpyDeviceToHost);
+        if (e != hipSuccess) return hip_fail(e, "hierarchy download");
+        for (size_t i = 0; i < n; ++i)
+            for (int k = 0; k < 3; ++k) sorted_xyz_out[3 * i + k] = l4[4 * i + k];
+        if (h->sorted_read) h->sorted_xyz.assign(sorted_xyz_out, sorted_xyz_out + 3 * n);
+        h->sorted_read = true;
         return HRR_OK;
     }
-    hipError_t e = hipSetDevice(h->owner->device);
-    std::vector<float> l4(4 * n);
-    if (e == hipSuccess) e = hipMemcpy(l4.data(), h->d_lights, 4 * n * sizeof(float), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return hip_fail(e, "hierarchy download");
-    for (size_t i = 0; i < n; ++i)
-        for (int k = 0; k < 3; ++k) sorted_xyz_out[3 * i + k] = l4[4 * i + k];
+    memcpy(sorted_xyz_out, h->sorted_xyz.data(), 3 * n * sizeof(float));
     return HRR_OK;
 }
 

@@ -92,7 +92,6 @@ HRR_EXPORT hrr_status hrr_build_hierarchy_device(hrr_ctx* ctx, const float* ligh
     h->n_lights = n;
     h->leaf_size = leaf_size;
     h->split = split;
-    h->host_copies = false;
     struct Release {   // of a scratch too large to keep, on every path
         DevBuf& b;
         ~Release() {

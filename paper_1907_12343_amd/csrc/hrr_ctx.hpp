@@ -26,10 +26,12 @@ struct hrr_hierarchy {
     void* d_base = nullptr;           // device build: the one allocation of every table but d_nodes
     float* d_lights = nullptr;       // float4 per light
     uint32_t* d_perm = nullptr;
-    // host copies (hierarchies built on the host; the others read the device's)
-    std::vector<uint32_t> perm;
-    std::vector<float> sorted_xyz;
-    bool host_copies = true;
+    // host copies: of hierarchies built on the host, and of what has been read
+    // twice from one built on the device (reading once, as most programs do, need
+    // not fill a copy)
+    mutable std::vector<uint32_t> perm;
+    mutable std::vector<float> sorted_xyz;
+    mutable bool perm_read = false, sorted_read = false;
     uint64_t device_bytes = 0;
 };
 

@@ -1,6 +1,7 @@
 """What the host side of a call launches and refuses, on a replaced HIP runtime."""
 import re
 
+import numpy as np
 import pytest
 
 import paper_1907_12343_amd as hrr
@@ -146,3 +147,20 @@ def test_scattered_lights_take_the_node_walk(ctx, device):
     ctx.lib.host_spread(1.0)
     for h in hs.values():
         ctx.free(h)
+
+
+@pytest.mark.parametrize("device", [False, True])
+def test_repeated_readbacks_need_no_device_copy(ctx, device):
+    """A program that asks for the light order again and again is served from a
+    host copy: one built on the device is read twice at the most."""
+    n = 5000
+    h = ctx.hierarchy(n, device=device)
+    ctx.log()
+    for call, shape, dtype, size in ((ctx.lib.hrr_hierarchy_permutation, n, np.uint32, 4 * n),
+                                     (ctx.lib.hrr_hierarchy_sorted_lights, 3 * n, np.float32, 16 * n)):
+        outs = [np.zeros(shape, dtype) for _ in range(5)]
+        for out in outs:
+            assert call(h, out.ctypes.data) == hrr.HRR_OK
+        assert all(np.array_equal(out, outs[0]) for out in outs) and len(np.unique(outs[0])) > n // 2
+        assert ctx.log() == (["read %d" % size] * 2 if device else [])
+    ctx.free(h)
