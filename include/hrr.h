@@ -178,7 +178,8 @@ hrr_status hrr_build_hierarchy(hrr_ctx* ctx, const float* lights_xyz,
  * a stable radix sort, then every node from its split position.  Work is
  * ordered on `stream`; the call returns when the hierarchy is complete.  The
  * context keeps the build's scratch and the memory of freed hierarchies for
- * later builds, at most 512 MiB of each.  Non-finite coordinates return HRR_E_INVALID. */
+ * later builds, at most 512 MiB of each, until it is destroyed or another of its
+ * allocations finds no room.  Non-finite coordinates return HRR_E_INVALID. */
 hrr_status hrr_build_hierarchy_device(hrr_ctx* ctx, const float* lights_xyz_dev,
                                       uint32_t n_lights, uint32_t leaf_size,
                                       const float* box, void* stream, hrr_hierarchy** out);

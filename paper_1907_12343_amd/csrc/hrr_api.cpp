@@ -57,7 +57,25 @@ hrr_status hip_fail(hipError_t e, const char* what) {
 
 int ilog2_floor(uint64_t x) { return x ? 63 - __builtin_clzll(x) : 0; }
 
-hipError_t DevBuf::ensure(size_t want) {
+hipError_t device_alloc(hrr_ctx* ctx, void** p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        ctx->blocks.release();
+        {
+            std::lock_guard<std::mutex> g(ctx->build_mu);
+            if (!ctx->building) ctx->build_scratch.release();
+        }
+        e = hipMalloc(p, bytes);
+    }
+    if (e != hipSuccess) {
+        *p = nullptr;
+        (void)hipGetLastError();   // reported by the caller, not by its next launch
+    }
+    return e;
+}
+
+hipError_t DevBuf::ensure(hrr_ctx* ctx, size_t want) {
     if (want <= bytes) return hipSuccess;
     if (p) {
         hipError_t e = hipFree(p);
@@ -66,13 +84,9 @@ hipError_t DevBuf::ensure(size_t want) {
         if (e != hipSuccess) return e;
     }
     size_t sz = std::max<size_t>(want, 256);
-    hipError_t e = hipMalloc(&p, sz);
-    if (e != hipSuccess) {
-        p = nullptr;
-        return e;
-    }
-    bytes = sz;
-    return hipSuccess;
+    hipError_t e = device_alloc(ctx, &p, sz);
+    if (e == hipSuccess) bytes = sz;
+    return e;
 }
 
 void DevBuf::release() {
@@ -395,7 +409,7 @@ namespace hrr {
 hrr_status attach_frontier(hrr_hierarchy* h, hipStream_t stream) {
     if (!h->n_nodes) return HRR_OK;
     const size_t fb = kFrontierWords * sizeof(float);
-    hipError_t e = hipMalloc((void**)&h->d_frontier, fb);
+    hipError_t e = device_alloc(h->owner, (void**)&h->d_frontier, fb);
     if (e == hipSuccess) e = hrr_launch_frontier(h->d_nodes, h->n_lights, h->leaf_size, h->d_blocks, h->d_frontier, stream);
     if (e != hipSuccess) return hip_fail(e, "hierarchy top");
     h->device_bytes += fb;
@@ -405,7 +419,7 @@ hrr_status attach_frontier(hrr_hierarchy* h, hipStream_t stream) {
 hrr_status attach_blocks(hrr_hierarchy* h, hipStream_t stream) {
     if (!h->n_lights) return HRR_OK;
     const size_t bytes = block_tree_floats(h->n_lights) * sizeof(float);
-    hipError_t e = hipMalloc((void**)&h->d_blocks, bytes);
+    hipError_t e = device_alloc(h->owner, (void**)&h->d_blocks, bytes);
     if (e == hipSuccess) e = hrr_launch_blocks(h->d_lights, h->n_lights, h->d_blocks, stream);
     if (e != hipSuccess) return hip_fail(e, "block tree");
     h->device_bytes += bytes;
@@ -447,8 +461,9 @@ HRR_EXPORT hrr_status hrr_build_hierarchy(hrr_ctx* ctx, const float* lights_xyz,
     std::vector<float> l4(4 * (size_t)n_lights, 0.0f);
     for (size_t i = 0; i < n_lights; ++i)
         for (int k = 0; k < 3; ++k) l4[4 * i + k] = H.sorted_xyz[3 * i + k];
-    if ((e = hipMalloc((void**)&h->d_nodes, nb)) != hipSuccess || (e = hipMalloc((void**)&h->d_lights, lb)) != hipSuccess ||
-        (e = hipMalloc((void**)&h->d_perm, pb)) != hipSuccess) {
+    if ((e = device_alloc(ctx, (void**)&h->d_nodes, nb)) != hipSuccess ||
+        (e = device_alloc(ctx, (void**)&h->d_lights, lb)) != hipSuccess ||
+        (e = device_alloc(ctx, (void**)&h->d_perm, pb)) != hipSuccess) {
         hrr_free_hierarchy(ctx, h);
         return hip_fail(e, "hierarchy allocation");
     }
@@ -721,7 +736,7 @@ HRR_EXPORT hrr_status hrr_autotune(hrr_ctx* ctx, const hrr_hierarchy* const* hs,
             result = r;
             break;
         }
-        if ((e = out.ensure(std::max<uint64_t>(cnt, 1) * 8)) != hipSuccess) {
+        if ((e = out.ensure(ctx, std::max<uint64_t>(cnt, 1) * 8)) != hipSuccess) {
             result = hip_fail(e, "tuner output");
             break;
         }
@@ -812,7 +827,7 @@ HRR_EXPORT hrr_status hrr_autotune_batched(hrr_ctx* ctx, const hrr_work_item* se
             items[k].out_capacity = cnt[k];
             total += cnt[k];
         }
-        if ((e = out.ensure(std::max<uint64_t>(total, 1) * 8)) != hipSuccess) {
+        if ((e = out.ensure(ctx, std::max<uint64_t>(total, 1) * 8)) != hipSuccess) {
             result = hip_fail(e, "tuner output");
             break;
         }

@@ -92,12 +92,18 @@ HRR_EXPORT hrr_status hrr_build_hierarchy_device(hrr_ctx* ctx, const float* ligh
     h->n_lights = n;
     h->leaf_size = leaf_size;
     h->split = split;
-    struct Release {   // of a scratch too large to keep, on every path
-        DevBuf& b;
-        ~Release() {
-            if (b.bytes > kKeepScratch) b.release();
+    struct Building {   // the scratch is in use; one too large to keep is released, on every path
+        hrr_ctx* c;
+        explicit Building(hrr_ctx* ctx) : c(ctx) {
+            std::lock_guard<std::mutex> g(c->build_mu);
+            c->building = true;
         }
-    } release{ctx->build_scratch};
+        ~Building() {
+            std::lock_guard<std::mutex> g(c->build_mu);
+            c->building = false;
+            if (c->build_scratch.bytes > kKeepScratch) c->build_scratch.release();
+        }
+    } building(ctx);
     auto fail_free = [&](hrr_status st) {
         (void)hipStreamSynchronize(stream);   // the scratch is the context's
         hrr_free_hierarchy(ctx, h);
@@ -114,7 +120,7 @@ HRR_EXPORT hrr_status hrr_build_hierarchy_device(hrr_ctx* ctx, const float* ligh
         return fail_free(hip_fail(e, "sort size"));
     Carver size{nullptr};
     (void)Scratch(size, n, sort_bytes);
-    if ((e = ctx->build_scratch.ensure(size.at)) != hipSuccess) return fail_free(hip_fail(e, "build scratch"));
+    if ((e = ctx->build_scratch.ensure(ctx, size.at)) != hipSuccess) return fail_free(hip_fail(e, "build scratch"));
     Carver carve{static_cast<unsigned char*>(ctx->build_scratch.p)};
     const Scratch T(carve, n, sort_bytes);
     const size_t n_block_floats = n ? block_tree_floats(n) : 0;

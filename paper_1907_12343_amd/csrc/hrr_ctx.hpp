@@ -37,18 +37,24 @@ struct hrr_hierarchy {
 
 namespace hrr {
 
+// hipMalloc for `ctx`.  When the device has no room, the memory that the context
+// keeps for later builds is given back first (freed hierarchies' blocks, and the
+// build scratch unless a build is running) and the allocation tried once more.
+// Safe from the server's workers while another thread builds.
+hipError_t device_alloc(hrr_ctx* ctx, void** p, size_t bytes);
+
 // Device buffer that only grows.
 struct DevBuf {
     void* p = nullptr;
     size_t bytes = 0;
-    hipError_t ensure(size_t want);
+    hipError_t ensure(hrr_ctx* ctx, size_t want);
     void release();
 };
 
 // Device blocks of freed hierarchies, for the next builds of about their size
 // (hipMalloc and hipFree of a 2^20-light hierarchy's two blocks cost 0.4 ms, a
 // third of its build).  At most kBlockCacheBytes; given back with the context, or
-// when the device runs out of memory.  A block enters only once the device is
+// when one of its allocations finds no room.  A block enters only once the device is
 // idle, as hipFree itself would wait, so no work still reads it.
 constexpr size_t kBlockCacheBytes = (size_t)512 << 20;
 struct BlockCache {
@@ -136,6 +142,8 @@ struct hrr_ctx {
     std::mutex server_mu;
     hrr::BlockCache blocks;              // of device-built hierarchies
     hrr::DevBuf build_scratch;           // of device builds, kept between them up to a bound
+    std::mutex build_mu;                 // guards `building`, and build_scratch while it is false
+    bool building = false;
     uint32_t* build_pin = nullptr;       // pinned readback words of device builds
     void* noalloc_scratch = nullptr;   // this device's scratch of hrr_traverse_noalloc
 };

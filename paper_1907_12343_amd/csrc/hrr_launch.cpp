@@ -182,9 +182,9 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
                 o.scale[q] = ext > 0.0f ? (float)(1u << bits) / ext : 0.0f;
             }
         }
-        if ((e = S.order_keys.ensure(vtotal * sizeof(uint32_t))) != hipSuccess) return hip_fail(e, "order keys");
-        if ((e = S.order_idx.ensure(vtotal * sizeof(uint32_t))) != hipSuccess) return hip_fail(e, "eye order");
-        if ((e = S.order_hist.ensure((((size_t)n << (3 * bits + rbits)) + 1024) * sizeof(uint32_t))) != hipSuccess)
+        if ((e = S.order_keys.ensure(ctx, vtotal * sizeof(uint32_t))) != hipSuccess) return hip_fail(e, "order keys");
+        if ((e = S.order_idx.ensure(ctx, vtotal * sizeof(uint32_t))) != hipSuccess) return hip_fail(e, "eye order");
+        if ((e = S.order_hist.ensure(ctx, (((size_t)n << (3 * bits + rbits)) + 1024) * sizeof(uint32_t))) != hipSuccess)
             return hip_fail(e, "order histogram");
     }
 
@@ -199,15 +199,15 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
     const size_t oi_at = (tasks_at + (n + 1) * sizeof(uint32_t) + 7) / 8 * 8;
     const size_t vb_at = oi_at + (ordered ? n * sizeof(OrderItem) : 0);
     const size_t table_bytes = vb_at + (ordered ? (n + 1) * sizeof(uint32_t) : 0);
-    if ((e = S.tables.ensure(table_bytes)) != hipSuccess) return hip_fail(e, "launch tables");
+    if ((e = S.tables.ensure(ctx, table_bytes)) != hipSuccess) return hip_fail(e, "launch tables");
     unsigned char* const d_tables = static_cast<unsigned char*>(S.tables.p);
-    if ((e = S.partials.ensure(std::max<unsigned long long>(partial_total, 1) * 2 * sizeof(unsigned long long))) != hipSuccess)
+    if ((e = S.partials.ensure(ctx, std::max<unsigned long long>(partial_total, 1) * 2 * sizeof(unsigned long long))) != hipSuccess)
         return hip_fail(e, "partial-chunk list");
-    if ((e = S.plan.ensure(std::max<unsigned long long>(plan_total, 1) * sizeof(unsigned long long))) != hipSuccess)
+    if ((e = S.plan.ensure(ctx, std::max<unsigned long long>(plan_total, 1) * sizeof(unsigned long long))) != hipSuccess)
         return hip_fail(e, "compaction plan");
-    if ((e = S.slack_pairs.ensure(std::max<unsigned long long>(slack_total, 1) * 2 * sizeof(uint32_t))) != hipSuccess)
+    if ((e = S.slack_pairs.ensure(ctx, std::max<unsigned long long>(slack_total, 1) * 2 * sizeof(uint32_t))) != hipSuccess)
         return hip_fail(e, "output slack");
-    if (with_w && (e = S.slack_weights.ensure(std::max<unsigned long long>(slack_total, 1) * sizeof(float))) != hipSuccess)
+    if (with_w && (e = S.slack_weights.ensure(ctx, std::max<unsigned long long>(slack_total, 1) * sizeof(float))) != hipSuccess)
         return hip_fail(e, "weight slack");
     unsigned long long* d_counters = reinterpret_cast<unsigned long long*>(d_tables);
     unsigned long long* d_misc = d_counters + n * CNT_STRIDE;
@@ -339,7 +339,7 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
         const uint64_t bound = 128ull * (dmax + 2);
         const uint32_t spill_cap = (uint32_t)(((bound + 63) / 64) * 64 + 64);
         const size_t spill_bytes = (size_t)waves * spill_cap * sizeof(unsigned long long);
-        if (!shape.blocks && (e = S.spill.ensure(spill_bytes)) != hipSuccess) return hip_fail(e, "spill stacks");
+        if (!shape.blocks && (e = S.spill.ensure(ctx, spill_bytes)) != hipSuccess) return hip_fail(e, "spill stacks");
 
         TravArgs A;
         memset(&A, 0, sizeof A);

@@ -396,7 +396,7 @@ HRR_EXPORT hrr_status hrr_server_start(hrr_ctx* ctx, const hrr_server_config* cf
     sv->ctx = ctx;
     sv->cfg = *cfg;
     const uint64_t budget = cfg->hbm_budget_bytes / kAlign * kAlign;
-    if ((e = hipMalloc((void**)&sv->base, budget)) != hipSuccess) {
+    if ((e = device_alloc(ctx, (void**)&sv->base, budget)) != hipSuccess) {
         delete sv;
         return hip_fail(e, "server arena");
     }

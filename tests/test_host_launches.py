@@ -164,3 +164,43 @@ def test_repeated_readbacks_need_no_device_copy(ctx, device):
         assert all(np.array_equal(out, outs[0]) for out in outs) and len(np.unique(outs[0])) > n // 2
         assert ctx.log() == (["read %d" % size] * 2 if device else [])
     ctx.free(h)
+
+
+def _server(ctx, budget):
+    import ctypes
+    cfg = hrr.HrrServerConfig(budget, 1, 1 << 16, 64, 0, 64.0, 100.0)
+    return ctx.lib.hrr_server_start(ctx.handle, ctypes.byref(cfg))
+
+
+@pytest.mark.parametrize("what", ["traverse", "host build", "device build", "server"])
+def test_kept_memory_is_given_back_when_room_is_short(ctx, what):
+    """Blocks of freed hierarchies and the build scratch, which a context keeps for
+    later builds, are no reason to refuse any other allocation."""
+    lib = ctx.lib
+    h = ctx.hierarchy(1000)
+    before = lib.host_used()
+    for g in [ctx.hierarchy(1 << 18) for _ in range(4)]:
+        ctx.free(g)
+    kept = lib.host_used() - before
+    assert kept > 50 << 20
+    lib.host_limit(before + kept + (1 << 20))             # room for 1 MiB beside what is kept
+    try:
+        if what == "traverse":
+            st = ctx.traverse(h, 30000, 3 << 23)           # its chunks need tens of MiB of slack
+        elif what == "host build":
+            st, g = ctx.build(1 << 18, device=False, leaf=8)
+        elif what == "device build":
+            st, g = ctx.build(1 << 19)                      # outgrows every kept block
+        else:
+            st = _server(ctx, 40 << 20)
+        assert st == hrr.HRR_OK, ctx.error()
+        # what does not fit even so is refused, and the next call is not
+        assert _server(ctx, 1 << 40) in (hrr.HRR_E_NOMEM, hrr.HRR_E_BUSY)
+        assert ctx.traverse(h, 10, 100) == hrr.HRR_OK
+    finally:
+        lib.host_limit(2 ** 64 - 1)
+    assert lib.host_last_error() == 0
+    lib.hrr_server_stop(ctx.handle)
+    if what.endswith("build"):
+        ctx.free(g)
+    ctx.free(h)
