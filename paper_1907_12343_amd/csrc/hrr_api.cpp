@@ -95,8 +95,8 @@ void DevBuf::release() {
     bytes = 0;
 }
 
-hipError_t BlockCache::get(void** p, size_t bytes) {
-    *p = nullptr;
+hipError_t BlockCache::get(Entry* block, size_t bytes) {
+    *block = Entry();
     bytes = std::max<size_t>(bytes, 256);
     std::lock_guard<std::mutex> g(mu);
     size_t best = idle.size();
@@ -104,37 +104,48 @@ hipError_t BlockCache::get(void** p, size_t bytes) {
         if (idle[q].bytes >= bytes && idle[q].bytes / 2 <= bytes && (best == idle.size() || idle[q].bytes < idle[best].bytes))
             best = q;
     if (best < idle.size()) {
-        *p = idle[best].p;
-        live[*p] = idle[best].bytes;
-        idle_bytes -= idle[best].bytes;
+        *block = idle[best];
+        idle_bytes -= block->bytes;
         idle.erase(idle.begin() + best);
         return hipSuccess;
     }
-    hipError_t e = hipMalloc(p, bytes);
+    hipError_t e = hipMalloc(&block->p, bytes);
     if (e == hipErrorOutOfMemory && !idle.empty()) {
         for (auto& x : idle) (void)hipFree(x.p);
         idle.clear();
         idle_bytes = 0;
         (void)hipGetLastError();
-        e = hipMalloc(p, bytes);
+        e = hipMalloc(&block->p, bytes);
     }
-    if (e == hipSuccess) live[*p] = bytes;
-    else *p = nullptr;
+    if (e == hipSuccess) {
+        block->bytes = bytes;
+    } else {
+        block->p = nullptr;
+        (void)hipGetLastError();   // reported by the caller, not by its next launch
+    }
     return e;
 }
 
-void BlockCache::put(void* p) {
-    if (!p) return;
+void BlockCache::put(Entry block) noexcept {
+    if (!block.p) return;
     std::lock_guard<std::mutex> g(mu);
-    auto it = live.find(p);
-    const size_t bytes = it == live.end() ? 0 : it->second;
-    if (it != live.end()) live.erase(it);
-    if (bytes == 0 || bytes > kBlockCacheBytes / 2 || hipDeviceSynchronize() != hipSuccess) {
-        (void)hipFree(p);
+    bool keep = block.bytes <= kBlockCacheBytes / 2;
+    if (keep && hipDeviceSynchronize() != hipSuccess) {   // as while a stream is being captured
+        (void)hipGetLastError();
+        keep = false;
+    }
+    if (keep) {
+        try {
+            idle.push_back(block);
+        } catch (...) {
+            keep = false;
+        }
+    }
+    if (!keep) {
+        (void)hipFree(block.p);
         return;
     }
-    idle.push_back({p, bytes});
-    idle_bytes += bytes;
+    idle_bytes += block.bytes;
     while (idle_bytes > kBlockCacheBytes) {
         (void)hipFree(idle.front().p);
         idle_bytes -= idle.front().bytes;
@@ -552,14 +563,13 @@ HRR_EXPORT hrr_status hrr_hierarchy_records(const hrr_hierarchy* h, void* nodes_
 HRR_EXPORT void hrr_free_hierarchy(hrr_ctx* ctx, hrr_hierarchy* h) {
     if (!h) return;
     if (ctx) (void)hipSetDevice(ctx->device);
-    if (h->d_base) {   // one allocation, with the records inside it or beside it
-        void* const records = h->n_nodes ? h->d_nodes : nullptr;
-        if (ctx) {
-            ctx->blocks.put(records);
-            ctx->blocks.put(h->d_base);
+    if (h->base.p) {   // one allocation, with the records inside it or beside it
+        if (ctx && ctx == h->owner) {
+            ctx->blocks.put(h->records);
+            ctx->blocks.put(h->base);
         } else {
-            if (records) (void)hipFree(records);
-            (void)hipFree(h->d_base);
+            if (h->records.p) (void)hipFree(h->records.p);
+            (void)hipFree(h->base.p);
         }
     } else {
         if (h->d_nodes) (void)hipFree(h->d_nodes);

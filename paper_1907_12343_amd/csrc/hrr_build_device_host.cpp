@@ -136,8 +136,8 @@ HRR_EXPORT hrr_status hrr_build_hierarchy_device(hrr_ctx* ctx, const float* ligh
     };
     Carver need{nullptr};
     tables(need);
-    if ((e = ctx->blocks.get(&h->d_base, need.at)) != hipSuccess) return fail_free(hip_fail(e, "hierarchy allocation"));
-    Carver own{static_cast<unsigned char*>(h->d_base)};
+    if ((e = ctx->blocks.get(&h->base, need.at)) != hipSuccess) return fail_free(hip_fail(e, "hierarchy allocation"));
+    Carver own{static_cast<unsigned char*>(h->base.p)};
     tables(own);
     h->device_bytes = need.at;
 
@@ -173,8 +173,9 @@ HRR_EXPORT hrr_status hrr_build_hierarchy_device(hrr_ctx* ctx, const float* ligh
         if (pin[0] > max_internal) return fail_free(fail(HRR_E_DEVICE, "device build: record count overflow"));
         const uint32_t n_records = 2u * (1u + pin[0]);
         h->depth = pin[1];
-        if ((e = ctx->blocks.get((void**)&h->d_nodes, (size_t)n_records * sizeof(Node))) != hipSuccess)
+        if ((e = ctx->blocks.get(&h->records, (size_t)n_records * sizeof(Node))) != hipSuccess)
             return fail_free(hip_fail(e, "node records"));
+        h->d_nodes = static_cast<Node*>(h->records.p);
         h->n_nodes = n_records;
         h->device_bytes += (size_t)n_records * sizeof(Node);
         if ((e = hipMemsetAsync(h->d_nodes, 0, (size_t)n_records * sizeof(Node), stream)) != hipSuccess ||

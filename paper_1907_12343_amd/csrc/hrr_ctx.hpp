@@ -13,28 +13,6 @@
 #include "hrr_build.hpp"
 #include "hrr_types.hpp"
 
-struct hrr_hierarchy {
-    hrr_ctx* owner = nullptr;
-    uint32_t n_lights = 0, leaf_size = 1, n_nodes = 0, depth = 0;
-    uint32_t split = HRR_SPLIT_RADIX;
-    float box[6] = {0, 0, 0, 0, 0, 0};
-    hrr::Node* d_nodes = nullptr;
-    float* d_frontier = nullptr;      // kFrontierMax entries of kFrontierFloats, then their number and the spread
-    uint32_t n_frontier = 0;
-    float spread = 0.0f;              // of the block tree (hrr_types.hpp)
-    float* d_blocks = nullptr;        // block tree (hrr_types.hpp), for n_lights > 0
-    void* d_base = nullptr;           // device build: the one allocation of every table but d_nodes
-    float* d_lights = nullptr;       // float4 per light
-    uint32_t* d_perm = nullptr;
-    // host copies: of hierarchies built on the host, and of what has been read
-    // twice from one built on the device (reading once, as most programs do, need
-    // not fill a copy)
-    mutable std::vector<uint32_t> perm;
-    mutable std::vector<float> sorted_xyz;
-    mutable bool perm_read = false, sorted_read = false;
-    uint64_t device_bytes = 0;
-};
-
 namespace hrr {
 
 // hipMalloc for `ctx`.  When the device has no room, the memory that the context
@@ -59,17 +37,42 @@ struct DevBuf {
 constexpr size_t kBlockCacheBytes = (size_t)512 << 20;
 struct BlockCache {
     struct Entry {
-        void* p;
-        size_t bytes;
+        void* p = nullptr;
+        size_t bytes = 0;
     };
     std::mutex mu;
     std::vector<Entry> idle;                 // oldest first
-    std::map<void*, size_t> live;            // blocks handed out
     size_t idle_bytes = 0;
-    hipError_t get(void** p, size_t bytes);  // at least `bytes`
-    void put(void* p);                       // a block from get(), or null
+    hipError_t get(Entry* block, size_t bytes);   // at least `bytes`; {null, 0} on failure
+    void put(Entry block) noexcept;          // a block from get(), or {null, 0}
     void release();                          // every idle block
 };
+
+}  // namespace hrr
+
+struct hrr_hierarchy {
+    hrr_ctx* owner = nullptr;
+    uint32_t n_lights = 0, leaf_size = 1, n_nodes = 0, depth = 0;
+    uint32_t split = HRR_SPLIT_RADIX;
+    float box[6] = {0, 0, 0, 0, 0, 0};
+    hrr::Node* d_nodes = nullptr;
+    float* d_frontier = nullptr;      // kFrontierMax entries of kFrontierFloats, then their number and the spread
+    uint32_t n_frontier = 0;
+    float spread = 0.0f;              // of the block tree (hrr_types.hpp)
+    float* d_blocks = nullptr;        // block tree (hrr_types.hpp), for n_lights > 0
+    hrr::BlockCache::Entry base, records;   // device build: the allocation of every table but the records, and theirs
+    float* d_lights = nullptr;       // float4 per light
+    uint32_t* d_perm = nullptr;
+    // host copies: of hierarchies built on the host, and of what has been read
+    // twice from one built on the device (reading once, as most programs do, need
+    // not fill a copy)
+    mutable std::vector<uint32_t> perm;
+    mutable std::vector<float> sorted_xyz;
+    mutable bool perm_read = false, sorted_read = false;
+    uint64_t device_bytes = 0;
+};
+
+namespace hrr {
 
 struct TuneKey {
     int log_lights, log_eyes;

@@ -204,3 +204,36 @@ def test_kept_memory_is_given_back_when_room_is_short(ctx, what):
     if what.endswith("build"):
         ctx.free(g)
     ctx.free(h)
+
+
+def test_freeing_a_hierarchy_fails_quietly(ctx):
+    """hrr_free_hierarchy has no status: when the block cannot be kept (a stream is
+    being captured, host memory is out, another context frees it) it is freed, and
+    neither an exception nor an error is left behind."""
+    lib = ctx.lib
+    before = lib.host_used()
+    other = HostContext(lib)
+    base = lib.host_used()
+    for how in ("sync", "new", "other", "no context"):
+        h = ctx.hierarchy(5000)
+        if how == "sync":
+            lib.host_fail_device_sync(1)
+            ctx.free(h)
+            lib.host_fail_device_sync(0)
+        elif how == "new":
+            lib.host_fail_new(0)
+            ctx.free(h)
+            lib.host_fail_new(-1)
+        elif how == "other":
+            other.free(h)
+        else:
+            lib.hrr_free_hierarchy(None, h)
+        assert lib.host_last_error() == 0, how
+        g = ctx.hierarchy(5000)
+        assert ctx.traverse(g, 10, 100) == hrr.HRR_OK
+        ctx.free(g)
+    ctx.free(ctx.hierarchy(5000))
+    other.close()
+    ctx.close()
+    assert lib.host_used() <= before
+    ctx.handle = HostContext(lib).handle       # for the fixture to close
