@@ -96,6 +96,27 @@ HRR_HD unsigned long long prefix_rank(const unsigned long long* prefix, unsigned
     return lo;
 }
 
+// The same, for e < prefix[n], from a rank q whose prefix is at most e: looks at
+// prefix[q + 1], then twice as far each time, so that a run of empty entries
+// (the partly filled chunks past the target, most of them where a launch left
+// many waves few pairs) costs a few reads and not one each.
+template <typename Prefix>
+HRR_HD unsigned long long prefix_advance(const Prefix& prefix, unsigned long long n, unsigned long long q,
+                                         unsigned long long e) {
+    if (prefix[q + 1] > e) return q;
+    unsigned long long lo = q + 1, step = 1;
+    while (lo + step < n && prefix[lo + step] <= e) {
+        lo += step;
+        step *= 2;
+    }
+    unsigned long long hi = umin64(lo + step, n);   // prefix[lo] <= e < prefix[hi]
+    while (hi - lo > 1) {
+        const unsigned long long mid = lo + (hi - lo) / 2;
+        if (prefix[mid] <= e) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
 // Which moved elements a thread of compact_move_kernel handles.  Two
 // mappings over `threads` threads (a multiple of the 64-lane wave):
 //   run mode  (lanes = false): thread t takes the runs [t R, t R + R),

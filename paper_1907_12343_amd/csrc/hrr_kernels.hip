@@ -1862,7 +1862,10 @@ constexpr uint32_t kMoveRun = 16;   // moved elements per lane and step
 // so the 64 lanes of one access read and write whole cache lines (frame:
 // 258 -> 95 us).  With smaller chunks a lane stepping by kWave would cross a
 // hole boundary, a dependent load, almost every step; there each lane moves
-// its own run of kMoveRun consecutive elements instead.
+// its own run of kMoveRun consecutive elements instead.  A boundary may be
+// thousands of empty holes wide (300,000 eyes x 2^14 lights into 2^26 pairs,
+// 4.1e5 pairs in 8,192 chunks: 33 or 700 .. 1,100 us, by the order in which the
+// waves ended, with a read for each; 39 us with prefix_advance).
 __global__ __launch_bounds__(256) void compact_move_kernel(const ItemDesc* __restrict__ items) {
     const ItemDesc& D = items[blockIdx.y];
     const unsigned long long moved = D.counters[CNT_MOVED];
@@ -1884,8 +1887,8 @@ __global__ __launch_bounds__(256) void compact_move_kernel(const ItemDesc* __res
         unsigned long long i = prefix_rank(Ds, nd, e0);
         const unsigned long long e1 = move_run_end(mm, e0, moved);
         for (unsigned long long e = e0; e < e1; e += mm.stride) {
-            while (Hs[q + 1] <= e) ++q;
-            while (Ds[i + 1] <= e) ++i;
+            q = prefix_advance(Hs, g.P, q, e);
+            i = prefix_advance(Ds, nd, i, e);
             const unsigned long long dst = hole_lo(g, pl[2 * q], pl[2 * q + 1]) + (e - Hs[q]);
             const unsigned long long src = data_lo(g, i) + (e - Ds[i]);
             out[dst] = src < cap ? out[src] : sl[src - cap];
