@@ -146,15 +146,17 @@ struct LaunchSize {
 //   dense output: spread 1 .. 4 at least 2; 3,000 eyes 2.2 .. 5.5 at spread 2^8,
 //     0.94 .. 1.5 at 2^13 (2^18 lights), 0.71 at 2^15 (2^20); 30,000 eyes 1.03 ..
 //     2.5 at 2^8, 0.98 .. 1.4 at 2^9, 0.43 .. 1.3 from 2^10; below 2^16 lights
-//     and in small launches never under 1, as blocks that are cut among several
-//     waves make up for it;
+//     and in small launches hardly under 1, as blocks that are cut among several
+//     waves make up for it (5 items of 300 eyes, spread 2^15, 2^20 lights: 0.67);
 //   chunks: 3,000 .. 30,000 eyes 0.9 .. 1.8 at 2^6 and 2^7, 0.6 .. 1.8 at 2^8,
 //     0.17 .. 0.9 from 2^10, and 0.5 with 2^12 lights where an eye is in every
 //     second block; 300,000 eyes 0.9 .. 1.8 up to 2^10, 0.6 .. 0.9 from 2^11;
 //     below 2^12 lights at least 1.
 inline bool node_walk_scattered(float spread, uint32_t n_lights, const LaunchSize& size, bool dense) {
-    if (dense)
-        return n_lights >= (1u << 16) && size.cost >= 1e7 && spread >= 512.0f && (double)spread * (double)size.eyes >= 2.4e7;
+    if (dense) {
+        const double met = (double)spread * (double)size.eyes;   // blocks that the launch's eyes stand in
+        return n_lights >= (1u << 16) && spread >= 512.0f && (met >= 6e7 || (met >= 2.4e7 && size.cost >= 1e7));
+    }
     const uint32_t n_blocks = block_tree_lights(n_lights) >> block_leaf_log(block_tree_log(n_lights));
     const float bound = size.eyes < (1u << 17) ? fminf(256.0f, (float)n_blocks / 8.0f) : 2048.0f;
     return n_lights >= (1u << 12) && spread >= bound;

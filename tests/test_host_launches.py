@@ -127,6 +127,7 @@ def test_scattered_lights_take_the_node_walk(ctx, device):
         (2048.0, 1 << 18, 1 << 17, 1 << 26, True), (2048.0, 1 << 18, 1 << 17, 1 << 20, True),
         (1e4, 5000, 1 << 20, 1 << 20, False), (1e4, 1 << 18, 3000, 1 << 20, False), (1e4, 1 << 18, 6000, 1 << 20, True),
         (1e4, 1 << 18, 6000, 0, True), (511.0, 1 << 18, 300000, 1 << 20, False), (512.0, 1 << 18, 300000, 1 << 20, True),
+        (1e4, 1 << 18, 5500, 1 << 20, False), (5e4, 1 << 18, 1199, 1 << 20, False), (5e4, 1 << 18, 1200, 1 << 20, True),
         (1000.0, 1 << 18, 23999, 1 << 20, False), (1000.0, 1 << 18, 24000, 1 << 20, True),
         (float("nan"), 1 << 18, 300000, 1 << 20, False)]
     hs = {}
