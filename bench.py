@@ -395,9 +395,11 @@ def batched_workload(args, steps=None, warmup=None):
     eyes, s = 1e-4) in ONE call (one persistent launch) against 256 plain launches of the same items on the
     same GPU.  Before timing, the batched autotuner runs once per light
     class (log2 of the light count) on all caches of the class together, over
-    leaf sizes 1, 2, 4, 8 and the launch shapes; every cache is built with
-    its class's leaf size.  The items of every tuned launch shape are also
-    measured with a call of their own."""
+    leaf sizes 1, 2, 4, 8 and the launch shapes of the node walk; every cache is
+    built with its class's leaf size.  The timed calls of the default method walk
+    index blocks, which have no shape and do not depend on the leaf size.  The
+    items whose classes the tuner gave one shape (a split by hierarchy size) are
+    also measured with a call of their own."""
     import numpy as np
     import torch
     import paper_1907_12343_amd as hrr

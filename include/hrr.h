@@ -110,7 +110,9 @@ int hrr_version(void);
                                  A traversal of this method walks aligned index blocks instead of
                                  the hierarchy's nodes where that is faster (same pairs): there a
                                  range minimum and the numbers that follow it are one subtraction
-                                 apart; HRR_F_STATS counts the node walk */
+                                 apart.  It walks nodes where s is outside [2^-60, 2^60], where the
+                                 lights' order says little about their place (a scene far from the
+                                 box of its build), and with HRR_F_STATS, which counts that walk */
 #define HRR_RMQ_DIRECT 1u     /* ablation: every step in O(1) bit arithmetic, no refinement walk */
 #define HRR_RMQ_PAPER_FULL 2u /* ablation: the sweeps as loops, refining every candidate in turn */
 #define HRR_RMQ_PAPER_LOOP 3u /* ablation: the sweeps as loops, refining only the candidate whose
@@ -290,11 +292,11 @@ hrr_status hrr_traverse(hrr_ctx* ctx, const hrr_hierarchy* h, const hrr_eyes* ey
  *     result_dev[0] > capacity).
  *   opts: as hrr_traverse; HRR_F_STATS and HRR_F_TIMING are rejected
  *     (HRR_E_INVALID), and eyes are processed in index order.
- * The grid is cut to as many whole blocks as the scratch holds.  The default
- * method needs little of it; methods that walk records (and s outside [2^-60,
- * 2^60]) need the stack spill area sized for the hierarchy's depth, about
- * 23 KB per wave at depth 20, and a hierarchy too deep for one block returns
- * HRR_E_INVALID.
+ * The grid is cut to as many whole blocks as the scratch holds.  The walk over
+ * index blocks needs little of it; the node walk (see HRR_RMQ_PAPER for where the
+ * default method takes it) needs the stack spill area sized for the hierarchy's
+ * depth, about 23 KB per wave at depth 20, and a hierarchy too deep for one
+ * block returns HRR_E_INVALID.
  * Output chunks hold at most 1024 pairs.  All calls on one GPU share its
  * scratch: calls that overlap in time on one GPU (several streams, several
  * threads) race and must be serialised by the caller. */
@@ -315,12 +317,16 @@ typedef struct hrr_work_item {
 
 /* Many independent (hierarchy, eye set) items in one persistent launch fed by
  * a device work queue; every item is the culling of hrr_traverse (Section 1,
- * as above) for its own eyes and hierarchy.  With opts->eyes_per_wave = 0 each item's shape is
+ * as above) for its own eyes and hierarchy.  The default method's items that walk
+ * index blocks are one launch, largest hierarchies first.  For the others, which
+ * walk nodes, with opts->eyes_per_wave = 0 each item's shape is
  * resolved on its own (tuned entry of its light class or a neighbouring one,
  * else 8 eyes per wave below 2^16 lights, 4 below 2^17, then 1) and the call
- * enqueues one such launch per group of equal shape on `stream`, largest
- * hierarchies first.  items: host array of at most 1024 items (HRR_E_INVALID
- * beyond).  counts_out (host u64[n_items])
+ * enqueues one launch per group of equal shape on `stream`, largest
+ * hierarchies first.  items: host array of at most 1024 items of one shape
+ * (HRR_E_INVALID beyond; 1024 in all with opts->eyes_per_wave set), whichever way
+ * they are walked.  Every item is checked before any is launched.  counts_out
+ * (host u64[n_items])
  * receives each item's true pair count; items whose count exceeds their
  * capacity store only the first out_capacity pairs and make the call return
  * HRR_E_OVERFLOW.  stats (optional) sums the work of all launches (max_stack:
@@ -395,7 +401,7 @@ uint32_t hrr_tuned_leaf_size(const hrr_ctx* ctx, uint32_t n_lights);
  * to max_batch_items requests and max_batch_eyes eyes, and as much arena as
  * is free; a request that does not fit is passed over by later ones that do
  * until it has waited overtake_ms) and run them as the items of one
- * persistent traversal launch per eyes-per-wave group (Section 1: every
+ * hrr_traverse_batched call (Section 1: every
  * request is the culling of its eye set against one hierarchy); while one
  * launch runs, newly arrived requests are batched into the next.  Each
  * request reserves output space from a running estimate of pairs per eye for
@@ -417,7 +423,8 @@ typedef struct hrr_server_config {
                                     limit near the typical request keeps large requests
                                     alone (2^16 for requests of 2^8..2^18 eyes) */
     uint32_t max_batch_items;    /* requests per launch, 1..1024 */
-    uint32_t eyes_per_wave;      /* 0 = tuned / default by hierarchy size; else 1, 2, 4 or 8 */
+    uint32_t eyes_per_wave;      /* of requests that walk nodes (see HRR_RMQ_PAPER): 0 = tuned / default by
+                                    hierarchy size; else 1, 2, 4 or 8 */
     float pairs_per_eye_guess;   /* output reservation per eye before any request on a
                                     hierarchy has finished (> 0; adapted online) */
     float overtake_ms;           /* a queued request that does not fit is skipped by later

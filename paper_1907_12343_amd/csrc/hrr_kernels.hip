@@ -1010,11 +1010,12 @@ void traverse_kernel(TravArgs A) {
 // counts the candidates that pass the bound, and only splits a block while
 // that bound is loose (many candidates would fail their own test); otherwise
 // it lists the candidates, and each is tested exactly like a one-light leaf.
-// On the 1920x1080 x 2^20 frame an eye's 2,305 accepted pairs take 1,512 box
-// tests and 3,930 candidate tests (simulated), where the node walk tests
-// 25,500 children, each with a range minimum: 4,500 vector instructions an eye
-// a wave, 19.3 ms a frame against 106.6.  What bounds it: the L1's line accesses
-// (9.8e9 a frame, 0.9 per CU-cycle; one per cycle is its rate), four fifths of
+// On the 1920x1080 x 2^20 frame an eye's 2,342 accepted pairs take 1,285 box
+// tests and 4,085 candidate tests (simulated for 3,001 of its eyes with the
+// split rule below), where the node walk tests 25,500 children, each with a range
+// minimum: 4,700 vector instructions an eye a wave, 20.1 ms a frame against
+// 101.7 .. 106.6.  What bounds it: the L1's line accesses
+// (1.0e10 a frame, 0.9 per CU-cycle; one per cycle is its rate), four fifths of
 // them candidates' lights, one line per lane where neighbouring lanes do not
 // share it; hence the eye order by shift class, and 16 eyes of that order to
 // a step (below).
@@ -1301,9 +1302,9 @@ __device__ __forceinline__ void cull_close(OutState& O, const ItemDesc* item, co
 // and takes exactly as many positions with one atomic, so the output is dense
 // as it is written and needs no chunks and no compaction; the last pairs of a
 // block's four waves share one atomic.  Same-address atomics are the cost (about
-// 15 ns each on this GPU): 512 staged pairs keep them below the compaction's
-// two launches up to about 2^21 pairs, and large outputs keep the chunks of
-// thousands of pairs.
+// 13 ns each on this GPU): 512 staged pairs keep them below the cost of chunks
+// and compaction up to about 2^24 pairs (block_walk_dense), and larger outputs
+// take the chunks of thousands of pairs.
 template <bool W, bool DENSE>
 __global__ __launch_bounds__(kWave * kWavesPerBlock)
 __attribute__((amdgpu_waves_per_eu(DENSE ? 1 : (W ? 7 : 8), 8)))
@@ -1439,8 +1440,8 @@ void cull_kernel(TravArgs A) {
             const uint32_t u = bit_reverse(p | tag) + __float_as_uint(e.w);
             const uint32_t m0 = __builtin_amdgcn_ubfe(u, 0u, rsh);   // the block's minimum
             uint32_t c = act && m0 <= T ? ((T - m0) >> rsh) + 1u : 0u;
-            // (a block that holds no light has v = 0 candidates at most, which
-            // lie past N)
+            // (a block that holds no light is infinitely far: T = 0 lists at most
+            // the one index whose random number is 0, which lies past N)
             const uint64_t wide = ballot(c > 1u) & ballot(v > leaf_log);
             uint64_t ms = 0;
             if (wide) {

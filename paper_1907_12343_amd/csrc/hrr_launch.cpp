@@ -94,6 +94,7 @@ hrr_status launch_items(hrr_ctx* ctx, LaunchScratch& S, const std::vector<HostIt
                      : hrr_traverse_occupancy(epw, method, stats, with_w,
                                               hrr_trav_lds_per_block((uint32_t)n, lds_wave), &bpc);
     if (e != hipSuccess) return hip_fail(e, "occupancy");
+    if (bpc <= 0 && shape.blocks) return fail(HRR_E_DEVICE, "the block walk does not fit in LDS");   // it has no stack size
     if (bpc <= 0) return fail(HRR_E_INVALID, "stack of %u entries does not fit in LDS", cap);
 
     std::vector<uint64_t> tasks_of(n);
@@ -431,6 +432,7 @@ hrr_status launch_noalloc(hrr_ctx* ctx, const hrr_hierarchy* h, const hrr_eyes& 
     e = block_walk ? hrr_cull_occupancy(with_w, dense, 1, &bpc)
                    : hrr_traverse_occupancy(epw, method, 0, with_w, hrr_trav_lds_per_block(1, lds_wave), &bpc);
     if (e != hipSuccess) return hip_fail(e, "occupancy");
+    if (bpc <= 0 && block_walk) return fail(HRR_E_DEVICE, "the block walk does not fit in LDS");   // it has no stack size
     if (bpc <= 0) return fail(HRR_E_INVALID, "stack of %u entries does not fit in LDS", cap);
     uint32_t task_shift = 0, sub_log = 0;
     if (block_walk)
