@@ -225,8 +225,8 @@ __device__ __forceinline__ void range_box(const float4* __restrict__ lights, con
 }
 
 // Bound by the scattered 64-byte stores and the lights' loads: 39 us for 2^20
-// lights (67 MB of records); the nodes and ranks before it 20 and 44 us, the
-// sort 204 us.  A build of 2^20 lights takes 0.49 ms against 3.9 ms with one
+// lights (67 MB of records); the nodes and ranks before it 20 and 36 .. 73 us,
+// the sort 210 us.  A build of 2^20 lights takes 0.49 ms against 3.9 ms with one
 // launch and one host wait per tree level.
 __global__ __launch_bounds__(256) void records_kernel(const uint2* __restrict__ range, const uint32_t* __restrict__ parent,
                                                       const uint32_t* __restrict__ first,
