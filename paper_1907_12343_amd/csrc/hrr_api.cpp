@@ -516,6 +516,17 @@ HRR_EXPORT hrr_status hrr_hierarchy_get_info(const hrr_hierarchy* h, hrr_hierarc
     return HRR_OK;
 }
 
+// Keep a host copy of what a second readback returned; without room for it the
+// next one reads the device again.
+template <typename T>
+static void keep_copy(std::vector<T>& copy, const T* data, size_t n) noexcept {
+    try {
+        copy.assign(data, data + n);
+    } catch (...) {
+        copy.clear();
+    }
+}
+
 HRR_EXPORT hrr_status hrr_hierarchy_permutation(const hrr_hierarchy* h, uint32_t* perm_out) {
     if (!h || (!perm_out && h->n_lights)) return fail(HRR_E_INVALID, "hrr_hierarchy_permutation: null argument");
     const size_t n = h->n_lights;
@@ -524,7 +535,7 @@ HRR_EXPORT hrr_status hrr_hierarchy_permutation(const hrr_hierarchy* h, uint32_t
         hipError_t e = hipSetDevice(h->owner->device);
         if (e == hipSuccess) e = hipMemcpy(perm_out, h->d_perm, n * sizeof(uint32_t), hipMemcpyDeviceToHost);
         if (e != hipSuccess) return hip_fail(e, "hierarchy download");
-        if (h->perm_read) h->perm.assign(perm_out, perm_out + n);
+        if (h->perm_read) keep_copy(h->perm, perm_out, n);
         h->perm_read = true;
         return HRR_OK;
     }
@@ -543,7 +554,7 @@ HRR_EXPORT hrr_status hrr_hierarchy_sorted_lights(const hrr_hierarchy* h, float*
         if (e != hipSuccess) return hip_fail(e, "hierarchy download");
         for (size_t i = 0; i < n; ++i)
             for (int k = 0; k < 3; ++k) sorted_xyz_out[3 * i + k] = l4[4 * i + k];
-        if (h->sorted_read) h->sorted_xyz.assign(sorted_xyz_out, sorted_xyz_out + 3 * n);
+        if (h->sorted_read) keep_copy(h->sorted_xyz, sorted_xyz_out, 3 * n);
         h->sorted_read = true;
         return HRR_OK;
     }

@@ -167,6 +167,23 @@ def test_repeated_readbacks_need_no_device_copy(ctx, device):
     ctx.free(h)
 
 
+def test_a_readback_without_room_for_its_copy(ctx):
+    """The host copy is a convenience: a full heap costs the next call a device
+    copy, not this one its result."""
+    n = 5000
+    h = ctx.hierarchy(n)
+    out = [np.zeros(n, np.uint32) for _ in range(4)]
+    assert ctx.lib.hrr_hierarchy_permutation(h, out[0].ctypes.data) == hrr.HRR_OK
+    ctx.lib.host_fail_new(0)
+    st = ctx.lib.hrr_hierarchy_permutation(h, out[1].ctypes.data)
+    ctx.lib.host_fail_new(-1)
+    assert st == hrr.HRR_OK
+    for o in out[2:]:
+        assert ctx.lib.hrr_hierarchy_permutation(h, o.ctypes.data) == hrr.HRR_OK
+    assert all(np.array_equal(o, out[0]) for o in out) and out[0].any()
+    ctx.free(h)
+
+
 def _server(ctx, budget):
     import ctypes
     cfg = hrr.HrrServerConfig(budget, 1, 1 << 16, 64, 0, 64.0, 100.0)
